@@ -20,9 +20,10 @@
 // which is what the back substitution of the gradient needs (L_tC^T x).
 //
 // Per tile column t:
-//   1. the owner of the diagonal tile factors it (one row per lane, 64-bit
-//      DPP row broadcasts) and publishes the strictly lower factor and the
-//      inverse pivots;
+//   1. the owner of the diagonal tile factors it in its registers, four
+//      columns at a time (one row per lane, 64-bit DPP row broadcasts, then a
+//      rank-4 update on the matrix core), and publishes the substitution
+//      weights -L[j][c] / L[c][c] and the inverse pivots;
 //   2. the owners of the tiles below solve X L_tt^T = A in registers by
 //      forward substitution over the 16 columns (column c of an N-layout
 //      tile lives in lane c of every 16-lane row, so each step is one DPP
@@ -55,23 +56,23 @@ __host__ __device__ constexpr int tiles_per_wave(int T, int W) { return (tile_co
 // LDS layout of the tiled kernel, in doubles.  The great-circle codes add
 // cos(latitude) of every row at the end; the other offsets do not depend on it.
 //
-// CUR[t % NPAR] receives diagonal tile t before its factorisation (row-major,
-// row stride 17) and then its strictly lower factor, with 1 / L_jj in
-// column 16 and again, contiguous, after the 16 x 17 block.  With several waves the buffer alternates by the parity of t:
-// the one tile t + 1 is stored into served column t - 1, whose readers all
-// passed a workgroup barrier since.  One array of T slots (DS doubles each)
-// serves both the panel and, with the gradient, the factored diagonal tiles:
-// while column t is processed, slot R > t holds the panel tile X_R (T-layout,
-// lane-major), and slot t' <= t holds factor t' in the CUR format, copied
-// there once every reader of X_t' has passed a barrier.
+// CUR[t % NPAR] receives the substitution weights of diagonal tile t
+// (row-major, row stride 17) and, after that block, its 16 inverse pivots.
+// With several waves the buffer alternates by the parity of t: the one tile
+// t + 1 is published into served column t - 1, whose readers all passed a
+// workgroup barrier since.  One array of T slots (DS doubles each) serves both
+// the panel and, with the gradient, the factored diagonal tiles: while column
+// t is processed, slot R > t holds the panel tile X_R (T-layout, lane-major),
+// and slot t' <= t holds factor t' in the CUR format, copied there once every
+// reader of X_t' has passed a barrier.
 //
 // A workgroup that evaluates G parameter vectors of one conditional in
 // lockstep keeps G copies of everything that depends on the parameters (CUR,
 // SLOT, YP, Q, UB, SCAL, RED); the gathered coordinates, observations and the
 // exponential table are shared.  G = 1 is the one-vector layout.  With one
 // wavefront per vector (INPLACE, also for G = 1) there is no CUR: the
-// wavefront stores diagonal tile t + 1 into slot t + 1 once its trailing
-// updates have read X_(t+1) there, and the tile is factored in place.
+// wavefront publishes factor t + 1 into slot t + 1 once its trailing updates
+// have read X_(t+1) there.
 template <int T, int W, bool GRAD, bool GCD = false, int G = 1>
 struct TileLds {
     static constexpr int KP = 16 * T;
@@ -318,14 +319,6 @@ __device__ __forceinline__ double augment_value(int a, int b, int k, double v, c
     return v;
 }
 
-// Stores an N-layout tile (lane (g, n), register r: M[4r + g][n]) row-major
-// with row stride 17 at D.
-__device__ __forceinline__ void store_rowmajor17(const dvec4 &v, double *D) {
-    const int l = threadIdx.x % kWave, g = l / 16, n = l % 16;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) D[(4 * r + g) * 17 + n] = v[r];
-}
-
 // Writes an N-layout tile to a panel slot in T-layout, lane-major: the reader
 // lane (g', j) finds M[j][4r' + g'] at slot[(16 g' + j) 4 + r'].  Element
 // (4r + g, n) of this lane goes to reader lane (n % 4, 4r + g), register n / 4.
@@ -335,127 +328,131 @@ __device__ __forceinline__ void store_panel_tlayout(const dvec4 &v, double *slot
     for (int r = 0; r < 4; ++r) slot[(16 * (n % 4) + 4 * r + g) * 4 + n / 4] = v[r];
 }
 
-// Factors diagonal tile t, which the calling wave has stored row-major (stride
-// 17) in D, in place: row j of D becomes the strictly lower part of row j of
-// the factor (zeros from column j on) and D[j][16] = 1 / L_jj.  Records L_kk
-// and the part of factor row k+1 that falls in this tile.  Every row is
-// factored: the padding rows have pivot 1 and the observation row's diagonal
-// is 2^600 (augment_value), so their pivots are positive and nothing past row
-// k reaches rows up to k.  A pivot that is not positive and finite turns
-// L_kk, and with it the conditional's value, into NaN, which the caller
-// reports.
-template <int T>
-__device__ __forceinline__ void factor_diag(int t, int k, double *D, double *scal, double *yp) {
+// The values of x in the four 16-lane row groups, each copied to every row
+// group: o[r] in lane (g, j) is x of lane (r, j).
+__device__ __forceinline__ void row_groups(double x, double (&o)[4]) {
+    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+    const unsigned int lo = (unsigned int)__double2loint(x), hi = (unsigned int)__double2hiint(x);
+    // 32-lane halves, then the two 16-lane rows of each half
+    const u32x2 l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    const u32x2 h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    const u32x2 l01 = __builtin_amdgcn_permlane16_swap(l[0], l[0], false, false);
+    const u32x2 h01 = __builtin_amdgcn_permlane16_swap(h[0], h[0], false, false);
+    const u32x2 l23 = __builtin_amdgcn_permlane16_swap(l[1], l[1], false, false);
+    const u32x2 h23 = __builtin_amdgcn_permlane16_swap(h[1], h[1], false, false);
+    o[0] = __hiloint2double((int)h01[0], (int)l01[0]);
+    o[1] = __hiloint2double((int)h01[1], (int)l01[1]);
+    o[2] = __hiloint2double((int)h23[0], (int)l23[0]);
+    o[3] = __hiloint2double((int)h23[1], (int)l23[1]);
+}
+
+// acc - a b over one 16 x 4 by 4 x 16 product (the matrix core negates its
+// first operand).
+__device__ __forceinline__ dvec4 mfma_sub(double a, double b, const dvec4 &acc) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 1);
+}
+
+// Factors diagonal tile t, held by the calling wave in N-layout registers
+// (the whole symmetric tile), four columns at a time, and publishes to D the
+// substitution weights W[j][c] = -L[j][c] / L[c][c] of the strictly lower part
+// (row-major, stride 17, zeros elsewhere) and the inverse pivots D[272 + c].
+// Records L_kk and the part of factor row k+1 that falls in this tile.
+//
+// Column block b (columns 4b .. 4b + 3): by symmetry rows 4b .. 4b + 3 of the
+// tile, register b, are its columns, so row-group copies of that register
+// give every lane j row j of the block.  The four columns are factored one
+// row per lane (DPP row broadcasts), the four row groups alike; each row
+// group g then selects column 4b + g, which is register b of the factor in
+// T-layout and both operands of the rank-4 update of the tile on the matrix
+// core.  Rows above the block hold rounding residue that nothing reads.
+// (One row per lane over all 16 columns, 120 broadcast FMAs and 16 row
+// registers, took 663 vector instructions per tile; this takes about 300 and
+// a dependency chain half as long.)
+//
+// Every row is factored: the padding rows have pivot 1 and the observation
+// row's diagonal is 2^600 (augment_value), so their pivots are positive and
+// nothing past row k reaches rows up to k.  A pivot that is not positive and
+// finite turns L_kk, and with it the conditional's value, into NaN, which the
+// caller reports.
+__device__ __forceinline__ void factor_diag(dvec4 A, int t, int k, double *D, double *scal, double *yp) {
     int l = threadIdx.x % kWave;
     asm volatile("" : "+v"(l));  // keep the lane masks below inside the tile loop (no hoisting)
     const int g = l / 16, j = l % 16;
+    const bool g1 = (g & 1) != 0, g2 = (g & 2) != 0;
+    const int base = 16 * t;
+    const bool has_k = (k >> 4) == t, has_y = ((k + 1) >> 4) == t;  // rows k and k + 1 lie in this tile
+    const int jk = k - base, jy = k + 1 - base;
     // this wave is the critical path of the workgroup: let it win instruction
     // issue over the other waves sharing its SIMD while it factors
     __builtin_amdgcn_s_setprio(3);
-    wave_lds_sync();
-    double R[16];
-#pragma unroll
-    for (int c = 0; c < 16; ++c) R[c] = D[j * 17 + c];
-    wave_lds_sync();
-
-    const int base = 16 * t;
-    const int jk = k - base;      // local index of row k (point i) if it lies in this tile
-    const int jy = k + 1 - base;  // local index of row k+1 (observations) if it lies in this tile
-    double myinv = 1.0;           // 1 / L[j][j], kept per lane as column j passes
-    static_for<0, 16>([&](auto qc) {
-        constexpr int q = decltype(qc)::value;
-        const double piv = bcast_row<q>(R[q]);
-        const double inv = rsqrt_refined(piv);
-        // column q of L: L[j][q] below the diagonal, L[q][q] = piv inv in
-        // lane q; the entries above the diagonal are never read
-        const double lq = R[q] * inv;
-        R[q] = lq;
-        // trailing update first, it carries the next pivot:
-        // R[c] -= L[j][q] L[c][q] with L[c][q] = lq of lane c
-        static_for<q + 1, 16>([&](auto cc) {
-            constexpr int c = decltype(cc)::value;
-            fms_bcast_row<c, c == q + 1>(R[c], lq, lq);
+    static_for<0, 4>([&](auto bc) {
+        constexpr int b = decltype(bc)::value;
+        double R[4], inv[4];
+        row_groups(A[b], R);
+        static_for<0, 4>([&](auto qc) {
+            constexpr int q = decltype(qc)::value;
+            inv[q] = rsqrt_refined(bcast_row<4 * b + q>(R[q]));
+            // column 4b + q of L: L[j][.] below the diagonal, piv inv in its own lane
+            const double lq = R[q] * inv[q];
+            R[q] = lq;
+            static_for<q + 1, 4>([&](auto cc) {
+                constexpr int c = decltype(cc)::value;
+                fms_bcast_row<4 * b + c, c == q + 1>(R[c], lq, lq);
+            });
         });
-        myinv = (j == q) ? inv : myinv;
-        // take the select here: sunk to the end it would keep all 16
-        // inverses live through the factorisation
-        asm volatile("" : "+v"(myinv));
+        // column 4b + g of row j, and its inverse pivot
+        const double L4 = g2 ? (g1 ? R[3] : R[2]) : (g1 ? R[1] : R[0]);
+        const double i4 = g2 ? (g1 ? inv[3] : inv[2]) : (g1 ? inv[1] : inv[0]);
+        if constexpr (b < 3) A = mfma_sub(L4, L4, A);
+        const int c = 4 * b + g;
+        D[j * 17 + c] = (j > c) ? -(L4 * i4) : 0.0;
+        if (j == 0) D[272 + c] = i4;
+        if (has_k && j == jk && c == jk) scal[0] = L4;
+        if (has_y && j == jy && c < jy) yp[base + c] = L4;
     });
-    // L_kk = 1 / (its refined reciprocal square-root pivot), within an ulp of
-    // pivot * rsqrt(pivot)
-    if (g == 0 && j == jk) scal[0] = 1.0 / myinv;
-    if (g == 0 && jy >= 0 && jy < 16 && j == jy) {
-#pragma unroll
-        for (int c = 0; c < 16; ++c)
-            if (c < jy) yp[base + c] = R[c];
-    }
-    // publish: the four row groups hold the same rows and write a quarter of
-    // the columns each
-#pragma unroll
-    for (int c = 0; c < 16; ++c)
-        if (c % 4 == g) D[j * 17 + c] = (c < j) ? R[c] : 0.0;
-    if (g == 0) D[j * 17 + 16] = myinv;
-    if (g == 1) D[272 + j] = myinv;
     __builtin_amdgcn_s_setprio(0);
 }
 
-// Forward substitution X L^T = A for the N-layout tiles x[0..P) held in
-// registers (row a of a tile in register a / 4 of row group a % 4, column n
-// in lane n): with the strictly lower factor Ls and the inverse pivots in D
-// (the CUR format), column c is final at step c, and column n > c loses
-// A[.][c] L[n][c] / L[c][c].  Column c of every row group sits in lane c of
-// that row, so each step is one DPP broadcast FMA per register; the inverse
-// pivots scale the columns at the end.  Backward stable like any triangular
-// substitution (no explicit inverse).  The weights of four steps are loaded
-// while the previous four steps run.
-template <int P>
-__device__ __forceinline__ void panel_solve(dvec4 (&x)[P], const double *D) {
+// Forward substitution X L^T = A for the N-layout tile x held in registers
+// (row a of the tile in register a / 4 of row group a % 4, column n in lane
+// n): with the weights W in D (factor_diag), column c is final at step c up to
+// its pivot, and column n > c gains A[.][c] W[n][c].  Column c of every row
+// group sits in lane c of that row, so each step is one DPP broadcast FMA per
+// register; the inverse pivots scale the columns at the end.  Backward stable
+// like any triangular substitution (no explicit inverse).  The weights of four
+// steps are loaded while the previous four steps run; the last column has
+// nothing to update.
+__device__ __forceinline__ void panel_solve(dvec4 &x, const double *D) {
     const int n = threadIdx.x % 16;
-    const double *Lrow = D + n * 17;  // row n of the strictly lower factor
-    const double *dinv = D + 272;     // 1 / L_cc, contiguous
-    double la[4], da[4], w[4];
+    const double *Wrow = D + n * 17;
+    double w[4], wn[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        la[q] = Lrow[q];
-        da[q] = dinv[q];
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) w[q] = -(la[q] * da[q]);
-    double xs[P][4];
-#pragma unroll
-    for (int p = 0; p < P; ++p)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) xs[p][r] = x[p][r];
+    for (int q = 0; q < 4; ++q) w[q] = Wrow[q];
+    const double dn = D[272 + n];
+    double xs[4] = {x[0], x[1], x[2], x[3]};
     static_for<0, 4>([&](auto gc) {
         constexpr int G = decltype(gc)::value;
         if constexpr (G < 3) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                la[q] = Lrow[4 * G + 4 + q];
-                da[q] = dinv[4 * G + 4 + q];
-            }
+            for (int q = 0; q < 4; ++q)
+                if (4 * G + 4 + q < 15) wn[q] = Wrow[4 * G + 4 + q];
         }
         static_for<0, 4>([&](auto qc) {
             constexpr int q = decltype(qc)::value;
             constexpr int c = 4 * G + q;
-            static_for<0, P>([&](auto pc) {
-                constexpr int p = decltype(pc)::value;
+            if constexpr (c < 15) {
                 // the first DPP read of a register follows its write by at least three instructions,
                 // except at the very first step
-                fma_bcast_row_self<c, c == 0 && p == 0>(xs[p][0], w[q]);
-                fma_bcast_row_self<c, false>(xs[p][1], w[q]);
-                fma_bcast_row_self<c, false>(xs[p][2], w[q]);
-                fma_bcast_row_self<c, false>(xs[p][3], w[q]);
-            });
+                fma_bcast_row_self<c, c == 0>(xs[0], w[q]);
+                fma_bcast_row_self<c, false>(xs[1], w[q]);
+                fma_bcast_row_self<c, false>(xs[2], w[q]);
+                fma_bcast_row_self<c, false>(xs[3], w[q]);
+            }
         });
-        if constexpr (G < 3) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) w[q] = -(la[q] * da[q]);
-        }
+        for (int q = 0; q < 4; ++q) w[q] = wn[q];
     });
-    const double dn = dinv[n];
-#pragma unroll
-    for (int p = 0; p < P; ++p) x[p] = dvec4{xs[p][0] * dn, xs[p][1] * dn, xs[p][2] * dn, xs[p][3] * dn};
+    x = dvec4{xs[0] * dn, xs[1] * dn, xs[2] * dn, xs[3] * dn};
 }
 
 // One conditional (modes as lds_conditional: qloc == NULL for the
@@ -624,7 +621,6 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
 #pragma unroll
             for (int r = 0; r < 4; ++r) tile[s][r] = augment_value(16 * R_ + 4 * r + g, b, k, tile[s][r], Z);
         }
-        if (R_ == 0 && C_ == 0) store_rowmajor17(tile[s], Ls::INPLACE ? SLOTq : CURq);
     }
     // every wavefront has read the shared distances before any writes a
     // panel tile over them
@@ -641,32 +637,30 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
         const int par = Ls::INPLACE ? t * DS : (Ls::NPAR == 2 ? (t & 1) : 0) * DS;
         double *D = (Ls::INPLACE ? SLOTq : CURq) + par;
         const bool diag_owner = w == tile_index(T, t, t) % W;
-        // 1. diagonal tile t (fully updated, stored to D by its owner)
-        if (diag_owner) factor_diag<T>(t, k, D, SCALq, YPq);
-        group_sync();
-        // the factor goes to slot t for the back substitution: the panel tile
-        // X_t it replaces was last read by the trailing update of column t - 1
-        if constexpr (GRAD && !Ls::INPLACE) {
-            if (diag_owner) {
-                double *St = SLOTq + t * DS;
-                for (int e = l; e < DS; e += kWave) St[e] = D[e];
-            }
+        // 1. diagonal tile t (fully updated, in its owner's registers)
+        if (diag_owner) {
+            dvec4 dt = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int s = 0; s < NTW; ++s)
+                if (SR(s) == t && SC(s) == t) {
+                    asm volatile("");  // a branch, not eight selects per slot
+                    dt = tile[s];
+                }
+            factor_diag(dt, t, k, D, SCALq, YPq);
         }
+        group_sync();
         // 2. tiles below: X = A L_t^-T by substitution, kept in registers
         // (N-layout, the factor tile itself) and published in T-layout
 #pragma unroll
         for (int s = 0; s < NTW; ++s) {
             if (SC(s) == t && SR(s) > t) {
-                dvec4 one[1] = {tile[s]};
-                panel_solve<1>(one, D);
-                tile[s] = one[0];
+                panel_solve(tile[s], D);
                 store_panel_tlayout(tile[s], SLOTq + SR(s) * DS);
             }
         }
         group_sync();
         // 3. trailing update of the tiles right of column t, the next diagonal
-        // tile first: it is then handed to the factorisation
-        double *Dn = CURq + (Ls::NPAR == 2 ? ((t + 1) & 1) : 0) * DS;
+        // tile first: it is what the next step waits for
 #pragma unroll
         for (int pass = 0; pass < 2; ++pass) {
 #pragma unroll
@@ -676,17 +670,18 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
                     const dvec4 xr = *reinterpret_cast<const dvec4 *>(SLOTq + SR(s) * DS + lo);
                     const dvec4 xc = *reinterpret_cast<const dvec4 *>(SLOTq + SC(s) * DS + lo);
 #pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        tile[s] = __builtin_amdgcn_mfma_f64_16x16x4f64(-xr[q], xc[q], tile[s], 0, 0, 0);
-                    if (nextdiag && !Ls::INPLACE) store_rowmajor17(tile[s], Dn);
+                    for (int q = 0; q < 4; ++q) tile[s] = mfma_sub(xr[q], xc[q], tile[s]);
                 }
             }
         }
-        if constexpr (Ls::INPLACE) {
-            // X_(t+1) in slot t + 1 has had its last reader (this wavefront)
-#pragma unroll
-            for (int s = 0; s < NTW; ++s)
-                if (SR(s) == t + 1 && SC(s) == t + 1) store_rowmajor17(tile[s], SLOTq + (t + 1) * DS);
+        // the factor goes to slot t for the back substitution: the panel tile
+        // X_t it replaces was last read by the trailing update of column
+        // t - 1, and the buffer it leaves is written again by column t + 2
+        if constexpr (GRAD && !Ls::INPLACE) {
+            if (diag_owner) {
+                double *St = SLOTq + t * DS;
+                for (int e = l; e < DS; e += kWave) St[e] = D[e];
+            }
         }
     }
     // observation row k+1 from the tiles left of its diagonal tile: row jy of
@@ -734,38 +729,30 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
         group_sync();
 #pragma unroll 1
         for (int t = T - 1; t >= 0; --t) {
-            const double *St = SLOTq + t * DS;  // strictly lower L_tt, 1 / L_jj in column 16
+            const double *St = SLOTq + t * DS;  // weights and inverse pivots of tile t
             if (w == tile_index(T, t, t) % W) {
-                double qv = (g < 2) ? Q[2 * (16 * t + j) + g] : 0.0;
-                // column c from the last: x_c = q_c / L_cc, then q_n -= L_cn x_c (n < c);
-                // weights -L[c][n] / L[c][c] (zero for n >= c), four steps loaded ahead
-                double la[4], da[4], wg[4];
+                // x_n = q_n / L_nn, then from the last column x_n += W[c][n] x_c (n < c; the
+                // weights W[c][n] = -L[c][n] / L[n][n] are zero for n >= c), four steps loaded ahead
+                double qv = (g < 2) ? Q[2 * (16 * t + j) + g] * St[272 + j] : 0.0;
+                double wg[4], wn[4];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    la[q] = St[(15 - q) * 17 + j];
-                    da[q] = St[272 + 15 - q];
-                }
-#pragma unroll
-                for (int q = 0; q < 4; ++q) wg[q] = -(la[q] * da[q]);
+                for (int q = 0; q < 4; ++q) wg[q] = St[(15 - q) * 17 + j];
                 static_for<0, 4>([&](auto gc) {
                     constexpr int S = decltype(gc)::value;  // steps 4S .. 4S + 3 from the last column
                     if constexpr (S < 3) {
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            la[q] = St[(11 - 4 * S - q) * 17 + j];
-                            da[q] = St[272 + 11 - 4 * S - q];
-                        }
+                        for (int q = 0; q < 4; ++q)
+                            if (11 - 4 * S - q > 0) wn[q] = St[(11 - 4 * S - q) * 17 + j];
                     }
                     static_for<0, 4>([&](auto qc) {
                         constexpr int q = decltype(qc)::value;
-                        fma_bcast_row_self<15 - 4 * S - q, true>(qv, wg[q]);
+                        constexpr int c = 15 - 4 * S - q;
+                        if constexpr (c > 0) fma_bcast_row_self<c, true>(qv, wg[q]);
                     });
-                    if constexpr (S < 3) {
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) wg[q] = -(la[q] * da[q]);
-                    }
+                    for (int q = 0; q < 4; ++q) wg[q] = wn[q];
                 });
-                if (g < 2) UB[2 * (16 * t + j) + g] = qv * St[272 + j];
+                if (g < 2) UB[2 * (16 * t + j) + g] = qv;
             }
             group_sync();
             if (t > 0) {
