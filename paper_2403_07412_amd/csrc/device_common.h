@@ -111,23 +111,6 @@ __device__ __forceinline__ double exp_neg_tab(double r, const double *tab) {
     return __builtin_ldexp(t.x + fma(t.x, q, t.y), n >> 6);
 }
 
-// sqrt(s) for a squared distance s >= 0 without a branch: s is raised by
-// 2^-1000 (below half an ulp of any s >= 2^-946, so other distances are
-// unchanged) so that the reciprocal square root never sees 0; coincident
-// points get distance 2^-500, whose covariance is the zero-distance value to
-// the last bit.  Then the coupled Newton refinement of sqrt_dist.
-__device__ __forceinline__ double sqrt_pos(double s) {
-    s += 0x1p-1000;
-    const double y = __builtin_amdgcn_rsq(s);
-    double g = s * y;
-    double h = 0.5 * y;
-    const double e = fma(-h, g, 0.5);
-    g = fma(g, e, g);
-    h = fma(h, e, h);
-    const double d = fma(-g, g, s);
-    return fma(d, h, g);
-}
-
 // sin x.  Neighbouring points give half-angle differences far below 0.25
 // rad, where the Taylor polynomial to x^13 is used (truncation below 1e-21
 // relative, Horner in x^2, one rounding at the end); larger arguments take
@@ -205,55 +188,133 @@ __device__ __forceinline__ double cov_scaled(double d, const Params &P, const do
     return dist_pow<KC>(d, P, tab) * P.inv_beta;
 }
 
-// dist_pow of the distance between points a and b (cos of the latitudes in
-// ca, cb for the great-circle codes).  The coordinates must be finite.
+// ---- the tiled kernel's forms -------------------------------------------------
+//
+// The exponential of exp_neg_tab rearranged for fewer instructions (15 against
+// 19; the tiled kernels evaluate it for every pair and are bound by vector
+// issue).  Entry j of the staged table holds hi = 2^(j/64) with j 2^14
+// subtracted from its high word, and lo / hi: adding n 2^14 = k 2^20 + j 2^14
+// to the high word then scales hi by 2^k in one integer instruction, and the
+// low part joins e^f - 1 in the polynomial's last step.  n = rint(64 x / ln2)
+// is the low word of 64 x / ln2 + 1.5 2^52.
+__device__ __forceinline__ void stage_exp_entry(int j, double *tab) {
+    const ExpTableEntry e = kExp2Frac64[j];
+    tab[2 * j] = __hiloint2double(__double2hiint(e.hi) - (j << 14), __double2loint(e.hi));
+    tab[2 * j + 1] = e.lo * __builtin_amdgcn_rcp(e.hi);  // |lo / hi| < 2^-53: the estimate is plenty
+}
+
+// e^-r for r >= -709, one rounding at the end (just above half an ulp, as
+// exp_neg_tab).  Arguments beyond 708 give e^-708 (3e-308), NaN as well, so
+// callers validate their inputs.
+__device__ __forceinline__ double exp_neg_staged(double r, const double *tab) {
+    r = fmin(r, 708.0);
+    const double t = fma(r, -0x1.71547652b82fep+6, 0x1.8p52);  // 64 / ln2
+    const int n = __double2loint(t);
+    const double nf = t - 0x1.8p52;
+    double f = fma(nf, -0x1.62e42fefa0000p-7, -r);  // head of ln2/64
+    f = fma(nf, -0x1.cf79abc9e3b3ap-46, f);         // tail of ln2/64
+    double q = fma(f, 1.0 / 720.0, 1.0 / 120.0);
+    q = fma(q, f, 1.0 / 24.0);
+    q = fma(q, f, 1.0 / 6.0);
+    q = fma(q, f, 0.5);
+    q = fma(q, f, 1.0);
+    const double2 e = *reinterpret_cast<const double2 *>(tab + 2 * (n & 63));
+    const double hi = __hiloint2double(__double2hiint(e.x) + (n << 14), __double2loint(e.x));
+    return fma(hi, fma(q, f, e.y), hi);
+}
+
+// Distance of two points from their coordinate differences, without a branch:
+// the square is raised by 2^-1000 (below half an ulp of any square from 2^-946
+// up, so other distances are unchanged) so that the reciprocal square root
+// never sees 0; coincident points get distance 2^-500, whose covariance is the
+// zero-distance value to the last bit.  One coupled Newton step and one
+// correction by the residual, as in sqrt_dist, but without the refinement of
+// 1/(2 sqrt): the correction is a factor 2^-47 of the result and the hardware
+// estimate serves it.
+__device__ __forceinline__ double dist_pos(double dx, double dy) {
+    const double s = fma(dx, dx, fma(dy, dy, 0x1p-1000));
+    const double y = __builtin_amdgcn_rsq(s);
+    double g = s * y;
+    const double h = 0.5 * y;
+    g = fma(g, fma(-h, g, 0.5), g);
+    return fma(fma(-g, g, s), h, g);
+}
+
+// log x for positive normal x: x = 2^e m with m in [sqrt(1/2), sqrt 2),
+// log m = 2 atanh(s), s = (m - 1) / (m + 1), by the odd Taylor series to s^21
+// (truncation below 2^-55 relative at |s| <= 0.1716).  About 40 instructions;
+// NaN and non-positive arguments give NaN.
+__device__ __forceinline__ double log_pos(double x) {
+    double m = __builtin_amdgcn_frexp_mant(x);
+    int e = __builtin_amdgcn_frexp_exp(x);
+    const bool low = m < 0x1.6a09e667f3bcdp-1;
+    m = low ? m + m : m;
+    e = low ? e - 1 : e;
+    const double f = m - 1.0, d = m + 1.0;
+    double y = __builtin_amdgcn_rcp(d);
+    y = fma(fma(-d, y, 1.0), y, y);
+    y = fma(fma(-d, y, 1.0), y, y);
+    double s = f * y;
+    s = fma(fma(-s, d, f), y, s);
+    const double z = s * s;
+    double p = fma(z, 1.0 / 21.0, 1.0 / 19.0);
+    p = fma(p, z, 1.0 / 17.0);
+    p = fma(p, z, 1.0 / 15.0);
+    p = fma(p, z, 1.0 / 13.0);
+    p = fma(p, z, 1.0 / 11.0);
+    p = fma(p, z, 1.0 / 9.0);
+    p = fma(p, z, 1.0 / 7.0);
+    p = fma(p, z, 1.0 / 5.0);
+    p = fma(p, z, 1.0 / 3.0);
+    const double s2 = s + s;
+    const double lm = fma(s2 * z, p, s2);
+    const double k = (double)e;
+    // ln2 as a 32-bit head (k head is exact) and a tail
+    const double r = fma(k, 0x1.62e42fee00000p-1, fma(k, 0x1.a39ef35793c76p-33, lm));
+    return x > 0.0 ? r : __builtin_nan("");
+}
+
+// The parameter-free part of the scaled distance for a pair of points (cos of
+// the latitudes in ca, cb for the great-circle codes): d, or d^alpha for the
+// power exponential (0 at d = 0).  The coordinates must be finite.
 template <int KC>
 __device__ __forceinline__ double pair_dist_pow(double xa, double ya, double ca, double xb, double yb, double cb,
                                                 const Params &P, const double *tab) {
-    if constexpr (kc_gcd(KC)) {
-        return dist_pow<KC>(gcd_km(xa, ya, ca, xb, yb, cb), P, tab);
-    } else {
-        const double dx = xa - xb, dy = ya - yb;
-        return dist_pow<KC>(sqrt_pos(fma(dx, dx, dy * dy)), P, tab);
+    double d;
+    if constexpr (kc_gcd(KC)) d = gcd_km(xa, ya, ca, xb, yb, cb);
+    else d = dist_pos(xa - xb, ya - yb);
+    if constexpr (kc_family(KC) == 3) {
+        if (P.alpha == 2.0) d = d * d;
+        else if (P.alpha != 1.0) d = (d > 0.0) ? exp_neg_staged(-(P.alpha * log(d)), tab) : 0.0;
     }
+    return d;
 }
 
-// Covariance C and, with WITH_D, its beta-derivative from da = dist_pow of
-// the pair's distance, using exp_neg_tab.  With r = da / beta the scaled
-// distance, the Matern forms are sigma2 m(r) and sigma2 h(r) / beta (h as in
-// matern_dbeta_r); the power exponential is sigma2 e^-r with derivative
-// sigma2 r e^-r / beta, the nu = 1/2 form.
-template <int KC, bool WITH_D>
-__device__ __forceinline__ void cov_from_dist(double da, const Params &P, double s2b, const double *tab, double &c,
-                                              double &db) {
-    double r = da * P.inv_beta;
+// Covariance from da = pair_dist_pow: sigma2 e^-r, sigma2 (1 + r) e^-r,
+// sigma2 (1 + r + r^2 / 3) e^-r with r = da / beta.  Every sum is an explicit
+// FMA: kernels that share distances between parameter vectors must give the
+// bits of those that do not, so nothing is left for the compiler to contract
+// in one kernel and not in another.
+template <int KC>
+__device__ __forceinline__ double cov_value(double r, double e, const Params &P) {
     constexpr int F = kc_family(KC);
-    // for nu = 3/2 and 5/2, r is opaque to the optimiser: 1 + r below could
-    // be fused with the product that forms r in one kernel and not in another
-    // (it was, for nu = 3/2 on great-circle distances), and kernels that share
-    // distances between parameter vectors must give the bits of those that do
-    // not
-    if constexpr (F == 1 || F == 2) asm volatile("" : "+v"(r));
-    const double e = exp_neg_tab(r, tab);
-    if constexpr (F == 0 || F == 3) {
-        c = P.sigma2 * e;
-        if constexpr (WITH_D) db = s2b * (r * e);
-    } else if constexpr (F == 1) {
-        c = P.sigma2 * ((1.0 + r) * e);
-        if constexpr (WITH_D) db = s2b * ((r * r) * e);
-    } else {
-        c = P.sigma2 * ((1.0 + r * (1.0 + r * (1.0 / 3.0))) * e);
-        if constexpr (WITH_D) db = s2b * ((r * r) * (1.0 + r) * (1.0 / 3.0) * e);
-    }
+    if constexpr (F == 1) return fma(r, P.sigma2, P.sigma2) * e;
+    else if constexpr (F == 2) return fma(r, fma(r, P.sigma2 * (1.0 / 3.0), P.sigma2), P.sigma2) * e;
+    else return P.sigma2 * e;
 }
 
-// Covariance C(d) and, with WITH_D, its beta-derivative for points a and b
-// (cos of the latitudes in ca, cb for the great-circle codes).  The
-// coordinates must be finite.
-template <int KC, bool WITH_D>
-__device__ __forceinline__ void cov_pair(double xa, double ya, double ca, double xb, double yb, double cb,
-                                         const Params &P, double s2b, const double *tab, double &c, double &db) {
-    cov_from_dist<KC, WITH_D>(pair_dist_pow<KC>(xa, ya, ca, xb, yb, cb, P, tab), P, s2b, tab, c, db);
+// The beta-derivative of the covariance up to the pair-independent factor
+// dbeta_scale: r e^-r, r^2 e^-r, (r^2 + r^3) e^-r.
+template <int KC>
+__device__ __forceinline__ double dbeta_raw(double r, double e) {
+    constexpr int F = kc_family(KC);
+    if constexpr (F == 1) return (r * r) * e;
+    else if constexpr (F == 2) return fma(r * r, r, r * r) * e;
+    else return r * e;
+}
+template <int KC>
+__device__ __forceinline__ double dbeta_scale(const Params &P) {
+    return (P.sigma2 * P.inv_beta) * (kc_family(KC) == 2 ? 1.0 / 3.0 : 1.0);
 }
 
 // Closed forms in the scaled distance r: Matern, Eq. (2), for half-integer

@@ -15,9 +15,7 @@
 // holding M[j][4r + g]) is the one panel tiles take in LDS, because as
 // either MFMA operand a T-layout tile X enters a product directly:
 //   SYRK   A_RC -= X_R X_C^T   operands -X_R and X_C, register s of each,
-//                              accumulating straight into the N-layout tile;
-// and an N-layout tile passed as the first operand enters as its transpose,
-// which is what the back substitution of the gradient needs (L_tC^T x).
+//                              accumulating straight into the N-layout tile.
 //
 // Per tile column t:
 //   1. the owner of the diagonal tile factors it in its registers, four
@@ -31,9 +29,9 @@
 //   3. the owners of the trailing tiles subtract X_R X_C^T (4 MFMAs per
 //      tile), the next diagonal tile first, so that its factorisation
 //      overlaps the other updates of the column.
-// Gradient: back substitution with L^T by tiles: x_t = L_tt^-T q_t by
-// substitution (one wave), then q_C -= L_tC^T x_t on the matrix cores for
-// the tiles of row t.  No step multiplies by an explicit inverse, so every
+// Gradient: back substitution with L^T by columns of tiles: the sums of
+// L_Rt^T x_R over the tiles below diagonal tile t on the vector units (every
+// wave its own tiles), then x_t by substitution (one wave).  No step multiplies by an explicit inverse, so every
 // solve is backward stable, as in the unblocked kernel.
 #pragma once
 
@@ -68,7 +66,7 @@ __host__ __device__ constexpr int tiles_per_wave(int T, int W) { return (tile_co
 //
 // A workgroup that evaluates G parameter vectors of one conditional in
 // lockstep keeps G copies of everything that depends on the parameters (CUR,
-// SLOT, YP, Q, UB, SCAL, RED); the gathered coordinates, observations and the
+// SLOT, YP, UB, SCAL, RED); the gathered coordinates, observations and the
 // exponential table are shared.  G = 1 is the one-vector layout.  With one
 // wavefront per vector (INPLACE, also for G = 1) there is no CUR: the
 // wavefront publishes factor t + 1 into slot t + 1 once its trailing updates
@@ -84,11 +82,10 @@ struct TileLds {
     static constexpr int XY = SLOT + G * T * DS;          // [KP][2]        coordinates
     static constexpr int ZV = XY + 2 * KP;                // [KP]           observations
     static constexpr int YP = ZV + KP;                    // [G][KP]        factor row k+1
-    static constexpr int Q = YP + G * KP;                 // [G][KP][2]     back-substitution right-hand sides (gradient),
-    static constexpr int UB = Q;                          //                overwritten in place by the solutions (u, b)
-    static constexpr int SCAL = Q + (GRAD ? G * 2 * KP : 0);  // [G][16]    scalars: [0] L_kk
+    static constexpr int UB = YP + G * KP;                // [G][KP][2]     back-substitution solutions (u, b), gradient
+    static constexpr int SCAL = UB + (GRAD ? G * 2 * KP : 0);  // [G][16]   scalars: [0] L_kk, [1] 1 / L_kk
     static constexpr int RED = SCAL + G * 16;             // [G][2][4W]     reductions (two values, W waves x 4 rows)
-    static constexpr int EXPT = RED + G * 8 * W;          // [64][2]        2^(j/64) as hi, lo for exp_neg_tab
+    static constexpr int EXPT = RED + G * 8 * W;          // [64][2]        2^(j/64) for exp_neg_staged
     static constexpr int CL = EXPT + 2 * kExpTableSize;   // [KP]           cos(latitude) (great-circle codes only)
     static constexpr int TOTAL = CL + (GCD ? KP : 0);
     static constexpr size_t BYTES = (size_t)TOTAL * sizeof(double);
@@ -176,21 +173,27 @@ __host__ __device__ constexpr bool keep_dbeta(int T, int W, bool gcd = false) {
 
 // Tile enumeration: column C descending, row R ascending inside a column, so
 // the tiles still active after step t form a prefix and a round-robin owner
-// assignment balances every step.
-__device__ inline void tile_rc(int T, int idx, int &R, int &C) {
-    int start = 0;
-    R = -1;
-    C = -1;
-    for (int c = T - 1; c >= 0; --c) {
-        const int cnt = T - c;
-        if (idx < start + cnt) {
-            C = c;
-            R = c + (idx - start);
-            return;
-        }
-        start += cnt;
+// assignment balances every step.  Slot s of wavefront w holds tile w + W s;
+// its (R, C) is byte s of the wavefront's row of the map, R in the high four
+// bits.  Slots past the last tile read as (0, 15), a column no step reaches.
+template <int T, int W>
+struct TileMap {
+    static constexpr int WORDS = (tiles_per_wave(T, W) + 3) / 4;
+    uint32_t word[W][WORDS];
+    constexpr TileMap() : word{} {
+        for (int w = 0; w < W; ++w)
+            for (int q = 0; q < WORDS; ++q) word[w][q] = 0x0F0F0F0Fu;
+        int idx = 0;
+        for (int c = T - 1; c >= 0; --c)
+            for (int r = c; r < T; ++r, ++idx) {
+                const int sh = 8 * ((idx / W) % 4);
+                uint32_t &x = word[idx % W][idx / W / 4];
+                x = (x & ~(0xFFu << sh)) | ((uint32_t)(r * 16 + c) << sh);
+            }
     }
-}
+};
+template <int T, int W>
+__device__ constexpr TileMap<T, W> kTileMap = TileMap<T, W>();
 
 __device__ inline int tile_index(int T, int R, int C) {
     // tiles of columns T-1 .. C+1 come first
@@ -275,29 +278,10 @@ __device__ __forceinline__ double row_sum16(double v) {
     return v;
 }
 
-// Sums of two values over the W wavefronts of a parameter vector's group in a
-// fixed order (rows, then rows of waves in ascending order); every thread of
-// the group gets both totals.  `red` holds 2 * 4W doubles per group.  Every
-// wavefront of the workgroup calls it together.
-template <int W>
-__device__ __forceinline__ void block_sum2(double &a, double &b, double *red) {
-    const int l = threadIdx.x % kWave, w = (threadIdx.x / kWave) % W;
-    a = row_sum16(a);
-    b = row_sum16(b);
-    __syncthreads();
-    if (l % 16 == 0) {
-        red[4 * w + l / 16] = a;
-        red[4 * W + 4 * w + l / 16] = b;
-    }
-    __syncthreads();
-    double sa = 0.0, sb = 0.0;
-#pragma unroll
-    for (int i = 0; i < 4 * W; ++i) {
-        sa += red[i];
-        sb += red[4 * W + i];
-    }
-    a = sa;
-    b = sb;
+// The value of v in one lane, uniform over the wavefront.
+__device__ __forceinline__ double read_lane(double v, int lane) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                            __builtin_amdgcn_readlane(__double2loint(v), lane));
 }
 
 __device__ __forceinline__ void wave_lds_sync() {
@@ -346,6 +330,18 @@ __device__ __forceinline__ void row_groups(double x, double (&o)[4]) {
     o[3] = __hiloint2double((int)h23[1], (int)l23[1]);
 }
 
+// Sums of x and of y over the four row groups: row groups 0 and 1 end with
+// the sum of x, row groups 2 and 3 with the sum of y.
+__device__ __forceinline__ double sum_row_groups2(double x, double y) {
+    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+    u32x2 l = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(x), (unsigned)__double2loint(y), false, false);
+    u32x2 h = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(x), (unsigned)__double2hiint(y), false, false);
+    x = __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+    l = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(x), (unsigned)__double2loint(x), false, false);
+    h = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(x), (unsigned)__double2hiint(x), false, false);
+    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+}
+
 // acc - a b over one 16 x 4 by 4 x 16 product (the matrix core negates its
 // first operand).
 __device__ __forceinline__ dvec4 mfma_sub(double a, double b, const dvec4 &acc) {
@@ -356,7 +352,8 @@ __device__ __forceinline__ dvec4 mfma_sub(double a, double b, const dvec4 &acc) 
 // (the whole symmetric tile), four columns at a time, and publishes to D the
 // substitution weights W[j][c] = -L[j][c] / L[c][c] of the strictly lower part
 // (row-major, stride 17, zeros elsewhere) and the inverse pivots D[272 + c].
-// Records L_kk and the part of factor row k+1 that falls in this tile.
+// Records L_kk, its inverse and the part of factor row k+1 that falls in this
+// tile.
 //
 // Column block b (columns 4b .. 4b + 3): by symmetry rows 4b .. 4b + 3 of the
 // tile, register b, are its columns, so row-group copies of that register
@@ -407,7 +404,10 @@ __device__ __forceinline__ void factor_diag(dvec4 A, int t, int k, double *D, do
         const int c = 4 * b + g;
         D[j * 17 + c] = (j > c) ? -(L4 * i4) : 0.0;
         if (j == 0) D[272 + c] = i4;
-        if (has_k && j == jk && c == jk) scal[0] = L4;
+        if (has_k && j == jk && c == jk) {
+            scal[0] = L4;
+            scal[1] = i4;
+        }
         if (has_y && j == jy && c < jy) yp[base + c] = L4;
     });
     __builtin_amdgcn_s_setprio(0);
@@ -484,8 +484,8 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
     constexpr int DS = Ls::DS;
     const int tid = threadIdx.x;
     const int wg = __builtin_amdgcn_readfirstlane(tid / kWave);
-    const int w = G > 1 ? wg % W : wg;   // wavefront within the vector's group
-    const int wq = G > 1 ? wg / W : 0;   // the group's parameter vector
+    const int w = W == 1 ? 0 : (G > 1 ? wg % W : wg);  // wavefront within the vector's group
+    const int wq = G > 1 ? wg / W : 0;                 // the group's parameter vector
     const int tg = tid % NTG;            // thread within the group
     double *const CURq = smem + Ls::CUR + wq * Ls::CUR_G;
     double *const SLOTq = smem + Ls::SLOT + wq * Ls::SLOT_G;
@@ -508,33 +508,31 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
     double *XY = smem + Ls::XY;
     double *Z = smem + Ls::ZV;
     double *CLv = smem + Ls::CL;
-    bool bad = false;
 
-    // my tiles: slot s holds tile index w + W s; (R, C) packed as R * 32 + C, -1 if unused
-    int sRC[NTW];
+    // my tiles (TileMap); with one wavefront per vector all of this is known
+    // at compile time
+    uint32_t tmap[TileMap<T, W>::WORDS];
 #pragma unroll
-    for (int s = 0; s < NTW; ++s) {
-        const int idx = w + W * s;
-        int R_ = -1, C_ = -1;
-        if (idx < NTILES) tile_rc(T, idx, R_, C_);
-        sRC[s] = (R_ < 0) ? -1 : R_ * 32 + C_;
-    }
-#define SR(s) (sRC[s] < 0 ? -1 : (sRC[s] >> 5))
-#define SC(s) (sRC[s] < 0 ? -1 : (sRC[s] & 31))
+    for (int q = 0; q < TileMap<T, W>::WORDS; ++q)
+        tmap[q] = W == 1 ? kTileMap<T, W>.word[0][q] : (uint32_t)__builtin_amdgcn_readfirstlane((int)kTileMap<T, W>.word[w][q]);
+#define SR(s) ((int)((tmap[(s) / 4] >> (8 * ((s) % 4) + 4)) & 15u))
+#define SC(s) ((int)((tmap[(s) / 4] >> (8 * ((s) % 4))) & 15u))
+#define SVALID(s) (W * ((s) + 1) <= NTILES || w + W * (s) < NTILES)
 
-    __syncthreads();  // the previous conditional is done with smem
-    // gather (Algorithm 1: s_{J_i}, y_{J_i}); indices are checked before use
-    // and non-finite inputs flag the conditional (the covariance code below
-    // assumes finite coordinates)
+    // gather (Algorithm 1: s_{J_i}, y_{J_i}); indices are checked before use.
+    // An index out of range or a non-finite input turns the row's observation
+    // into NaN, which the forward solve carries into the conditional's value
+    // (that is how it is reported); its coordinates become 0, since the
+    // covariance code below assumes finite ones.
     for (int t = tid; t < KP; t += NT) {
         double x = 0.0, y = 0.0, zz = 0.0;
         if (t <= k) {
             int64_t jj = i;
+            bool ok = true;
             if (t < k) {
                 const int32_t jn = nbr[i * (int64_t)m + t];
-                const bool okj = (jn >= 0) && ((int64_t)jn < lim);
-                bad |= !okj;
-                jj = okj ? (int64_t)jn : 0;
+                ok = (jn >= 0) && ((int64_t)jn < lim);
+                jj = ok ? (int64_t)jn : 0;
             }
             if (t == k && qloc) {  // prediction point, observation taken as 0
                 x = qloc[0];
@@ -545,17 +543,17 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
                 y = p.y;
                 zz = z[jj];
             }
-            bad |= !(isfinite(x) && isfinite(y) && isfinite(zz));
+            ok = ok && isfinite(x) && isfinite(y) && isfinite(zz);
+            x = ok ? x : 0.0;
+            y = ok ? y : 0.0;
+            zz = ok ? zz : __builtin_nan("");
         }
         XY[2 * t] = x;
         XY[2 * t + 1] = y;
         Z[t] = zz;
         if constexpr (GCD) CLv[t] = cos(y * kDeg2Rad);
     }
-    if (tid < kExpTableSize) {
-        smem[Ls::EXPT + 2 * tid] = kExp2Frac64[tid].hi;
-        smem[Ls::EXPT + 2 * tid + 1] = kExp2Frac64[tid].lo;
-    }
+    if (tid < kExpTableSize) stage_exp_entry(tid, smem + Ls::EXPT);
     __syncthreads();
 
     // covariance generation straight into the N-layout register tiles: lane
@@ -568,7 +566,6 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
     const double *ET = smem + Ls::EXPT;
     dvec4 tile[NTW];
     dvec4 dtile[KEEP_D ? NTW : 1];
-    const double s2b = P.sigma2 * P.inv_beta;
     // With one wavefront per vector (INPLACE) every group needs the same
     // distances: each group's wavefront evaluates those of every G-th (tile,
     // register) pair, 64 lanes at a time, into the panel slots past slot 0,
@@ -598,24 +595,26 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
         tile[s] = dvec4{0.0, 0.0, 0.0, 0.0};
         if constexpr (KEEP_D) dtile[s] = dvec4{0.0, 0.0, 0.0, 0.0};
         const int R_ = SR(s), C_ = SC(s);
-        if (R_ < 0) continue;
+        if (!SVALID(s)) continue;
         const int b = 16 * C_ + j;
         const double xb = XY[2 * b], yb = XY[2 * b + 1], cb = GCD ? CLv[b] : 0.0;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int a = 16 * R_ + 4 * r + g;
-            double cv, db;
+            double da;
             if constexpr (SHARE_D)
-                cov_from_dist<KC, KEEP_D>(dslot(4 * s + r)[l], P, s2b, ET, cv, db);
+                da = dslot(4 * s + r)[l];
             else
-                cov_pair<KC, KEEP_D>(XY[2 * a], XY[2 * a + 1], GCD ? CLv[a] : 0.0, xb, yb, cb, P, s2b, ET, cv, db);
-            tile[s][r] = cv;
-            if constexpr (KEEP_D) dtile[s][r] = db;
+                da = pair_dist_pow<KC>(XY[2 * a], XY[2 * a + 1], GCD ? CLv[a] : 0.0, xb, yb, cb, P, ET);
+            const double rs = da * P.inv_beta;
+            const double e = exp_neg_staged(rs, ET);
+            tile[s][r] = cov_value<KC>(rs, e, P);
+            if constexpr (KEEP_D) dtile[s][r] = dbeta_raw<KC>(rs, e);
         }
         if (R_ == C_) {
+            asm volatile("");  // a branch: the selects cost more than it
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (16 * R_ + 4 * r + g == b) tile[s][r] += P.tau2;
+            for (int r = 0; r < 4; ++r) tile[s][r] = (4 * r + g == j) ? tile[s][r] + P.tau2 : tile[s][r];
         }
         if (16 * R_ + 15 > k) {
 #pragma unroll
@@ -627,6 +626,7 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
     if constexpr (SHARE_D) __syncthreads();
 
     // blocked right-looking Cholesky
+    const int ty = (k + 1) / 16, jy = (k + 1) % 16;  // the observation row's tile row, and its row there
 #pragma unroll 1
     for (int t = 0; t < T; ++t) {
         // the lane's offset inside a tile slot, opaque to the compiler in every
@@ -659,20 +659,20 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
             }
         }
         group_sync();
-        // 3. trailing update of the tiles right of column t, the next diagonal
-        // tile first: it is what the next step waits for
+        // 3. trailing update of the tiles right of column t
 #pragma unroll
-        for (int pass = 0; pass < 2; ++pass) {
+        for (int s = 0; s < NTW; ++s) {
+            if (SC(s) > t && SVALID(s)) {
+                const dvec4 xr = *reinterpret_cast<const dvec4 *>(SLOTq + SR(s) * DS + lo);
+                const dvec4 xc = *reinterpret_cast<const dvec4 *>(SLOTq + SC(s) * DS + lo);
 #pragma unroll
-            for (int s = 0; s < NTW; ++s) {
-                const bool nextdiag = SR(s) == t + 1 && SC(s) == t + 1;
-                if (SC(s) > t && (pass == 0) == nextdiag) {
-                    const dvec4 xr = *reinterpret_cast<const dvec4 *>(SLOTq + SR(s) * DS + lo);
-                    const dvec4 xc = *reinterpret_cast<const dvec4 *>(SLOTq + SC(s) * DS + lo);
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) tile[s] = mfma_sub(xr[q], xc[q], tile[s]);
-                }
+                for (int q = 0; q < 4; ++q) tile[s] = mfma_sub(xr[q], xc[q], tile[s]);
             }
+        }
+        // the part of the observation row that lies in this column: row jy of
+        // X_ty, entry c in T-layout at lane (c % 4, jy), register c / 4
+        if (w == W - 1 && t < ty) {
+            if (l < 16) YPq[16 * t + l] = SLOTq[ty * DS + (16 * (l % 4) + jy) * 4 + l / 4];
         }
         // the factor goes to slot t for the back substitution: the panel tile
         // X_t it replaces was last read by the trailing update of column
@@ -684,56 +684,72 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
             }
         }
     }
-    // observation row k+1 from the tiles left of its diagonal tile: row jy of
-    // an N-layout tile is register jy / 4 of row group jy % 4
-    const int ty = (k + 1) / 16, jy = (k + 1) % 16;
-#pragma unroll
-    for (int s = 0; s < NTW; ++s) {
-        if (SR(s) == ty && SC(s) < ty) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (4 * r + g == jy) YPq[16 * SC(s) + j] = tile[s][r];
-        }
-    }
     group_sync();
 
     CondOut o;
-    const double Lkk = SCALq[0];
+    const double Lkk = SCALq[0], invk = SCALq[1];
     const double wv = YPq[k];
-    o.ell = -0.5 * (kLog2Pi + 2.0 * log(Lkk) + wv * wv);
     o.g0 = o.g1 = o.g2 = 0.0;
-    o.var = Lkk * Lkk;
-    o.mean = Z[k] - wv * Lkk;
 
     if constexpr (GRAD) {
-        const double c = Lkk * Lkk;
-        const double rr = wv / Lkk;
-        const double half = 0.5 * (rr * rr - 1.0 / c);
-        // back substitution with L^T for both right-hand sides at once.  Q
-        // holds (q_u, q_b) pairs, and (u, b) replace them in place (UB is
-        // the same array): block t of q is read only by the solve that
-        // writes block t of the solution, and later updates touch blocks
-        // C < t only.  Per tile row t, from the last: the owner of the
-        // diagonal tile solves L_tt^T x_t = q_t by substitution (lanes of row
-        // groups 0 and 1 hold the two right-hand sides, lane n entry n), then
-        // the owners of the tiles (t, C), C < t, subtract L_tC^T x_t from q_C
-        // on the matrix cores: an N-layout tile as the first operand enters
-        // as its transpose, and x_t as the second operand sits in lanes
-        // (g, j < 2), register q holding x_j[4q + g].
-        double *Q = smem + Ls::Q + wq * Ls::QUB_G, *UB = smem + Ls::UB + wq * Ls::QUB_G;
-        const double *YP = YPq;
-        for (int t = tg; t < KP; t += NTG) {
-            Q[2 * t] = (t < k) ? rr * YP[t] : (t == k ? half * Lkk : 0.0);
-            Q[2 * t + 1] = (t == k) ? Lkk : 0.0;
-        }
-        group_sync();
+        const double rr = wv * invk;
+        const double half = 0.5 * fma(rr, rr, -(invk * invk));
+        // back substitution with L^T for both right-hand sides at once, by
+        // columns of tiles from the last: x_t = L_tt^-T (q_t - sum_{R > t}
+        // L_Rt^T x_R).  The right-hand sides are q_u = rr y' (y' the
+        // observation row of the factor), half L_kk at k, and q_b = L_kk e_k.
+        // The sums are taken on the vector units (lane (g, n), register r of
+        // an N-layout tile is L[4r + g][n], so a lane's four rows meet the
+        // four solution values of its row group: 8 FMAs per tile for both
+        // right-hand sides, where a matrix-core product spends 4 x 64 cycles
+        // on 2 of 16 columns), then over the row groups.  Every wavefront
+        // adds up its tiles R > t + 1 while x_(t+1) is being solved; after
+        // the one barrier of a column the owner of tile (t + 1, t) adds that
+        // tile and the wavefronts' sums in order and substitutes (row groups
+        // 0, 1 and 2, 3 hold the two right-hand sides, lane n entry n).
+        double *UB = smem + Ls::UB + wq * Ls::QUB_G;
+        double *PART = CURq;  // [2][W][16][2] sums by parity of t; the factors in CUR are in their slots by now
+        static_assert(W == 1 || Ls::NPAR * DS >= 64 * W, "the column sums fit in the diagonal-tile buffers");
 #pragma unroll 1
         for (int t = T - 1; t >= 0; --t) {
             const double *St = SLOTq + t * DS;  // weights and inverse pivots of tile t
-            if (w == tile_index(T, t, t) % W) {
+            double su = 0.0, sb = 0.0;
+            int uo = 2 * g;  // the lane's rows within a block of the solution, opaque per step (no hoisting)
+            asm volatile("" : "+v"(uo));
+            auto add_tile = [&](const dvec4 &L, int R) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const double2 x = *reinterpret_cast<const double2 *>(UB + 32 * R + 8 * r + uo);
+                    su = fma(L[r], x.x, su);
+                    sb = fma(L[r], x.y, sb);
+                }
+            };
+            double *Pt = PART + (t & 1) * 32 * W;
+            if constexpr (W > 1) {
+#pragma unroll
+                for (int s = 0; s < NTW; ++s)
+                    if (SC(s) == t && SR(s) > t + 1) add_tile(tile[s], SR(s));
+                const double sum = sum_row_groups2(su, sb);
+                if ((g & 1) == 0) Pt[32 * w + 2 * j + (g >> 1)] = sum;
+                group_sync();
+                su = sb = 0.0;
+            }
+            // the solver: the owner of tile (t + 1, t), of tile (t, t) in the last column
+            if (w == tile_index(T, t < T - 1 ? t + 1 : t, t) % W) {
+#pragma unroll
+                for (int s = 0; s < NTW; ++s)
+                    if (SC(s) == t && (W > 1 ? SR(s) == t + 1 : SR(s) > t)) add_tile(tile[s], SR(s));
+                double sum = sum_row_groups2(su, sb);
+                if constexpr (W > 1) {
+#pragma unroll
+                    for (int v = 0; v < W; ++v) sum += Pt[32 * v + 2 * j + (g >> 1)];
+                }
+                const int row = 16 * t + j;
+                const double qu = (row < k) ? rr * YPq[row] : (row == k ? half * Lkk : 0.0);
+                const double q0 = (g >> 1) ? (row == k ? Lkk : 0.0) : qu;
                 // x_n = q_n / L_nn, then from the last column x_n += W[c][n] x_c (n < c; the
                 // weights W[c][n] = -L[c][n] / L[n][n] are zero for n >= c), four steps loaded ahead
-                double qv = (g < 2) ? Q[2 * (16 * t + j) + g] * St[272 + j] : 0.0;
+                double qv = (q0 - sum) * St[272 + j];
                 double wg[4], wn[4];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) wg[q] = St[(15 - q) * 17 + j];
@@ -752,107 +768,144 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
 #pragma unroll
                     for (int q = 0; q < 4; ++q) wg[q] = wn[q];
                 });
-                if (g < 2) UB[2 * (16 * t + j) + g] = qv;
+                if ((g & 1) == 0) UB[2 * row + (g >> 1)] = qv;
             }
-            group_sync();
-            if (t > 0) {
-                int qo = 2 * g + j;  // opaque per step, as in the factorisation loop
-                asm volatile("" : "+v"(qo));
-                const bool rhs_lane = j < 2;
-                dvec4 xq;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) xq[q] = rhs_lane ? UB[2 * (16 * t + 4 * q + g) + j] : 0.0;
-#pragma unroll
-                for (int s = 0; s < NTW; ++s) {
-                    if (SR(s) == t && SC(s) < t) {
-                        dvec4 d = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-                        for (int q = 0; q < 4; ++q)
-                            d = __builtin_amdgcn_mfma_f64_16x16x4f64(tile[s][q], xq[q], d, 0, 0, 0);
-                        if (rhs_lane) {
-#pragma unroll
-                            for (int r = 0; r < 4; ++r) Q[32 * SC(s) + 8 * r + qo] -= d[r];
-                        }
-                    }
-                }
-                group_sync();
-            }
+            if constexpr (W == 1) group_sync();
         }
-        // dl/dtau2 = u^T b; dl/dbeta = sum_{a > b} D_ab (u_a b_b + u_b b_a).
-        // u and b vanish past row k, so entries there add exact zeros; in a
-        // diagonal tile the symmetric pairs are both visited and weighted by
-        // one half, and D_aa (zero in exact arithmetic, about 2^-500 sigma2 /
-        // beta^2 after sqrt_pos) is set to zero.
+        group_sync();
+        // dl/dtau2 = u^T b; dl/dbeta = sum_{a > b} D_ab (u_a b_b + u_b b_a)
         double ub = 0.0;
         for (int t = tg; t <= k; t += NTG) ub += UB[2 * t] * UB[2 * t + 1];
-        if constexpr (SHARE_D && !KEEP_D) {
-            // the distances again, shared as in the fill, once every wavefront
-            // is past its back substitution (the last reader of its slots)
-            __syncthreads();
+        double gb = 0.0;
+        if constexpr (KEEP_D) {
+            // u and b vanish past row k, so entries there add exact zeros; in a
+            // diagonal tile the symmetric pairs are both visited and weighted
+            // by one half, and D_aa (zero in exact arithmetic, about 2^-500
+            // sigma2 / beta^2 with dist_pos) is set to zero.
 #pragma unroll
             for (int s = 0; s < NTW; ++s) {
-                if (16 * SR(s) > k) continue;
-                const int b = 16 * SC(s) + j;
-                const double xb = XY[2 * b], yb = XY[2 * b + 1], cb = GCD ? CLv[b] : 0.0;
+                const int R_ = SR(s), C_ = SC(s);
+                if (!SVALID(s) || 16 * R_ > k) continue;
+                const double2 ubb = *reinterpret_cast<const double2 *>(UB + 2 * (16 * C_ + j));
+                dvec4 db4 = dtile[s];
+                double wt = 1.0;
+                if (R_ == C_) {  // wave-uniform: only diagonal tiles hold a == b
+                    wt = 0.5;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (4 * r + g == j) db4[r] = 0.0;
+                }
+                double acc = 0.0;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    if ((4 * s + r) % G != wq) continue;  // wave-uniform
-                    const int a = 16 * SR(s) + 4 * r + g;
-                    dslot(4 * s + r)[l] = pair_dist_pow<KC>(XY[2 * a], XY[2 * a + 1], GCD ? CLv[a] : 0.0, xb, yb, cb,
-                                                            P, ET);
+                    const double2 uba = *reinterpret_cast<const double2 *>(UB + 2 * (16 * R_ + 4 * r + g));
+                    acc = fma(db4[r], fma(uba.x, ubb.y, ubb.x * uba.y), acc);
                 }
+                gb = fma(wt, acc, gb);
             }
+        } else {
+            // D again from the distances, over the N (N - 1) / 2 pairs of the
+            // N = k + 1 points alone: item p is the pair (b, (b + o) mod N)
+            // with b = p mod N and o = 1 + p / N, the items dealt out to the
+            // lanes in order (the 16 x 16 tiles hold 1.2 to 2 times as many
+            // entries, both halves of the diagonal tiles and the padding
+            // among them).  Positions are kept as byte offsets of the 16-byte
+            // entries of XY and UB.
+            const uint32_t N = (uint32_t)k + 1, NP = N * (uint32_t)k / 2;
+            const uint32_t N16 = 16 * N;
+            const uint32_t sb16 = 16 * (NTG % N), so16 = 16 * ((NTG / N) % N);
+            uint32_t b16 = 16 * ((uint32_t)tg % N), o16 = 16 + 16 * (((uint32_t)tg / N) % N);
+            const char *XYb = reinterpret_cast<const char *>(XY), *UBb = reinterpret_cast<const char *>(UB);
+            // the next item: b += NTG mod N, o += NTG / N, one more when b passes N
+            uint32_t a16 = b16 + o16;
+            a16 = min(a16, a16 - N16);
+            const uint32_t sa16 = sb16 + so16;
+            auto next_item = [&]() {
+                b16 += sb16;
+                a16 += sa16 + (b16 >= N16 ? 16u : 0u);
+                b16 = min(b16, b16 - N16);
+                a16 = min(a16, a16 - N16);
+                a16 = min(a16, a16 - N16);
+            };
+            auto pair_dist = [&](uint32_t pa, uint32_t pb) {
+                const double2 xa = *reinterpret_cast<const double2 *>(XYb + pa);
+                const double2 xb = *reinterpret_cast<const double2 *>(XYb + pb);
+                return pair_dist_pow<KC>(xa.x, xa.y, GCD ? CLv[pa / 16] : 0.0, xb.x, xb.y, GCD ? CLv[pb / 16] : 0.0, P,
+                                         ET);
+            };
+            if constexpr (SHARE_D) {
+                // the distances shared as in the fill, once every wavefront is
+                // past its back substitution (the last reader of its slots):
+                // wavefront q evaluates those of every G-th run of 64 items
+                static_assert(G * DCH >= (KP - 1) * (KP - 2) / 2 / kWave + 1, "the shared distances fit");
+                const uint32_t b0 = b16, a0 = a16;
+                __syncthreads();
+                for (uint32_t p = tg, c = 0; p - tg < NP; p += NTG, ++c) {
+                    if ((int)(c % G) == wq && p < NP) dslot((int)c)[l] = pair_dist(a16, b16);
+                    next_item();
+                }
+                __syncthreads();
+                b16 = b0;
+                a16 = a0;
+            }
+            auto add_item = [&](uint32_t pa, uint32_t pb, int c) {
+                double da;
+                if constexpr (SHARE_D) da = dslot(c)[l];
+                else da = pair_dist(pa, pb);
+                const double rs = da * P.inv_beta;
+                const double dr = dbeta_raw<KC>(rs, exp_neg_staged(rs, ET));
+                const double2 ua = *reinterpret_cast<const double2 *>(UBb + pa);
+                const double2 vb = *reinterpret_cast<const double2 *>(UBb + pb);
+                gb = fma(dr, fma(ua.x, vb.y, vb.x * ua.y), gb);
+            };
+            const uint32_t whole = NP / NTG;  // rounds in which every lane has an item
+#pragma unroll 2
+            for (uint32_t c = 0; c < whole; ++c) {
+                add_item(a16, b16, (int)c);
+                next_item();
+            }
+            if (whole * NTG + tg < NP) add_item(a16, b16, (int)whole);
+        }
+        // the totals over the lanes (fixed order), then over the wavefronts
+        ub = row_sum16(ub);
+        gb = row_sum16(gb);
+        const double both = sum_row_groups2(ub, gb);  // row groups 0, 1: ub; 2, 3: gb
+        if constexpr (W == 1) {
+            ub = read_lane(both, 0);
+            gb = read_lane(both, 32);
+        } else {
+            double *red = smem + Ls::RED + wq * Ls::RED_G;
+            if ((l & 31) == 0) red[2 * w + l / 32] = both;
             __syncthreads();
-        }
-        double gb = 0.0;
+            ub = gb = 0.0;
+            if (w == 0) {
 #pragma unroll
-        for (int s = 0; s < NTW; ++s) {
-            const int R_ = SR(s), C_ = SC(s);
-            if (R_ < 0 || 16 * R_ > k) continue;
-            const int b = 16 * C_ + j;
-            const double2 ubb = *reinterpret_cast<const double2 *>(UB + 2 * b);
-            dvec4 db4;
-            if constexpr (KEEP_D) {
-                db4 = dtile[s];
-            } else {
-                const double xb = XY[2 * b], yb = XY[2 * b + 1], cb = GCD ? CLv[b] : 0.0;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int a = 16 * R_ + 4 * r + g;
-                    double cv, db;
-                    if constexpr (SHARE_D)
-                        cov_from_dist<KC, true>(dslot(4 * s + r)[l], P, s2b, ET, cv, db);
-                    else
-                        cov_pair<KC, true>(XY[2 * a], XY[2 * a + 1], GCD ? CLv[a] : 0.0, xb, yb, cb, P, s2b, ET, cv,
-                                           db);
-                    db4[r] = db;
+                for (int v = 0; v < W; ++v) {
+                    ub += red[2 * v];
+                    gb += red[2 * v + 1];
                 }
             }
-            double wt = 1.0;
-            if (R_ == C_) {  // wave-uniform: only diagonal tiles hold a == b
-                wt = 0.5;
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (16 * R_ + 4 * r + g == b) db4[r] = 0.0;
-            }
-            double acc = 0.0;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const double2 uba = *reinterpret_cast<const double2 *>(UB + 2 * (16 * R_ + 4 * r + g));
-                acc = fma(db4[r], fma(uba.x, ubb.y, ubb.x * uba.y), acc);
-            }
-            gb = fma(wt, acc, gb);
         }
-        block_sum2<W>(ub, gb, smem + Ls::RED + wq * Ls::RED_G);
-        o.g2 = ub;
-        o.g0 = (0.5 * (rr * rr * c - 1.0) - P.tau2 * ub) / P.sigma2;
-        o.g1 = gb;
+        if (w == 0) {
+            o.g2 = ub;
+            o.g0 = (0.5 * fma(wv, wv, -1.0) - P.tau2 * ub) / P.sigma2;
+            o.g1 = gb * dbeta_scale<KC>(P);
+        }
     }
-    const bool anybad = __syncthreads_or(bad ? 1 : 0) != 0;
-    o.bad = anybad || !isfinite(o.ell) || !isfinite(o.g0) || !isfinite(o.g1) || !isfinite(o.g2);
+    // the vector's first wavefront reports
+    if (w == 0) {
+        o.ell = -0.5 * (kLog2Pi + 2.0 * log_pos(Lkk) + wv * wv);
+        o.var = Lkk * Lkk;
+        o.mean = Z[k] - wv * Lkk;
+        o.bad = !isfinite(o.ell) || !isfinite(o.g0) || !isfinite(o.g1) || !isfinite(o.g2);
+    } else {
+        o.ell = o.var = o.mean = 0.0;
+        o.bad = false;
+    }
     return o;
 #undef SR
 #undef SC
+#undef SVALID
 }
 
 }  // namespace vecchia
