@@ -203,19 +203,40 @@ __device__ __forceinline__ void stage_exp_entry(int j, double *tab) {
     tab[2 * j + 1] = e.lo * __builtin_amdgcn_rcp(e.hi);  // |lo / hi| < 2^-53: the estimate is plenty
 }
 
+// Constants of the covariance evaluation.  A vector instruction reads at most
+// one constant from scalar registers, and a constant in a vector register is
+// otherwise built again (two moves) in every basic block: PIN keeps the three
+// that meet another constant, or are overwritten by a fused multiply-add, in
+// vector registers of their own, and the rest in scalar registers.
+struct CovConst {
+    double eps, magic, c120;                                     // vector
+    double unmagic, inv_ln2_64, head, tail, c720, c24, c6, rmax;  // scalar
+};
+template <bool PIN>
+__device__ __forceinline__ CovConst cov_const() {
+    CovConst c{0x1p-1000, 0x1.8p52, 1.0 / 120.0, -0x1.8p52, -0x1.71547652b82fep+6, -0x1.62e42fefa0000p-7,
+               -0x1.cf79abc9e3b3ap-46, 1.0 / 720.0, 1.0 / 24.0, 1.0 / 6.0, 708.0};
+    if constexpr (PIN) {
+        asm volatile("" : "+v"(c.eps), "+v"(c.magic), "+v"(c.c120));
+        asm volatile("" : "+s"(c.unmagic), "+s"(c.inv_ln2_64), "+s"(c.head), "+s"(c.tail));
+        asm volatile("" : "+s"(c.c720), "+s"(c.c24), "+s"(c.c6), "+s"(c.rmax));
+    }
+    return c;
+}
+
 // e^-r for r >= -709, one rounding at the end (just above half an ulp, as
 // exp_neg_tab).  Arguments beyond 708 give e^-708 (3e-308), NaN as well, so
 // callers validate their inputs.
-__device__ __forceinline__ double exp_neg_staged(double r, const double *tab) {
-    r = fmin(r, 708.0);
-    const double t = fma(r, -0x1.71547652b82fep+6, 0x1.8p52);  // 64 / ln2
+__device__ __forceinline__ double exp_neg_staged(double r, const double *tab, const CovConst &c) {
+    r = fmin(r, c.rmax);
+    const double t = fma(r, c.inv_ln2_64, c.magic);
     const int n = __double2loint(t);
-    const double nf = t - 0x1.8p52;
-    double f = fma(nf, -0x1.62e42fefa0000p-7, -r);  // head of ln2/64
-    f = fma(nf, -0x1.cf79abc9e3b3ap-46, f);         // tail of ln2/64
-    double q = fma(f, 1.0 / 720.0, 1.0 / 120.0);
-    q = fma(q, f, 1.0 / 24.0);
-    q = fma(q, f, 1.0 / 6.0);
+    const double nf = t + c.unmagic;
+    double f = fma(nf, c.head, -r);
+    f = fma(nf, c.tail, f);
+    double q = fma(f, c.c720, c.c120);
+    q = fma(q, f, c.c24);
+    q = fma(q, f, c.c6);
     q = fma(q, f, 0.5);
     q = fma(q, f, 1.0);
     const double2 e = *reinterpret_cast<const double2 *>(tab + 2 * (n & 63));
@@ -231,8 +252,8 @@ __device__ __forceinline__ double exp_neg_staged(double r, const double *tab) {
 // correction by the residual, as in sqrt_dist, but without the refinement of
 // 1/(2 sqrt): the correction is a factor 2^-47 of the result and the hardware
 // estimate serves it.
-__device__ __forceinline__ double dist_pos(double dx, double dy) {
-    const double s = fma(dx, dx, fma(dy, dy, 0x1p-1000));
+__device__ __forceinline__ double dist_pos(double dx, double dy, const CovConst &c) {
+    const double s = fma(dx, dx, fma(dy, dy, c.eps));
     const double y = __builtin_amdgcn_rsq(s);
     double g = s * y;
     const double h = 0.5 * y;
@@ -279,13 +300,13 @@ __device__ __forceinline__ double log_pos(double x) {
 // power exponential (0 at d = 0).  The coordinates must be finite.
 template <int KC>
 __device__ __forceinline__ double pair_dist_pow(double xa, double ya, double ca, double xb, double yb, double cb,
-                                                const Params &P, const double *tab) {
+                                                const Params &P, const double *tab, const CovConst &cc) {
     double d;
     if constexpr (kc_gcd(KC)) d = gcd_km(xa, ya, ca, xb, yb, cb);
-    else d = dist_pos(xa - xb, ya - yb);
+    else d = dist_pos(xa - xb, ya - yb, cc);
     if constexpr (kc_family(KC) == 3) {
         if (P.alpha == 2.0) d = d * d;
-        else if (P.alpha != 1.0) d = (d > 0.0) ? exp_neg_staged(-(P.alpha * log(d)), tab) : 0.0;
+        else if (P.alpha != 1.0) d = (d > 0.0) ? exp_neg_staged(-(P.alpha * log(d)), tab, cc) : 0.0;
     }
     return d;
 }

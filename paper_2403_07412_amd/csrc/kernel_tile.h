@@ -168,7 +168,7 @@ __host__ __device__ constexpr int tile_waves_per_simd(int T, int W, bool keep_d,
 __host__ __device__ constexpr bool keep_dbeta(int T, int W, bool gcd = false) {
     return VECCHIA_KEEP_DBETA &&
            (tile_waves_per_simd(T, W, true, true, gcd) >= tile_waves_per_simd(T, W, false, true, gcd) ||
-            (gcd && tile_waves_per_simd(T, W, true, true, gcd) >= 2) || (T == 2 && W == 1));
+            (gcd && tile_waves_per_simd(T, W, true, true, gcd) >= 2) || ((T == 2 || T == 3) && W == 1));
 }
 
 // Tile enumeration: column C descending, row R ascending inside a column, so
@@ -243,6 +243,19 @@ __device__ __forceinline__ void static_for(F &&f) {
     if constexpr (B < E) {
         f(std::integral_constant<int, B>{});
         static_for<B + 1, E>(f);
+    }
+}
+
+// f(B), f(B + S), .. up to but excluding E: with UNROLL as compile-time
+// constants, else as ints in a loop that stays rolled.
+template <bool UNROLL, int B, int E, int S, class F>
+__device__ __forceinline__ void for_columns(F &&f) {
+    if constexpr (!UNROLL) {
+#pragma unroll 1
+        for (int t = B; t != E; t += S) f(t);
+    } else if constexpr (B != E) {
+        f(std::integral_constant<int, B>{});
+        for_columns<true, B + S, E, S>(f);
     }
 }
 
@@ -482,6 +495,7 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
     constexpr int NTILES = tile_count(T);
     constexpr int KP = Ls::KP;
     constexpr int DS = Ls::DS;
+    constexpr bool UNROLL = W == 1;
     const int tid = threadIdx.x;
     const int wg = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int w = W == 1 ? 0 : (G > 1 ? wg % W : wg);  // wavefront within the vector's group
@@ -564,6 +578,7 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
     // dC/dbeta is kept in dtile from the same exponential when registers allow.
     constexpr bool KEEP_D = GRAD && keep_dbeta(T, W, GCD);
     const double *ET = smem + Ls::EXPT;
+    const CovConst CC = cov_const<W == 1>();
     dvec4 tile[NTW];
     dvec4 dtile[KEEP_D ? NTW : 1];
     // With one wavefront per vector (INPLACE) every group needs the same
@@ -585,7 +600,7 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
                 if ((4 * s + r) % G != wq) continue;  // wave-uniform
                 const int a = 16 * SR(s) + 4 * r + g;
                 dslot(4 * s + r)[l] = pair_dist_pow<KC>(XY[2 * a], XY[2 * a + 1], GCD ? CLv[a] : 0.0, xb, yb, cb, P,
-                                                        ET);
+                                                        ET, CC);
             }
         }
         __syncthreads();
@@ -605,9 +620,9 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
             if constexpr (SHARE_D)
                 da = dslot(4 * s + r)[l];
             else
-                da = pair_dist_pow<KC>(XY[2 * a], XY[2 * a + 1], GCD ? CLv[a] : 0.0, xb, yb, cb, P, ET);
+                da = pair_dist_pow<KC>(XY[2 * a], XY[2 * a + 1], GCD ? CLv[a] : 0.0, xb, yb, cb, P, ET, CC);
             const double rs = da * P.inv_beta;
-            const double e = exp_neg_staged(rs, ET);
+            const double e = exp_neg_staged(rs, ET, CC);
             tile[s][r] = cov_value<KC>(rs, e, P);
             if constexpr (KEEP_D) dtile[s][r] = dbeta_raw<KC>(rs, e);
         }
@@ -627,8 +642,8 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
 
     // blocked right-looking Cholesky
     const int ty = (k + 1) / 16, jy = (k + 1) % 16;  // the observation row's tile row, and its row there
-#pragma unroll 1
-    for (int t = 0; t < T; ++t) {
+    auto column = [&](auto tc) __attribute__((always_inline)) {
+        const int t = tc;
         // the lane's offset inside a tile slot, opaque to the compiler in every
         // step: otherwise it hoists one address register per slot out of the
         // loop, which at this register budget spill to scratch
@@ -643,7 +658,7 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
 #pragma unroll
             for (int s = 0; s < NTW; ++s)
                 if (SR(s) == t && SC(s) == t) {
-                    asm volatile("");  // a branch, not eight selects per slot
+                    if constexpr (!UNROLL) asm volatile("");  // a branch, not eight selects per slot
                     dt = tile[s];
                 }
             factor_diag(dt, t, k, D, SCALq, YPq);
@@ -683,7 +698,10 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
                 for (int e = l; e < DS; e += kWave) St[e] = D[e];
             }
         }
-    }
+    };
+    // one wavefront per vector knows its tiles at compile time: with the
+    // columns unrolled no tile is tested or copied
+    for_columns<UNROLL, 0, T, 1>(column);
     group_sync();
 
     CondOut o;
@@ -710,8 +728,8 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
         double *UB = smem + Ls::UB + wq * Ls::QUB_G;
         double *PART = CURq;  // [2][W][16][2] sums by parity of t; the factors in CUR are in their slots by now
         static_assert(W == 1 || Ls::NPAR * DS >= 64 * W, "the column sums fit in the diagonal-tile buffers");
-#pragma unroll 1
-        for (int t = T - 1; t >= 0; --t) {
+        auto back_column = [&](auto tc) __attribute__((always_inline)) {
+            const int t = tc;
             const double *St = SLOTq + t * DS;  // weights and inverse pivots of tile t
             double su = 0.0, sb = 0.0;
             int uo = 2 * g;  // the lane's rows within a block of the solution, opaque per step (no hoisting)
@@ -771,7 +789,8 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
                 if ((g & 1) == 0) UB[2 * row + (g >> 1)] = qv;
             }
             if constexpr (W == 1) group_sync();
-        }
+        };
+        for_columns<UNROLL, T - 1, -1, -1>(back_column);
         group_sync();
         // dl/dtau2 = u^T b; dl/dbeta = sum_{a > b} D_ab (u_a b_b + u_b b_a)
         double ub = 0.0;
@@ -831,7 +850,7 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
                 const double2 xa = *reinterpret_cast<const double2 *>(XYb + pa);
                 const double2 xb = *reinterpret_cast<const double2 *>(XYb + pb);
                 return pair_dist_pow<KC>(xa.x, xa.y, GCD ? CLv[pa / 16] : 0.0, xb.x, xb.y, GCD ? CLv[pb / 16] : 0.0, P,
-                                         ET);
+                                         ET, CC);
             };
             if constexpr (SHARE_D) {
                 // the distances shared as in the fill, once every wavefront is
@@ -853,7 +872,7 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
                 if constexpr (SHARE_D) da = dslot(c)[l];
                 else da = pair_dist(pa, pb);
                 const double rs = da * P.inv_beta;
-                const double dr = dbeta_raw<KC>(rs, exp_neg_staged(rs, ET));
+                const double dr = dbeta_raw<KC>(rs, exp_neg_staged(rs, ET, CC));
                 const double2 ua = *reinterpret_cast<const double2 *>(UBb + pa);
                 const double2 vb = *reinterpret_cast<const double2 *>(UBb + pb);
                 gb = fma(dr, fma(ua.x, vb.y, vb.x * ua.y), gb);

@@ -11,6 +11,7 @@
 
 #include "device_common.h"
 #include "kernel_lds.h"
+#include "kernel_rows.h"
 #include "kernel_tile.h"
 #include "vecchia.h"
 
@@ -241,6 +242,90 @@ __global__ void __launch_bounds__(Impl::NT) __attribute__((amdgpu_waves_per_eu(I
     cond_item_group<Impl>(a, a.t0 + (int64_t)Impl::GROUP * blockIdx.x, smem);
 }
 
+// Rows kernel: wavefronts of four conditionals, kRowsWaves to a workgroup
+// (they share the staged exponential table).  Item t of KernelArgs is row
+// group (t - t0) % 4 of wavefront (t - t0) / 4, for t < t_end.
+constexpr int kRowsWaves = 4;
+constexpr int kRowsItems = 4 * kRowsWaves;  // items per workgroup
+
+template <int T, int KC, bool GRAD>
+struct RowsImpl {
+    static constexpr int NT = kRowsWaves * kWave;
+    // wavefronts per SIMD the tiles (and derivatives) held per lane leave room for
+    static constexpr int WPE =
+        GRAD ? (T == 1 ? 4 : 2) : (T == 1 ? 5 : T == 2 ? (KC < 3 ? 4 : 3) : T == 3 ? 3 : 2);
+    static constexpr size_t SMEM = (kRowsWaves * RowsLds<T, GRAD, kc_gcd(KC)>::TOTAL + 2 * kExpTableSize) * sizeof(double);
+};
+
+template <int T, int KC, bool GRAD>
+__global__ void __launch_bounds__(kRowsWaves *kWave)
+    __attribute__((amdgpu_waves_per_eu(RowsImpl<T, KC, GRAD>::WPE)))
+    rows_kernel(const KernelArgs a, int64_t t_end) {
+    extern __shared__ double smem[];
+    double *ET = smem;
+    if (threadIdx.x < kExpTableSize) stage_exp_entry((int)threadIdx.x, ET);
+    __syncthreads();
+    const int wave = threadIdx.x / kWave, g = (threadIdx.x % kWave) / 16;
+    const int64_t t = a.t0 + (int64_t)kRowsItems * blockIdx.x + 4 * wave + g;
+    const bool mine = t < t_end;
+    const double *locs = a.locs, *z = a.z, *theta = a.theta;
+    const int32_t *nbr = a.nbr;
+    int64_t n = a.n, i = 0, row = 0;
+    int32_t m = a.m;
+    if (a.fields) {
+        const int64_t tt = mine ? t : a.t0;
+        int lo = 0, hi = a.nfc;
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (a.item0[mid] <= tt) lo = mid;
+            else hi = mid;
+        }
+        const FieldDev &F = a.fields[a.fidx[lo]];
+        locs = F.locs;
+        z = F.z;
+        nbr = F.nbr;
+        n = F.n;
+        m = (int32_t)F.m;
+        const int64_t r = tt - a.item0[lo];
+        const int64_t ip = item_point(r, a.ntheta);
+        const int64_t q = r - ip * a.ntheta;
+        i = n - 1 - ip;
+        theta = a.theta + 3 * (F.eval0 + q);
+        row = F.vals0 + q * n + i;
+    } else if (mine) {
+        i = a.idx ? a.idx[t] : t;
+        row = t - a.row0;
+    }
+    Params P = load_params(theta, a.alpha);
+    const bool valid = P.valid;
+    if (!valid) {
+        P.sigma2 = P.beta = P.inv_beta = 1.0;
+        P.tau2 = 1.0;
+    }
+    const bool pred = a.qlocs != nullptr;
+    const bool run = mine && valid && i >= 0 && i < (pred ? a.nq : n);
+    CondOut o = rows_conditional<T, KC, GRAD>(locs, z, nbr, run ? i : 0, n, m, pred ? a.qlocs + 2 * (run ? i : 0) : nullptr,
+                                              P, run, ET,
+                                              smem + 2 * kExpTableSize + wave * RowsLds<T, GRAD, kc_gcd(KC)>::TOTAL);
+    const bool bad = o.bad || !run;
+    if (bad) o.ell = o.g0 = o.g1 = o.g2 = o.mean = o.var = __builtin_nan("");
+    if (mine && threadIdx.x % 16 == 0) {
+        if (pred) {
+            a.pmean[row] = o.mean;
+            a.pvar[row] = o.var;
+        } else {
+            a.ell[row * a.ell_stride] = o.ell;
+        }
+        if (a.g) {
+            a.g[row * a.g_stride + 0] = o.g0;
+            a.g[row * a.g_stride + 1] = o.g1;
+            a.g[row * a.g_stride + 2] = o.g2;
+        }
+        if (a.flags) a.flags[row] = bad ? 1 : 0;
+        if (a.status && bad && valid) atomicMin(a.status, (unsigned long long)(t + 1));
+    }
+}
+
 // A launch request: kernel arguments plus the item range [t_begin, t_end)
 // and the largest m among the items (sizes the LDS of the unblocked kernel).
 // group > 1 asks for the lockstep form with that many parameter vectors per
@@ -287,6 +372,23 @@ int launch_group_impl(const EvalArgs &a, hipStream_t s) {
     return hipGetLastError() == hipSuccess ? VECCHIA_OK : VECCHIA_EHIP;
 }
 
+template <int T, int KC, bool GRAD>
+int launch_rows(const EvalArgs &a, hipStream_t s) {
+    if (a.t_end <= a.t_begin) return VECCHIA_OK;
+    constexpr size_t smem = RowsImpl<T, KC, GRAD>::SMEM;
+    auto kern = rows_kernel<T, KC, GRAD>;
+    if (allow_smem(kern, smem) != hipSuccess) return VECCHIA_EHIP;
+    constexpr int64_t kMaxGrid = (int64_t)1 << 22;
+    for (int64_t t0 = a.t_begin; t0 < a.t_end; t0 += kMaxGrid * kRowsItems) {
+        const int64_t grid = std::min<int64_t>((a.t_end - t0 + kRowsItems - 1) / kRowsItems, kMaxGrid);
+        KernelArgs k = a.k;
+        k.t0 = t0;
+        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(RowsImpl<T, KC, GRAD>::NT), smem, s, k,
+                           std::min<int64_t>(a.t_end, t0 + grid * kRowsItems));
+    }
+    return hipGetLastError() == hipSuccess ? VECCHIA_OK : VECCHIA_EHIP;
+}
+
 // Kernel variants.  The tiled family is instantiated for T = ceil((m+2)/16)
 // tile rows and W wavefronts per conditional.
 enum Variant { V_AUTO = 0, V_UNBLOCKED = 1, V_TILE_W1 = 2, V_TILE_W2 = 3, V_TILE_W4 = 4, V_TILE_W8 = 5 };
@@ -305,6 +407,18 @@ inline int variant_waves(int variant) {
         default: return 0;
     }
 }
+
+// The one-wavefront variant is the rows kernel for the Matern codes on
+// Euclidean distances up to four tile rows (m <= 62), and the tiled kernel
+// elsewhere: five rows of tiles do not fit the 256 registers of a lane.  Tiles
+// against rows, Matern 3/2, 100,000 points, ms:
+//   value            m = 10: 0.148, 0.057   30: 0.314, 0.144   40: 0.538, 0.280   60: 0.881, 0.530
+//   value, gradient  m = 10: 0.180, 0.078   30: 0.361, 0.213   40: 0.729, 0.462   60: 1.239, 1.039
+// The rule does not look at the number of points, so that a field gives the
+// same bits alone and in a plan, nor at the gradient, so that the value is the
+// same with and without it; a launch too small to fill the GPU waits longer
+// for one wavefront of four (2,000 points, m = 30: 26 against 24 us).
+__host__ __device__ constexpr bool rows_shape(int T, int W, int KC) { return W == 1 && KC < 3 && T <= 4; }
 
 // register budget: at most 20 tiles per wavefront
 inline bool variant_feasible(int variant, int m) {
@@ -344,6 +458,13 @@ int launch_tile(const EvalArgs &a, hipStream_t s) {
         return VECCHIA_EUNSUPPORTED;
     } else {
         constexpr int G = lockstep_group(T, W);
+        if constexpr (rows_shape(T, W, KC)) {
+            // lockstep groups too: consecutive items are consecutive parameter
+            // vectors of a point, and every row group has its own parameters
+            if (a.group > 1 && (a.group != G || !a.k.fields || a.k.qlocs || a.k.ntheta % G != 0))
+                return VECCHIA_EUNSUPPORTED;
+            return launch_rows<T, KC, GRAD>(a, s);
+        }
         if (a.group > 1) {
             if constexpr (G > 1) {
                 if (a.group == G) return launch_group_impl<TileImpl<T, W, KC, GRAD, G>>(a, s);
