@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include "exp_table.h"
+#include "log_table.h"
 
 namespace vecchia {
 
@@ -295,20 +296,166 @@ __device__ __forceinline__ double log_pos(double x) {
     return x > 0.0 ? r : __builtin_nan("");
 }
 
+// Staged tables of the tiled and rows kernels: 64 entries of the exponential
+// and, for the power exponential, 64 of the logarithm after them.
+__host__ __device__ constexpr int staged_doubles(bool powexp) {
+    return 2 * kExpTableSize + (powexp ? 2 * kLogTableSize : 0);
+}
+template <int KC>
+__device__ __forceinline__ void stage_tables(int t, double *tab) {
+    if (t < kExpTableSize) stage_exp_entry(t, tab);
+    if constexpr (kc_family(KC) == 3) {
+        if (t < kLogTableSize) {
+            tab[2 * kExpTableSize + 2 * t] = kLogMant64[t].c;
+            tab[2 * kExpTableSize + 2 * t + 1] = kLogMant64[t].neg_log_c;
+        }
+    }
+}
+
+// log x for positive normal x, to an absolute error of about half an ulp of
+// the result plus 2^-54 (it feeds an exponential): x = 2^k m with m in
+// [1/2, 1), r = m c - 1 with c near 1 / m (|r| <= 2^-7), log x = k ln2 - log c
+// + log1p r, the last by its Taylor polynomial of degree 7 (truncation 2e-18).
+__device__ __forceinline__ double log_staged(double x, const double *tab) {
+    const double m = __builtin_amdgcn_frexp_mant(x);
+    const double k = (double)__builtin_amdgcn_frexp_exp(x);
+    const int j = (__double2hiint(m) >> 14) & 63;
+    const double2 e = *reinterpret_cast<const double2 *>(tab + 2 * kExpTableSize + 2 * j);
+    const double r = fma(m, e.x, -1.0);
+    double p = fma(r, 1.0 / 7.0, -1.0 / 6.0);
+    p = fma(p, r, 1.0 / 5.0);
+    p = fma(p, r, -1.0 / 4.0);
+    p = fma(p, r, 1.0 / 3.0);
+    p = fma(p, r, -0.5);
+    p = fma(r * r, p, r);
+    // ln2 as a 32-bit head (k head is exact) and a tail
+    return fma(k, 0x1.62e42fee00000p-1, e.y + fma(k, 0x1.a39ef35793c76p-33, p));
+}
+
+// sin x for |x| <= pi / 4 by its Taylor polynomial (truncation below 4e-17).
+__device__ __forceinline__ double sin_quarter(double x) {
+    const double z = x * x;
+    double q = 1.0 / 355687428096000.0;  // 1/17!
+    q = fma(q, z, -1.0 / 1307674368000.0);
+    q = fma(q, z, 1.0 / 6227020800.0);
+    q = fma(q, z, -1.0 / 39916800.0);
+    q = fma(q, z, 1.0 / 362880.0);
+    q = fma(q, z, -1.0 / 5040.0);
+    q = fma(q, z, 1.0 / 120.0);
+    q = fma(q, z, -1.0 / 6.0);
+    return fma(x * z, q, x);
+}
+
+// |sin| and cos of an angle in degrees, any finite one: reduced in degrees,
+// where every step is exact, to [0, 45] or its complement, sin(90 - b) = cos b
+// = 1 - 2 sin^2(b / 2).  Little code and no stack frame, unlike the library's
+// reduction, since it is inlined wherever a covariance is evaluated.
+__device__ __forceinline__ double reduce_degrees(double a) {  // |a| folded into [0, 180]
+    a = fabs(a);
+    while (a > 180.0) a = fabs(fma(__builtin_rint(a * (1.0 / 360.0)), -360.0, a));
+    return a;
+}
+__device__ __forceinline__ double sin_deg_90(double a) {  // a in [0, 90]
+    const bool top = a > 45.0;
+    const double s = sin_quarter((top ? 45.0 - 0.5 * a : a) * kDeg2Rad);
+    return top ? fma(-2.0 * s, s, 1.0) : s;
+}
+__device__ __forceinline__ double abs_sin_deg(double a) {
+    a = reduce_degrees(a);
+    return sin_deg_90(a > 90.0 ? 180.0 - a : a);
+}
+__device__ __forceinline__ double cos_deg(double a) {
+    a = reduce_degrees(a);
+    const double c = sin_deg_90(fabs(90.0 - a));
+    return a > 90.0 ? -c : c;
+}
+
+// sin x for |x| <= 0.25: sin_short's polynomial
+__device__ __forceinline__ double sin_near(double x) {
+    const double z = x * x;
+    double q = 1.0 / 6227020800.0;  // 1/13!
+    q = fma(q, z, -1.0 / 39916800.0);
+    q = fma(q, z, 1.0 / 362880.0);
+    q = fma(q, z, -1.0 / 5040.0);
+    q = fma(q, z, 1.0 / 120.0);
+    q = fma(q, z, -1.0 / 6.0);
+    return fma(x * z, q, x);
+}
+
+// sqrt x for normal x, as dist_pos
+__device__ __forceinline__ double sqrt_lean(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y;
+    const double h = 0.5 * y;
+    g = fma(g, fma(-h, g, 0.5), g);
+    return fma(fma(-g, g, x), h, g);
+}
+
 // The parameter-free part of the scaled distance for a pair of points (cos of
 // the latitudes in ca, cb for the great-circle codes): d, or d^alpha for the
-// power exponential (0 at d = 0).  The coordinates must be finite.
+// power exponential (0 for coincident points: the power of the 2^-500 that
+// stands for their distance need not be small).  The coordinates must be finite.
+//
+// Great-circle distances: h = hav(d / R) as in gcd_km, d = 2 R asin sqrt h by
+// the series of asin(s) / s in h up to h = 0.01 (1270 km).  For the power exponential the
+// square root is not taken: ln d = ln(4 R^2 h) / 2 + ln(asin(s) / s), the last
+// by its own series in h (to h^7, truncation 8e-19).
 template <int KC>
 __device__ __forceinline__ double pair_dist_pow(double xa, double ya, double ca, double xb, double yb, double cb,
                                                 const Params &P, const double *tab, const CovConst &cc) {
-    double d;
-    if constexpr (kc_gcd(KC)) d = gcd_km(xa, ya, ca, xb, yb, cb);
-    else d = dist_pos(xa - xb, ya - yb, cc);
-    if constexpr (kc_family(KC) == 3) {
-        if (P.alpha == 2.0) d = d * d;
-        else if (P.alpha != 1.0) d = (d > 0.0) ? exp_neg_staged(-(P.alpha * log(d)), tab, cc) : 0.0;
+    if constexpr (kc_gcd(KC)) {
+        const double dy = ya - yb, dx = xa - xb;
+        const double x1 = dy * (0.5 * kDeg2Rad), x2 = dx * (0.5 * kDeg2Rad);
+        double s1 = sin_near(x1), s2 = sin_near(x2);
+        if (fmax(fabs(x1), fabs(x2)) > 0.25) {
+            s1 = abs_sin_deg(0.5 * dy);
+            s2 = abs_sin_deg(0.5 * dx);
+        }
+        double h = fmin(fma(s1, s1, fma(ca * cb, s2 * s2, cc.eps)), 1.0);
+        // far pairs: the angle is halved (h becomes h / (2 (1 + sqrt(1 - h))))
+        // until the series holds
+        double r2 = 2.0 * kEarthRadiusKm;
+        if (h > 0.01) {
+            do {
+                const double u = 1.0 + sqrt_lean(fma(-1.0, h, 1.0) + 0x1p-1000);
+                h = (0.5 * h) / u;
+                r2 += r2;
+            } while (h > 0.01);
+        }
+        if constexpr (kc_family(KC) == 3) {
+            if (P.alpha != 1.0 && P.alpha != 2.0) {
+                double p = 36740617.0 / 3831077250.0;
+                p = fma(p, h, 92427157.0 / 7662154500.0);
+                p = fma(p, h, 14797.0 / 935550.0);
+                p = fma(p, h, 2497.0 / 113400.0);
+                p = fma(p, h, 191.0 / 5670.0);
+                p = fma(p, h, 11.0 / 180.0);
+                p = fma(p, h, 1.0 / 6.0);
+                const double lnd = fma(0.5, log_staged(h * (r2 * r2), tab), p * h);
+                const double da = exp_neg_staged(-(P.alpha * lnd), tab, cc);
+                return h > 0x1p-999 ? da : 0.0;
+            }
+        }
+        const double s = sqrt_lean(h);
+        double p = 6435.0 / 557056.0;
+        p = fma(p, h, 143.0 / 10240.0);
+        p = fma(p, h, 231.0 / 13312.0);
+        p = fma(p, h, 63.0 / 2816.0);
+        p = fma(p, h, 35.0 / 1152.0);
+        p = fma(p, h, 5.0 / 112.0);
+        p = fma(p, h, 3.0 / 40.0);
+        p = fma(p, h, 1.0 / 6.0);
+        double d = r2 * fma(s * h, p, s);
+        if constexpr (kc_family(KC) == 3) d = (P.alpha == 2.0) ? d * d : d;
+        return d;
+    } else {
+        double d = dist_pos(xa - xb, ya - yb, cc);
+        if constexpr (kc_family(KC) == 3) {
+            if (P.alpha == 2.0) d = d * d;
+            else if (P.alpha != 1.0) d = d > 0x1p-499 ? exp_neg_staged(-(P.alpha * log_staged(d, tab)), tab, cc) : 0.0;
+        }
+        return d;
     }
-    return d;
 }
 
 // Covariance from da = pair_dist_pow: sigma2 e^-r, sigma2 (1 + r) e^-r,

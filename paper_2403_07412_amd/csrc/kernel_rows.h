@@ -132,7 +132,7 @@ __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ l
         Z[r] = zz;
         YP[r] = 0.0;
         if constexpr (GCD) {
-            pc[R] = cos(y * kDeg2Rad);
+            pc[R] = cos_deg(y);
             CLv[r] = pc[R];
         }
     }

@@ -52,7 +52,7 @@ __host__ __device__ constexpr int tile_count(int T) { return T * (T + 1) / 2; }
 __host__ __device__ constexpr int tiles_per_wave(int T, int W) { return (tile_count(T) + W - 1) / W; }
 
 // LDS layout of the tiled kernel, in doubles.  The great-circle codes add
-// cos(latitude) of every row at the end; the other offsets do not depend on it.
+// cos(latitude) of every row, the power exponential a table of the logarithm.
 //
 // CUR[t % NPAR] receives the substitution weights of diagonal tile t
 // (row-major, row stride 17) and, after that block, its 16 inverse pivots.
@@ -71,7 +71,7 @@ __host__ __device__ constexpr int tiles_per_wave(int T, int W) { return (tile_co
 // wavefront per vector (INPLACE, also for G = 1) there is no CUR: the
 // wavefront publishes factor t + 1 into slot t + 1 once its trailing updates
 // have read X_(t+1) there.
-template <int T, int W, bool GRAD, bool GCD = false, int G = 1>
+template <int T, int W, bool GRAD, bool GCD = false, int G = 1, bool POWEXP = false>
 struct TileLds {
     static constexpr int KP = 16 * T;
     static constexpr int DS = 288;                        // a 16 x 17 tile, then 16 inverse pivots
@@ -85,22 +85,23 @@ struct TileLds {
     static constexpr int UB = YP + G * KP;                // [G][KP][2]     back-substitution solutions (u, b), gradient
     static constexpr int SCAL = UB + (GRAD ? G * 2 * KP : 0);  // [G][16]   scalars: [0] L_kk, [1] 1 / L_kk
     static constexpr int RED = SCAL + G * 16;             // [G][2][4W]     reductions (two values, W waves x 4 rows)
-    static constexpr int EXPT = RED + G * 8 * W;          // [64][2]        2^(j/64) for exp_neg_staged
-    static constexpr int CL = EXPT + 2 * kExpTableSize;   // [KP]           cos(latitude) (great-circle codes only)
-    static constexpr int TOTAL = CL + (GCD ? KP : 0);
+    static constexpr int CL = RED + G * 8 * W;            // [KP]           cos(latitude) (great-circle codes only)
+    static constexpr int EXPT = CL + (GCD ? KP : 0);      //                staged tables (stage_tables)
+    static constexpr int TOTAL = EXPT + staged_doubles(POWEXP);
     static constexpr size_t BYTES = (size_t)TOTAL * sizeof(double);
     // per-parameter-vector strides
     static constexpr int CUR_G = NPAR * DS, SLOT_G = T * DS, YP_G = KP, QUB_G = 2 * KP, SCAL_G = 16, RED_G = 8 * W;
 };
 
-// TileLds<T, W, grad, gcd, G>::TOTAL, for the occupancy estimate.
-__host__ __device__ constexpr int tile_lds_doubles(int T, int W, bool grad, bool gcd, int G = 1) {
+// TileLds<T, W, grad, gcd, G, powexp>::TOTAL, for the occupancy estimate.
+__host__ __device__ constexpr int tile_lds_doubles(int T, int W, bool grad, bool gcd, int G = 1, bool powexp = false) {
     return (W == 1 ? 0 : G * ((W > 1 && T > 1) ? 2 : 1) * 288) + G * T * 288 +
-           16 * T * (3 + G * (1 + (grad ? 2 : 0)) + (gcd ? 1 : 0)) + G * (16 + 8 * W) + 2 * kExpTableSize;
+           16 * T * (3 + G * (1 + (grad ? 2 : 0)) + (gcd ? 1 : 0)) + G * (16 + 8 * W) + staged_doubles(powexp);
 }
 static_assert(TileLds<8, 4, true, false>::TOTAL == tile_lds_doubles(8, 4, true, false), "LDS estimate out of date");
 static_assert(TileLds<3, 1, false, true>::TOTAL == tile_lds_doubles(3, 1, false, true), "LDS estimate out of date");
-static_assert(TileLds<4, 1, true, true, 4>::TOTAL == tile_lds_doubles(4, 1, true, true, 4), "LDS estimate out of date");
+static_assert(TileLds<4, 1, true, true, 4, true>::TOTAL == tile_lds_doubles(4, 1, true, true, 4, true),
+              "LDS estimate out of date");
 static_assert(TileLds<5, 2, false, false, 2>::TOTAL == tile_lds_doubles(5, 2, false, false, 2), "LDS estimate out of date");
 
 // Parameter vectors a workgroup evaluates in lockstep, per shape: four for
@@ -153,22 +154,22 @@ __host__ __device__ constexpr int tile_waves_per_simd(int T, int W, bool keep_d,
 
 // Whether the gradient keeps the beta-derivative tiles in registers (one
 // covariance evaluation per entry) or recomputes them after the solves.  For
-// the Matern codes on Euclidean distances an evaluation is about 32
-// instructions, and the tiles are kept only when the extra registers cost no
-// occupancy.  The great-circle codes spend two sines, an arcsine and (power
-// exponential) a logarithm and an exponential per entry: there the tiles are
-// kept whenever two wavefronts per SIMD still fit (measured: the 250,000-point
-// great-circle power-exponential gradient took 11.7 ms keeping them at two
-// wavefronts per SIMD, 17.0 ms recomputing at three).  The one-wavefront
-// shape of two tile rows keeps them as well (measured: 250,000 points,
-// m = 30, value + gradient 1.25 ms keeping at four wavefronts per SIMD, 1.33
-// ms recomputing at five).  Lockstep workgroups follow the one-vector
-// decision: the two ways round the derivative contract their arithmetic
+// the Matern codes on Euclidean distances an evaluation is about 36 issue
+// slots, and the tiles are kept only when the extra registers cost no
+// occupancy.  The great-circle codes spend about 100 to 130 (two sines, a root
+// and a series, for the power exponential a logarithm and an exponential):
+// there one-wavefront shapes keep the tiles whenever two wavefronts per SIMD
+// still fit (measured, power exponential, 100,000 points, m = 60: 2.17 ms
+// keeping at two wavefronts per SIMD, 2.56 recomputing at three; with four
+// wavefronts per conditional, m = 120, 50,000 points, keeping lost: 5.74
+// against 4.64 ms).  One-wavefront shapes of two and three tile rows always
+// keep them (Matern, m = 40, 100,000 points: 0.63 against 0.73 ms).
+// Lockstep workgroups follow the one-vector decision: the two ways round the derivative contract their arithmetic
 // differently, and the lockstep results must be the one-vector bits.
 __host__ __device__ constexpr bool keep_dbeta(int T, int W, bool gcd = false) {
     return VECCHIA_KEEP_DBETA &&
            (tile_waves_per_simd(T, W, true, true, gcd) >= tile_waves_per_simd(T, W, false, true, gcd) ||
-            (gcd && tile_waves_per_simd(T, W, true, true, gcd) >= 2) || ((T == 2 || T == 3) && W == 1));
+            (gcd && W == 1 && tile_waves_per_simd(T, W, true, true, gcd) >= 2) || ((T == 2 || T == 3) && W == 1));
 }
 
 // Tile enumeration: column C descending, row R ascending inside a column, so
@@ -488,7 +489,7 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
                                     const double *qloc, const Params &P, double *smem) {
     static_assert(G == 1 || G == 2 || G == 4, "one, two or four parameter vectors per workgroup");
     constexpr bool GCD = kc_gcd(KC);
-    using Ls = TileLds<T, W, GRAD, GCD, G>;
+    using Ls = TileLds<T, W, GRAD, GCD, G, kc_family(KC) == 3>;
     constexpr int NT = G * W * kWave;
     constexpr int NTG = W * kWave;  // threads per parameter vector
     constexpr int NTW = tiles_per_wave(T, W);
@@ -565,9 +566,9 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
         XY[2 * t] = x;
         XY[2 * t + 1] = y;
         Z[t] = zz;
-        if constexpr (GCD) CLv[t] = cos(y * kDeg2Rad);
+        if constexpr (GCD) CLv[t] = cos_deg(y);
     }
-    if (tid < kExpTableSize) stage_exp_entry(tid, smem + Ls::EXPT);
+    stage_tables<KC>(tid, smem + Ls::EXPT);
     __syncthreads();
 
     // covariance generation straight into the N-layout register tiles: lane

@@ -43,7 +43,7 @@ struct TileImpl {
     static constexpr int WPE = VECCHIA_WPE_OVERRIDE > 0
                                    ? VECCHIA_WPE_OVERRIDE
                                    : tile_waves_per_simd(T, W, GRAD && keep_dbeta(T, W, GCD), GRAD, GCD, G);
-    static size_t smem(int) { return TileLds<T, W, GRAD, GCD, G>::BYTES; }
+    static size_t smem(int) { return TileLds<T, W, GRAD, GCD, G, kc_family(KC) == 3>::BYTES; }
     static __device__ CondOut run(const double *locs, const double *z, const int32_t *nbr, int64_t i, int64_t n,
                                   int32_t m, const double *qloc, const Params &P, double *sm) {
         return tile_conditional<T, W, KC, GRAD, G>(locs, z, nbr, i, n, m, qloc, P, sm);
@@ -254,7 +254,7 @@ struct RowsImpl {
     // wavefronts per SIMD the tiles (and derivatives) held per lane leave room for
     static constexpr int WPE =
         GRAD ? (T == 1 ? 4 : 2) : (T == 1 ? 5 : T == 2 ? (KC < 3 ? 4 : 3) : T == 3 ? 3 : 2);
-    static constexpr size_t SMEM = (kRowsWaves * RowsLds<T, GRAD, kc_gcd(KC)>::TOTAL + 2 * kExpTableSize) * sizeof(double);
+    static constexpr size_t SMEM = (kRowsWaves * RowsLds<T, GRAD, kc_gcd(KC)>::TOTAL + staged_doubles(kc_family(KC) == 3)) * sizeof(double);
 };
 
 template <int T, int KC, bool GRAD>
@@ -263,7 +263,7 @@ __global__ void __launch_bounds__(kRowsWaves *kWave)
     rows_kernel(const KernelArgs a, int64_t t_end) {
     extern __shared__ double smem[];
     double *ET = smem;
-    if (threadIdx.x < kExpTableSize) stage_exp_entry((int)threadIdx.x, ET);
+    stage_tables<KC>((int)threadIdx.x, ET);
     __syncthreads();
     const int wave = threadIdx.x / kWave, g = (threadIdx.x % kWave) / 16;
     const int64_t t = a.t0 + (int64_t)kRowsItems * blockIdx.x + 4 * wave + g;
@@ -306,7 +306,7 @@ __global__ void __launch_bounds__(kRowsWaves *kWave)
     const bool run = mine && valid && i >= 0 && i < (pred ? a.nq : n);
     CondOut o = rows_conditional<T, KC, GRAD>(locs, z, nbr, run ? i : 0, n, m, pred ? a.qlocs + 2 * (run ? i : 0) : nullptr,
                                               P, run, ET,
-                                              smem + 2 * kExpTableSize + wave * RowsLds<T, GRAD, kc_gcd(KC)>::TOTAL);
+                                              smem + staged_doubles(kc_family(KC) == 3) + wave * RowsLds<T, GRAD, kc_gcd(KC)>::TOTAL);
     const bool bad = o.bad || !run;
     if (bad) o.ell = o.g0 = o.g1 = o.g2 = o.mean = o.var = __builtin_nan("");
     if (mine && threadIdx.x % 16 == 0) {
@@ -409,8 +409,11 @@ inline int variant_waves(int variant) {
 }
 
 // The one-wavefront variant is the rows kernel for the Matern codes on
-// Euclidean distances up to four tile rows (m <= 62), and the tiled kernel
-// elsewhere: five rows of tiles do not fit the 256 registers of a lane.  Tiles
+// Euclidean distances up to four tile rows (m <= 62), for the other codes up to
+// two, and the tiled kernel elsewhere: five rows of tiles do not fit the 256
+// registers of a lane, and with the branches of the other codes' distances
+// three already spill (great-circle power exponential, m = 40, value +
+// gradient: 1.52 ms rows, 1.39 tiles; m = 30: 0.57, 0.63).  Tiles
 // against rows, Matern 3/2, 100,000 points, ms:
 //   value            m = 10: 0.148, 0.057   30: 0.314, 0.144   40: 0.538, 0.280   60: 0.881, 0.530
 //   value, gradient  m = 10: 0.180, 0.078   30: 0.361, 0.213   40: 0.729, 0.462   60: 1.239, 1.039
@@ -418,7 +421,7 @@ inline int variant_waves(int variant) {
 // same bits alone and in a plan, nor at the gradient, so that the value is the
 // same with and without it; a launch too small to fill the GPU waits longer
 // for one wavefront of four (2,000 points, m = 30: 26 against 24 us).
-__host__ __device__ constexpr bool rows_shape(int T, int W, int KC) { return W == 1 && KC < 3 && T <= 4; }
+__host__ __device__ constexpr bool rows_shape(int T, int W, int KC) { return W == 1 && T <= (KC < 3 ? 4 : 2); }
 
 // register budget: at most 20 tiles per wavefront
 inline bool variant_feasible(int variant, int m) {
@@ -431,20 +434,16 @@ inline bool variant_feasible(int variant, int m) {
 
 // Built-in choice when the variant table has no entry: the fastest variant
 // per tile count measured on MI355X (value and value + gradient, nu = 1/2,
-// 3/2, 5/2, 60,000 uniform points; rows 4 with the gradient re-measured at
-// 300,000 points, nu = 1/2, once the occupancy targets allowed a fifth
-// wavefront per SIMD).  Three and four tile rows favour one wavefront with
-// the gradient and two without; up to six rows two wavefronts; beyond, four
-// (eight wavefronts lose to their barriers at every size).  Since the
-// one-wavefront kernels factor their diagonal tiles in place, one wavefront
-// is also the faster value-only kernel at three and four rows for the Matern
-// codes on Euclidean distances (kc 0..2; 250,000 points: 1.56 against 1.77 ms
-// at m = 40, 2.78 against 2.83 ms at m = 60), but not for kriging with the
-// great-circle power exponential (25,000 predictions at m = 60: 0.84 against
-// 0.69 ms): the other codes, kriging (kc < 0) and unknown callers keep two.
+// 3/2, 5/2, 60,000 to 300,000 uniform points).  One wavefront up to four tile
+// rows (the rows kernel, for the Matern codes on Euclidean distances), except
+// for values of the other codes at four rows, where two wavefronts of tiles
+// are faster (great-circle power exponential, 100,000 points, m = 60: 1.72
+// against 2.13 ms; m = 40: 1.17 against 1.06 ms).  Up to six rows two
+// wavefronts; beyond, four (eight wavefronts lose to their barriers at every
+// size).  kc < 0: the code is not known.
 inline int default_variant(int m, bool grad, int kc = -1) {
     const int T = tile_rows(m);
-    if (T <= 2) return V_TILE_W1;
+    if (T <= 3) return V_TILE_W1;
     if (T <= 4) return (grad || (kc >= 0 && kc <= 2)) ? V_TILE_W1 : V_TILE_W2;
     if (T <= 6) return V_TILE_W2;
     return V_TILE_W4;

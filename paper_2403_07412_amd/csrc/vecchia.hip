@@ -248,7 +248,7 @@ int run_predict(const double *locs, const double *z, int64_t n, const double *ql
     a.t_end = nq;
     a.m_max = m;
     hipLaunchKernelGGL(status_init_kernel, dim3(1), dim3(64), 0, s, st);
-    const int rc = launch_any(kc, false, resolve_variant(m, false, V_AUTO), a, s);
+    const int rc = launch_any(kc, false, resolve_variant(m, false, V_AUTO, kc), a, s);
     if (rc != VECCHIA_OK) return rc;
     hipLaunchKernelGGL(status_fix_kernel, dim3(1), dim3(64), 0, s, st, theta);
     return hipGetLastError() == hipSuccess ? VECCHIA_OK : VECCHIA_EHIP;
