@@ -6,11 +6,13 @@
 // Neighbour search: points are binned into a uniform grid over their bounding
 // box (about two points per cell) by a stable radix sort of (cell, index), so
 // every cell lists its points in ascending index and the points before i form
-// a prefix of each list.  One wavefront serves one query point: it scans rings
-// of cells around the query until no unscanned cell can hold a point closer
-// than the current m-th best, keeping candidates in an LDS buffer that is
-// sorted (bitonic, by squared distance then index) and cut back to m whenever
-// it fills.  Early points (i below kBruteMax) scan all j < i instead.  The
+// a prefix of each list.  One wavefront serves one query point: it scans a
+// square block of cells around the query sized for the points before it, then
+// rings, until no unscanned cell can hold a point closer than the current m-th
+// best.  Candidates that beat the m-th best are collected in LDS, 64 at a time
+// sorted across the lanes and merged into the best list, which lives sorted in
+// registers (64 entries per register).  Early points (i below kBruteMax) scan
+// all j < i instead.  The
 // result is exactly the brute-force answer: the order (squared distance,
 // index) is total and every candidate that could beat the m-th best is seen.
 // Prediction points search all observed points the same way.  Great-circle
@@ -35,11 +37,10 @@ namespace {
 
 constexpr int kWaveK = 64;
 constexpr int kKnnWaves = 4;         // query wavefronts per block
-constexpr int kKnnCap = 256;         // candidate buffer per wavefront (>= VECCHIA_MAX_M + 64)
 constexpr int64_t kBruteMax = 8192;  // queries up to this index scan all earlier points
 constexpr int kBoxBlocks = 256;
 constexpr int kMaxGrid = 8192;
-static_assert(kKnnCap >= VECCHIA_MAX_M + kWaveK, "candidate buffer too small");
+static_assert(VECCHIA_MAX_M <= 3 * kWaveK, "best list of up to three registers");
 
 // squared distance with each product rounded (no contraction), as the
 // conditioning sets are defined
@@ -191,56 +192,171 @@ __global__ void gather_sorted_kernel(const double *__restrict__ locs, int64_t n,
 
 // ---- queries ----------------------------------------------------------------
 
-// One wavefront's candidate buffer: sorts [0, c) (padded to kKnnCap) by
-// (distance, index), keeps min(c, k) entries and returns the new count.
-__device__ __forceinline__ int trim_buffer(double *bd, int32_t *bj, int c, int k, int lane) {
-    for (int t = c + lane; t < kKnnCap; t += kWaveK) {
-        bd[t] = INFINITY;
-        bj[t] = INT32_MAX;
-    }
-    wave_sync_lds();
-    for (int size = 2; size <= kKnnCap; size <<= 1) {
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            for (int t = lane; t < kKnnCap / 2; t += kWaveK) {
-                const int a = 2 * stride * (t / stride) + (t % stride);
-                const int b = a + stride;
-                const bool up = (a & size) == 0;
-                const double da = bd[a], db = bd[b];
-                const int32_t ja = bj[a], jb = bj[b];
-                const bool swap = up ? pair_less(db, jb, da, ja) : pair_less(da, ja, db, jb);
-                if (swap) {
-                    bd[a] = db;
-                    bd[b] = da;
-                    bj[a] = jb;
-                    bj[b] = ja;
-                }
-            }
-            wave_sync_lds();
-        }
-    }
-    return c < k ? c : k;
+// A candidate per lane: key and index, ordered by (key, index).
+struct Cand {
+    double d;
+    int32_t j;
+};
+
+// The value of lane ^ MASK (MASK a power of two, or 2^p - 1).
+template <int MASK>
+__device__ __forceinline__ int xor_lane(int v) {
+    if constexpr (MASK == 1) return __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false);        // quad_perm
+    else if constexpr (MASK == 2) return __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, false);
+    else if constexpr (MASK == 3) return __builtin_amdgcn_update_dpp(0, v, 0x1B, 0xF, 0xF, false);
+    else if constexpr (MASK == 7) return __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, false);  // row_half_mirror
+    else if constexpr (MASK == 8) return __builtin_amdgcn_update_dpp(0, v, 0x128, 0xF, 0xF, false);  // row_ror:8
+    else if constexpr (MASK == 15) return __builtin_amdgcn_update_dpp(0, v, 0x140, 0xF, 0xF, false); // row_mirror
+    else if constexpr (MASK < 32) return __builtin_amdgcn_ds_swizzle(v, (MASK << 10) | 0x1F);
+    else return __shfl_xor(v, MASK, kWaveK);
+}
+template <int MASK>
+__device__ __forceinline__ Cand xor_lane(const Cand &c) {
+    Cand o;
+    o.d = __hiloint2double(xor_lane<MASK>(__double2hiint(c.d)), xor_lane<MASK>(__double2loint(c.d)));
+    o.j = xor_lane<MASK>(c.j);
+    return o;
 }
 
+// One compare-exchange with lane ^ MASK: the lane of the pair with a zero in
+// the top bit of MASK keeps the smaller candidate.
+template <int MASK>
+__device__ __forceinline__ void exchange(Cand &c, int lane) {
+    constexpr int TOP = MASK >= 32 ? 32 : MASK >= 16 ? 16 : MASK >= 8 ? 8 : MASK >= 4 ? 4 : MASK >= 2 ? 2 : 1;
+    const Cand o = xor_lane<MASK>(c);
+    const bool less = pair_less(o.d, o.j, c.d, c.j);
+    const bool take = ((lane & TOP) != 0) != less;
+    c.d = take ? o.d : c.d;
+    c.j = take ? o.j : c.j;
+}
+
+// Half cleaners of strides 32 .. 1: sorts a bitonic sequence over the lanes.
+__device__ __forceinline__ void clean64(Cand &c, int lane) {
+    exchange<32>(c, lane);
+    exchange<16>(c, lane);
+    exchange<8>(c, lane);
+    exchange<4>(c, lane);
+    exchange<2>(c, lane);
+    exchange<1>(c, lane);
+}
+
+// Bitonic sort over the 64 lanes, ascending: every merge opens with the
+// mirrored comparison, so all its comparisons point the same way.
+__device__ __forceinline__ void sort64(Cand &c, int lane) {
+    exchange<1>(c, lane);
+    exchange<3>(c, lane);
+    exchange<1>(c, lane);
+    exchange<7>(c, lane);
+    exchange<2>(c, lane);
+    exchange<1>(c, lane);
+    exchange<15>(c, lane);
+    exchange<4>(c, lane);
+    exchange<2>(c, lane);
+    exchange<1>(c, lane);
+    exchange<31>(c, lane);
+    exchange<8>(c, lane);
+    exchange<4>(c, lane);
+    exchange<2>(c, lane);
+    exchange<1>(c, lane);
+    exchange<63>(c, lane);
+    exchange<16>(c, lane);
+    exchange<8>(c, lane);
+    exchange<4>(c, lane);
+    exchange<2>(c, lane);
+    exchange<1>(c, lane);
+}
+
+// lo and hi (lo of lower rank): the smaller of each pair goes to lo.
+__device__ __forceinline__ void order_pair(Cand &lo, Cand &hi) {
+    const bool swap = pair_less(hi.d, hi.j, lo.d, lo.j);
+    const Cand t = lo;
+    lo.d = swap ? hi.d : lo.d;
+    lo.j = swap ? hi.j : lo.j;
+    hi.d = swap ? t.d : hi.d;
+    hi.j = swap ? t.j : hi.j;
+}
+
+// The Q * 64 nearest candidates seen, sorted, entry e in register e / 64 of
+// lane e % 64; the k-th of them is the threshold a candidate has to beat.
+// Accepted candidates wait in the LDS buffer bd / bj (128 entries) until 64
+// are there.
+template <int Q>
 struct TopK {
     double *bd;
     int32_t *bj;
-    int c, k, lane;
+    int c, k, lane;  // c candidates wait; k are wanted
+    int seen;        // candidates merged so far, up to Q * 64
     double thr_d;
     int32_t thr_j;
+    Cand best[Q];
 
-    __device__ __forceinline__ void trim() {
-        c = trim_buffer(bd, bj, c, k, lane);
-        if (c == k) {
-            thr_d = bd[k - 1];
-            thr_j = bj[k - 1];
-        }
+    __device__ __forceinline__ void init(double *bd_, int32_t *bj_, int k_, int lane_) {
+        bd = bd_;
+        bj = bj_;
+        c = 0;
+        k = k_;
+        lane = lane_;
+        seen = 0;
+        thr_d = INFINITY;
+        thr_j = INT32_MAX;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) best[q] = Cand{INFINITY, INT32_MAX};
+    }
+
+    // merges the first 64 waiting candidates (fewer when they are the last)
+    __device__ __forceinline__ void merge() {
         wave_sync_lds();
+        Cand x{lane < c ? bd[lane] : INFINITY, lane < c ? bj[lane] : INT32_MAX};
+        // the rest moves to the front
+        const bool rest = lane + kWaveK < c;
+        const double rd = rest ? bd[lane + kWaveK] : 0.0;
+        const int32_t rj = rest ? bj[lane + kWaveK] : 0;
+        wave_sync_lds();
+        if (rest) {
+            bd[lane] = rd;
+            bj[lane] = rj;
+        }
+        seen = min(seen + min(c, kWaveK), Q * kWaveK);
+        c = max(c - kWaveK, 0);
+        sort64(x, lane);
+        // the last 64 of the list against the batch in reverse leave the Q * 64
+        // smallest, as a bitonic sequence in the last register; then the list
+        // is merged downwards
+        x = xor_lane<63>(x);
+        order_pair(best[Q - 1], x);
+        clean64(best[Q - 1], lane);
+#pragma unroll
+        for (int q = Q - 1; q > 0; --q) {
+            Cand r = xor_lane<63>(best[q]);
+            order_pair(best[q - 1], r);
+            best[q] = r;
+            clean64(best[q - 1], lane);
+            clean64(best[q], lane);
+        }
+        if (seen >= k) {
+            double d = best[0].d;
+            int32_t j = best[0].j;
+#pragma unroll
+            for (int q = 1; q < Q; ++q) {
+                d = (k - 1) / kWaveK == q ? best[q].d : d;
+                j = (k - 1) / kWaveK == q ? best[q].j : j;
+            }
+            const int at = (k - 1) % kWaveK;
+            thr_d = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(d), at),
+                                     __builtin_amdgcn_readlane(__double2loint(d), at));
+            thr_j = __builtin_amdgcn_readlane(j, at);
+        }
+    }
+
+    __device__ __forceinline__ void flush() {
+        while (c > 0) merge();
     }
 
     // one candidate per lane (valid lanes only); wave-uniform call
     __device__ __forceinline__ void consider(bool valid, double d, int32_t j) {
         const bool accept = valid && pair_less(d, j, thr_d, thr_j);
         const uint64_t mask = __ballot(accept);
+        if (mask == 0) return;
         const int below = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
         if (accept) {
@@ -248,8 +364,7 @@ struct TopK {
             bj[c + below] = j;
         }
         c += __popcll(mask);
-        wave_sync_lds();
-        if (c > kKnnCap - kWaveK) trim();
+        if (c >= kWaveK) merge();
     }
 };
 
@@ -283,14 +398,14 @@ __device__ __forceinline__ void ring_cell(int r, int e, int &dx, int &dy) {
 // least sin^2(a / 2) min(1, cos lat_q cos lat_min), cos lat_min the least
 // cosine over the points' latitudes (all in [-90, 90]).  A query whose
 // longitude span exceeds 180 degrees scans every cell.
-template <bool GCD>
+template <bool GCD, int Q>
 __global__ void __launch_bounds__(kKnnWaves *kWaveK) knn_query_kernel(
     const double *__restrict__ locs, int64_t n, const double *__restrict__ qlocs, int64_t nq, int32_t m,
     const double2 *__restrict__ sxy, const int32_t *__restrict__ sidx, const int32_t *__restrict__ cstart,
     const GridParams *__restrict__ gp, int g, const double *__restrict__ clat, const double *__restrict__ sclat,
     int32_t *__restrict__ nbr) {
-    __shared__ double sbd[kKnnWaves][kKnnCap];
-    __shared__ int32_t sbj[kKnnWaves][kKnnCap];
+    __shared__ double sbd[kKnnWaves][2 * kWaveK];
+    __shared__ int32_t sbj[kKnnWaves][2 * kWaveK];
     const int w = threadIdx.x / kWaveK, lane = threadIdx.x % kWaveK;
     const int64_t i = blockIdx.x * (int64_t)kKnnWaves + w;
     if (i >= nq) return;  // whole wavefront; the kernel has no workgroup barrier
@@ -305,7 +420,8 @@ __global__ void __launch_bounds__(kKnnWaves *kWaveK) knn_query_kernel(
     const double qx = qp[0], qy = qp[1];
     double cq = 0.0;
     if constexpr (GCD) cq = qlocs ? cos(qy * kDeg2Rad) : clat[i];
-    TopK top{sbd[w], sbj[w], 0, k, lane, INFINITY, INT32_MAX};
+    TopK<Q> top;
+    top.init(sbd[w], sbj[w], k, lane);
 
     if (lim <= kBruteMax) {
         for (int64_t base = 0; base < lim; base += kWaveK) {
@@ -328,12 +444,44 @@ __global__ void __launch_bounds__(kKnnWaves *kWaveK) knn_query_kernel(
             const double cmin = fmin(cos(p.y0 * kDeg2Rad), cos(p.ymax * kDeg2Rad));
             hfac = (span <= 180.0) ? fmin(1.0, cq * cmin) : 0.0;
         }
-        for (int r = 0;; ++r) {
-            const int ncell = (r == 0) ? 1 : 8 * r;
+        // the block: about two points per cell, a share lim / n of them
+        // eligible, so the m-th nearest is expected sqrt(m n / (2 pi lim))
+        // cells away; a tenth more and the query's place in its cell on top
+        const double want = sqrt((double)k * (double)n / (6.2831853 * (double)lim));
+        const int r0 = min((int)(1.1 * want + 0.6), g - 1);
+        const int x0 = max(cx - r0, 0), x1 = min(cx + r0, g - 1);
+        const int y0 = max(cy - r0, 0), y1 = min(cy + r0, g - 1);
+        // row y of the block is one run of the sorted points.  The wavefront
+        // takes rows in groups of 64 / S lanes' worth: S consecutive points of
+        // each of 64 / S rows at a time, S about the length of a run.
+        const int len = 2 * (x1 - x0 + 1);
+        const int S = len > 24 ? 64 : len > 10 ? 16 : 8;
+        const int sub = lane / S, off = lane % S, rows = kWaveK / S;
+        for (int y = y0; y <= y1; y += rows) {
+            const int Y = y + sub;
+            const bool have = Y <= y1;
+            int p0 = have ? cstart[Y * g + x0] + off : 0;
+            const int pe = have ? cstart[Y * g + x1 + 1] : 0;
+            while (__ballot(p0 < pe) != 0) {
+                const bool in = p0 < pe;
+                const int32_t j = in ? sidx[p0] : INT32_MAX;
+                const bool valid = in && j < lim;
+                double d = 0.0;
+                if (valid) {
+                    const double2 s = sxy[p0];
+                    if constexpr (GCD) d = hav_key(qx, qy, cq, s.x, s.y, sclat[p0]);
+                    else d = sqdist(qx, qy, s.x, s.y);
+                }
+                p0 += S;
+                top.consider(valid, d, j);
+            }
+        }
+        for (int r = r0;; ++r) {
+            const int ncell = (r == r0) ? 0 : 8 * r;  // the block is done
             for (int e0 = 0; e0 < ncell; e0 += kWaveK) {
                 const int e = e0 + lane;
                 int dx = 0, dy = 0;
-                if (r > 0 && e < ncell) ring_cell(r, e, dx, dy);
+                if (e < ncell) ring_cell(r, e, dx, dy);
                 const int X = cx + dx, Y = cy + dy;
                 const bool inside = e < ncell && X >= 0 && X < g && Y >= 0 && Y < g;
                 int32_t pp = inside ? cstart[Y * g + X] : 0;
@@ -356,8 +504,8 @@ __global__ void __launch_bounds__(kKnnWaves *kWaveK) knn_query_kernel(
             }
             const bool covered = cx - r <= 0 && cx + r >= g - 1 && cy - r <= 0 && cy + r >= g - 1;
             if (covered) break;
-            if (top.c >= k) {
-                if (top.c > k) top.trim();
+            if (top.seen + top.c >= k) {
+                top.flush();
                 // every unscanned point lies at least r cells off in x or y:
                 // its offset exceeds r h up to the rounding of the binning,
                 // which the margins cover
@@ -373,8 +521,12 @@ __global__ void __launch_bounds__(kKnnWaves *kWaveK) knn_query_kernel(
             }
         }
     }
-    top.trim();
-    for (int t = lane; t < m; t += kWaveK) out[t] = (t < top.c) ? top.bj[t] : -1;
+    top.flush();
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int t = q * kWaveK + lane;
+        if (t < m) out[t] = t < min(k, top.seen) ? top.best[q].j : -1;
+    }
 }
 
 __global__ void cos_lat_kernel(const double *__restrict__ locs, int64_t n, double *__restrict__ clat) {
@@ -679,16 +831,12 @@ int knn_run(const double *locs, int64_t n, const double *qlocs, int64_t nq, int3
         hipLaunchKernelGGL(gather_sorted_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, locs, n, sval,
                            (const double *)clat, sxy, sclat);
     }
-    if (gcd)
-        hipLaunchKernelGGL(knn_query_kernel<true>, dim3(blocks_for(nq, kKnnWaves)), dim3(kKnnWaves * kWaveK), 0, s,
-                           locs, n, qlocs, nq, m, (const double2 *)sxy, (const int32_t *)sval,
-                           (const int32_t *)cstart, (const GridParams *)gp, L.g, (const double *)clat,
-                           (const double *)sclat, nbr);
-    else
-        hipLaunchKernelGGL(knn_query_kernel<false>, dim3(blocks_for(nq, kKnnWaves)), dim3(kKnnWaves * kWaveK), 0, s,
-                           locs, n, qlocs, nq, m, (const double2 *)sxy, (const int32_t *)sval,
-                           (const int32_t *)cstart, (const GridParams *)gp, L.g, (const double *)nullptr,
-                           (const double *)nullptr, nbr);
+    // one instantiation per metric and length of the best list
+    auto kern = gcd ? (m <= 64 ? knn_query_kernel<true, 1> : m <= 128 ? knn_query_kernel<true, 2> : knn_query_kernel<true, 3>)
+                    : (m <= 64 ? knn_query_kernel<false, 1> : m <= 128 ? knn_query_kernel<false, 2> : knn_query_kernel<false, 3>);
+    hipLaunchKernelGGL(kern, dim3(blocks_for(nq, kKnnWaves)), dim3(kKnnWaves * kWaveK), 0, s, locs, n, qlocs, nq, m,
+                       (const double2 *)sxy, (const int32_t *)sval, (const int32_t *)cstart, (const GridParams *)gp, L.g,
+                       (const double *)clat, (const double *)sclat, nbr);
     return hipGetLastError() == hipSuccess ? VECCHIA_OK : VECCHIA_EHIP;
 }
 

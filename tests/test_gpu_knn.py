@@ -182,3 +182,30 @@ def test_conditioning_sets_replay_from_a_graph(v):
         junk = torch.randn(5000, device="cuda").sum()  # eager work between replays
         torch.cuda.synchronize()
         del junk
+
+
+@pytest.mark.parametrize("m", [63, 64, 65, 127, 128, 129])
+def test_best_list_lengths(v, m):
+    """Set sizes at the ends of the best list's 64-entry registers, brute-force and grid rows, with ties."""
+    rng = np.random.default_rng(300 + m)
+    locs = np.vstack([rng.uniform(size=(8300, 2)), rng.integers(0, 40, (900, 2)) / 40.0])
+    locs = locs[rng.permutation(len(locs))]
+    rows = np.concatenate([np.arange(0, 200), np.arange(8150, len(locs))])
+    got = gpu_knn(v, locs, m)
+    np.testing.assert_array_equal(got[rows], oracle.knn_rows(locs, m, rows=rows))
+
+
+def test_queries_far_outside_and_without_enough_finite_points(v):
+    import torch
+    rng = np.random.default_rng(377)
+    locs = rng.uniform(size=(9000, 2))
+    q = np.vstack([rng.uniform(size=(40, 2)), rng.uniform(-30, 30, (40, 2)), [[5.0, 0.5], [0.5, -9.0]]])
+    t = [torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in (locs, q)]
+    np.testing.assert_array_equal(v.vecchia_knn_query(*t, 70).cpu().numpy(), oracle.knn_query(locs, q, 70, 0))
+    few = np.full((9000, 2), np.nan)
+    few[100:103] = rng.uniform(size=(3, 2))
+    got = v.vecchia_knn_query(torch.from_numpy(few).cuda(), t[1][:5].contiguous(), 6).cpu().numpy()
+    for row, p in zip(got, q[:5]):
+        d = ((few[100:103] - p) ** 2).sum(1)
+        np.testing.assert_array_equal(row[:3], 100 + np.argsort(d, kind="stable"))
+        assert (row[3:] == -1).all()
