@@ -43,14 +43,18 @@ constexpr int kPutWords = 256;  // 8-byte words of table one writing launch carr
 struct PutChunk {
     uint64_t word0;  // first destination word
     uint32_t nwords;
-    uint32_t pad;
+    uint32_t nzero;  // counters to clear
     uint64_t w[kPutWords];
 };
 
-// Copies a chunk of the host-built table from the kernel arguments to the workspace.
-__global__ void __launch_bounds__(kPutWords) put_words_kernel(uint64_t *__restrict__ dst, const PutChunk c) {
+// Copies a chunk of the host-built table from the kernel arguments to the
+// workspace (block 0) and clears the counters.
+__global__ void __launch_bounds__(kPutWords) put_words_kernel(uint64_t *__restrict__ dst,
+                                                              int32_t *__restrict__ counter, const PutChunk c) {
     const uint32_t t = threadIdx.x;
-    if (t < c.nwords) dst[c.word0 + t] = c.w[t];
+    if (blockIdx.x == 0 && t < c.nwords) dst[c.word0 + t] = c.w[t];
+    for (uint64_t k = (uint64_t)blockIdx.x * kPutWords + t; k < c.nzero; k += (uint64_t)gridDim.x * kPutWords)
+        counter[k] = 0;
 }
 
 struct ClassPlan {
@@ -75,32 +79,34 @@ __device__ __forceinline__ int field_of_block(const FieldDev *__restrict__ field
     return lo;
 }
 
-__global__ void __launch_bounds__(kReduceThreads) batched_reduce_kernel(const double *__restrict__ vals,
-                                                                        const int32_t *__restrict__ flags,
-                                                                        const FieldDev *__restrict__ fields,
-                                                                        int32_t nf, double *__restrict__ partial,
-                                                                        int64_t *__restrict__ pfail) {
+// Fixed-order sums of every evaluation with points; block b of the launch is
+// reduce block b of the plan, and the last block of an evaluation finishes it
+// (counter[e] starts at 0).
+__global__ void __launch_bounds__(kReduceThreads) batched_reduce_kernel(
+    const double *__restrict__ vals, const int32_t *__restrict__ flags, const FieldDev *__restrict__ fields, int32_t nf,
+    double *partial, int64_t *pfail, int32_t *counter, const double *__restrict__ thetas, double *__restrict__ out,
+    double *__restrict__ grad, int64_t *__restrict__ status) {
     const int64_t b = blockIdx.x;
     const FieldDev F = fields[field_of_block(fields, nf, b)];
     const int64_t q = (b - F.pb0) / F.nb;
     const int64_t v0 = F.vals0 + q * F.n;
-    reduce_segment_block(vals + 4 * v0, flags + v0, F.n, b - F.pb0 - q * F.nb, partial + 8 * b, pfail + b);
+    const int64_t p0 = F.pb0 + q * F.nb, e = F.eval0 + q;
+    reduce_segment_block(vals + 4 * v0, flags + v0, F.n, b - p0, partial + 8 * b, pfail + b);
+    if (last_block_of_segment(counter + e, F.nb))
+        finalize_segment(partial + 8 * p0, pfail + p0, F.nb, thetas + 3 * e, out + e, grad ? grad + 3 * e : nullptr,
+                         status + e);
 }
 
-__global__ void __launch_bounds__(kFinalizeThreads) batched_finalize_kernel(const double *__restrict__ partial,
-                                                                            const int64_t *__restrict__ pfail,
-                                                                            const FieldDev *__restrict__ fields,
+// The evaluations of fields without points.
+__global__ void __launch_bounds__(kFinalizeThreads) batched_finalize_kernel(const FieldDev *__restrict__ fields,
                                                                             int32_t ntheta,
                                                                             const double *__restrict__ thetas,
                                                                             double *__restrict__ out,
                                                                             double *__restrict__ grad,
                                                                             int64_t *__restrict__ status) {
     const int64_t e = blockIdx.x;
-    const FieldDev F = fields[e / ntheta];
-    const int64_t q = e % ntheta;
-    const int64_t p0 = F.pb0 + q * F.nb;
-    finalize_segment(partial + 8 * p0, pfail + p0, F.nb, thetas + 3 * e, out + e, grad ? grad + 3 * e : nullptr,
-                     status + e);
+    if (fields[e / ntheta].nb > 0) return;
+    finalize_segment(nullptr, nullptr, 0, thetas + 3 * e, out + e, grad ? grad + 3 * e : nullptr, status + e);
 }
 
 }  // namespace
@@ -114,6 +120,8 @@ struct vecchia_plan {
     std::vector<ClassPlan> classes;
     int64_t total_rows = 0, total_pblocks = 0;
     std::vector<uint64_t> table;  // host image of the device table (fields, class lists), 8-byte words
+    bool any_empty = false;  // some field has no points
+    size_t ws_counter = 0;   // finished reduce blocks per evaluation
     size_t ws_vals = 0, ws_flags = 0, ws_partial = 0, ws_pfail = 0, ws_bytes = 0;
 };
 
@@ -135,16 +143,19 @@ int run_batched(const vecchia_plan *p, const double *thetas, double *out, double
     int32_t *flags = (int32_t *)(w + p->ws_flags);
     double *partial = (double *)(w + p->ws_partial);
     int64_t *pfail = (int64_t *)(w + p->ws_pfail);
+    int32_t *counter = (int32_t *)(w + p->ws_counter);
     const FieldDev *dfields = (const FieldDev *)w;  // the field array opens the table
 
-    // 1. the device table, from the kernel arguments of a few small launches
+    // 1. the device table, from the kernel arguments of a few small launches;
+    // the first one clears the counts of finished reduce blocks
     for (size_t w0 = 0; w0 < p->table.size(); w0 += kPutWords) {
         PutChunk c;
         c.word0 = w0;
         c.nwords = (uint32_t)std::min<size_t>(kPutWords, p->table.size() - w0);
-        c.pad = 0;
+        c.nzero = w0 == 0 ? (uint32_t)((int64_t)p->nf * p->ntheta) : 0;
         std::copy(p->table.begin() + w0, p->table.begin() + w0 + c.nwords, c.w);
-        hipLaunchKernelGGL(put_words_kernel, dim3(1), dim3(kPutWords), 0, s, table, c);
+        const uint32_t nb = std::min<uint32_t>(c.nzero / (8 * kPutWords) + 1, 1024);
+        hipLaunchKernelGGL(put_words_kernel, dim3(nb), dim3(kPutWords), 0, s, table, counter, c);
     }
     const int nc = (int)p->classes.size();
     // 2. one launch per tile class
@@ -186,11 +197,13 @@ int run_batched(const vecchia_plan *p, const double *thetas, double *out, double
         if (rc != VECCHIA_OK) return rc;
     }
     // 3. fixed-order sums per evaluation
+    double *g = p->grad ? grad : nullptr;
     if (p->total_pblocks > 0)
         hipLaunchKernelGGL(batched_reduce_kernel, dim3((unsigned)p->total_pblocks), dim3(kReduceThreads), 0, s, vals,
-                           flags, dfields, p->nf, partial, pfail);
-    hipLaunchKernelGGL(batched_finalize_kernel, dim3((unsigned)((int64_t)p->nf * p->ntheta)), dim3(kFinalizeThreads),
-                       0, s, partial, pfail, dfields, p->ntheta, thetas, out, p->grad ? grad : nullptr, status);
+                           flags, dfields, p->nf, partial, pfail, counter, thetas, out, g, status);
+    if (p->any_empty)
+        hipLaunchKernelGGL(batched_finalize_kernel, dim3((unsigned)((int64_t)p->nf * p->ntheta)),
+                           dim3(kFinalizeThreads), 0, s, dfields, p->ntheta, thetas, out, g, status);
     return hipGetLastError() == hipSuccess ? VECCHIA_OK : VECCHIA_EHIP;
 }
 
@@ -240,6 +253,7 @@ int plan_build(const vecchia_field *fields, int32_t nf, int32_t ntheta, const ve
         d.pb0 = pblocks;
         d.nb = num_reduce_blocks(d.n);
         pblocks += (int64_t)ntheta * d.nb;
+        p->any_empty |= d.nb == 0;
         rows += (int64_t)ntheta * d.n;
         p->fields.push_back(d);
     }
@@ -294,7 +308,7 @@ int plan_build(const vecchia_field *fields, int32_t nf, int32_t ntheta, const ve
         append_words(p->table, C.off_fidx, C.fidx.data(), C.fidx.size());
         append_words(p->table, C.off_item0, C.item0.data(), C.item0.size());
     }
-    // workspace layout: table, per-row values and flags, reduce partials
+    // workspace layout: table, per-row values and flags, reduce partials, counts
     size_t w = off;
     p->ws_vals = w;
     w = align256(w + (size_t)rows * 4 * sizeof(double));
@@ -304,6 +318,8 @@ int plan_build(const vecchia_field *fields, int32_t nf, int32_t ntheta, const ve
     w = align256(w + (size_t)pblocks * 8 * sizeof(double));
     p->ws_pfail = w;
     w = align256(w + (size_t)pblocks * sizeof(int64_t));
+    p->ws_counter = w;
+    w = align256(w + (size_t)nf * (size_t)ntheta * sizeof(int32_t));
     p->ws_bytes = w + 256;
     *plan = p;
     return VECCHIA_OK;

@@ -95,6 +95,7 @@ struct KernelArgs {
     double *g;
     int64_t g_stride;
     int32_t *flags;
+    int32_t *counter;  // set to 0 for the reduction that follows (when given)
     unsigned long long *status;
     int64_t t0;
     int64_t row0;  // single mode: results of item t go to row t - row0
@@ -180,6 +181,7 @@ template <class Impl>
 __global__ void __launch_bounds__(Impl::NT) __attribute__((amdgpu_waves_per_eu(Impl::WPE)))
     cond_kernel(const KernelArgs a) {
     extern __shared__ double smem[];
+    if (a.counter && blockIdx.x == 0 && threadIdx.x == 0) *a.counter = 0;
     cond_item<Impl>(a, a.t0 + blockIdx.x, smem);
 }
 
@@ -262,6 +264,7 @@ __global__ void __launch_bounds__(kRowsWaves *kWave)
     __attribute__((amdgpu_waves_per_eu(RowsImpl<T, KC, GRAD>::WPE)))
     rows_kernel(const KernelArgs a, int64_t t_end) {
     extern __shared__ double smem[];
+    if (a.counter && blockIdx.x == 0 && threadIdx.x == 0) *a.counter = 0;
     double *ET = smem;
     stage_tables<KC>((int)threadIdx.x, ET);
     __syncthreads();

@@ -5,7 +5,9 @@
 //            ascending order; the block combines its 256 sums in a fixed tree
 //            (double-double) into one partial;
 //   level 2  one block adds the partials of the segment in a fixed strided
-//            order and tree (double-double) and writes the outputs.
+//            order and tree (double-double) and writes the outputs: the block
+//            of level 1 that finishes last (a kernel of its own cost its
+//            launch and 4-6 us).
 // The order depends only on n, so a segment gives bitwise the same result in
 // the single and the batched entry points.
 #pragma once
@@ -16,7 +18,7 @@
 namespace vecchia {
 
 constexpr int kReduceThreads = 256;
-constexpr int kFinalizeThreads = 256;
+constexpr int kFinalizeThreads = kReduceThreads;  // the last reduce block goes on to level 2
 constexpr int64_t kPointsPerReduceBlock = (int64_t)kChunk * kReduceThreads;
 
 __host__ __device__ inline int64_t num_reduce_blocks(int64_t n) {
@@ -30,21 +32,47 @@ __host__ __device__ inline int64_t num_reduce_blocks(int64_t n) {
 // kNoFailure).  Called by every thread of a kReduceThreads-thread block.
 __device__ __forceinline__ void reduce_segment_block(const double *__restrict__ vals,
                                                      const int32_t *__restrict__ flags, int64_t n, int64_t bx,
-                                                     double *__restrict__ partial, int64_t *__restrict__ pfail,
-                                                     int64_t row0 = 0) {
+                                                     double *partial, int64_t *pfail, int64_t row0 = 0) {
     __shared__ DD sh[4][kReduceThreads];
     __shared__ int64_t shf[kReduceThreads];
     const int t = threadIdx.x;
     const int64_t i0 = (bx * kReduceThreads + t) * kChunk;
     double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
     int64_t f = kNoFailure;
-    for (int64_t i = i0; i < i0 + kChunk && i < n; ++i) {
-        const int64_t r = i - row0;
-        a0 += vals[4 * r + 0];
-        a1 += vals[4 * r + 1];
-        a2 += vals[4 * r + 2];
-        a3 += vals[4 * r + 3];
-        if (flags[r] && f == kNoFailure) f = i + 1;
+    if (i0 + kChunk <= n) {
+        // a thread's rows are 512 consecutive bytes: half of them in flight at
+        // a time, where one row after the other waits 16 times for memory
+        // (20,000 points: 10.8 us)
+        constexpr int kBatch = kChunk / 2;
+        int32_t fl[kChunk];
+#pragma unroll
+        for (int c = 0; c < kChunk; ++c) fl[c] = flags[i0 - row0 + c];
+#pragma unroll
+        for (int b = 0; b < kChunk; b += kBatch) {
+            double v[kBatch][4];
+#pragma unroll
+            for (int c = 0; c < kBatch; ++c)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) v[c][q] = vals[4 * (i0 - row0 + b + c) + q];
+#pragma unroll
+            for (int c = 0; c < kBatch; ++c) {
+                a0 += v[c][0];
+                a1 += v[c][1];
+                a2 += v[c][2];
+                a3 += v[c][3];
+            }
+        }
+#pragma unroll
+        for (int c = kChunk - 1; c >= 0; --c) f = fl[c] ? i0 + c + 1 : f;
+    } else {
+        for (int64_t i = i0; i < i0 + kChunk && i < n; ++i) {
+            const int64_t r = i - row0;
+            a0 += vals[4 * r + 0];
+            a1 += vals[4 * r + 1];
+            a2 += vals[4 * r + 2];
+            a3 += vals[4 * r + 3];
+            if (flags[r] && f == kNoFailure) f = i + 1;
+        }
     }
     sh[0][t] = DD{a0, 0.0};
     sh[1][t] = DD{a1, 0.0};
@@ -70,11 +98,28 @@ __device__ __forceinline__ void reduce_segment_block(const double *__restrict__ 
     }
 }
 
+// Whether the calling block is the last of the `nblocks` level-1 blocks of its
+// segment to get here.  Thread 0 has written the block's partial; the counter
+// starts at 0.  Called by every thread; on true the partials of all the
+// blocks are visible.
+__device__ __forceinline__ bool last_block_of_segment(int32_t *counter, int64_t nblocks) {
+    __shared__ int32_t last;
+    if (nblocks == 1) {
+        __syncthreads();
+        return true;
+    }
+    if (threadIdx.x == 0)
+        last = __hip_atomic_fetch_add(counter, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (int32_t)(nblocks - 1);
+    __syncthreads();
+    if (!last) return false;
+    __threadfence();
+    return true;
+}
+
 // Level 2 for one segment: partial [nblocks][8], pfail [nblocks]; writes
 // out[0], grad[0..3) (if grad) and status[0].  Called by every thread of a
 // kFinalizeThreads-thread block.
-__device__ __forceinline__ void finalize_segment(const double *__restrict__ partial,
-                                                 const int64_t *__restrict__ pfail, int64_t nblocks,
+__device__ __forceinline__ void finalize_segment(const double *partial, const int64_t *pfail, int64_t nblocks,
                                                  const double *__restrict__ theta, double *__restrict__ out,
                                                  double *__restrict__ grad, int64_t *__restrict__ status) {
     __shared__ DD sh[4][kFinalizeThreads];

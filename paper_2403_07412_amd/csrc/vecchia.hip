@@ -1,15 +1,15 @@
 // C ABI and launch logic of the Vecchia log-likelihood library (gfx950).
 //
 // Pipeline of one evaluation (Algorithm 1, fused):
-//   conditional kernel  one workgroup per point i: gathers the neighbours,
-//                       builds the covariance block, factors it, solves, forms
-//                       l_i (and its gradient) and writes the four values and
-//                       a failure flag for i;
+//   conditional kernel  one workgroup, wavefront or row group per point i:
+//                       gathers the neighbours, builds the covariance block,
+//                       factors it, solves, forms l_i (and its gradient) and
+//                       writes the four values and a failure flag for i;
 //   reduce kernel       every thread adds a fixed chunk of kChunk consecutive
 //                       points in ascending order; each workgroup combines its
-//                       threads' sums in a fixed tree (double-double);
-//   finalize kernel     sums the workgroup partials in a fixed order and writes
-//                       l, the gradient and the status.
+//                       threads' sums in a fixed tree (double-double); the last
+//                       workgroup to finish sums the partials in a fixed order
+//                       and writes l, the gradient and the status.
 // All summation orders are fixed, so results are bitwise reproducible
 // whatever order the hardware runs the workgroups in.
 #include <hip/hip_runtime.h>
@@ -82,12 +82,14 @@ namespace {
 size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 
 // Workspace layout: per-point values [n][4] double, per-point flags [n] int32,
-// then per-reduce-block partials [nb][4] double-double and first failures [nb] int64.
+// then per-reduce-block partials [nb][4] double-double and first failures [nb] int64,
+// and the count of finished reduce blocks (in the 256 bytes at the end).
 struct WsLayout {
     double *vals;
     int32_t *flags;
     double *partial;
     int64_t *pfail;
+    int32_t *counter;
     size_t bytes;
 };
 
@@ -104,14 +106,19 @@ WsLayout ws_layout(void *ws, int64_t n) {
     L.flags = (int32_t *)(base + vbytes);
     L.partial = (double *)(base + vbytes + fbytes);
     L.pfail = (int64_t *)(base + vbytes + fbytes + pbytes);
+    L.counter = (int32_t *)(base + vbytes + fbytes + pbytes + qbytes);
     return L;
 }
 
 __global__ void __launch_bounds__(kReduceThreads) reduce_kernel(const double *__restrict__ vals,
                                                                 const int32_t *__restrict__ flags, int64_t n,
-                                                                double *__restrict__ partial,
-                                                                int64_t *__restrict__ pfail) {
+                                                                double *partial, int64_t *pfail, int32_t *counter,
+                                                                const double *__restrict__ theta,
+                                                                double *__restrict__ out, double *__restrict__ grad,
+                                                                int64_t *__restrict__ status) {
     reduce_segment_block(vals, flags, n, blockIdx.x, partial + 8 * (int64_t)blockIdx.x, pfail + blockIdx.x);
+    if (last_block_of_segment(counter, gridDim.x))
+        finalize_segment(partial, pfail, gridDim.x, theta, out, grad, status);
 }
 
 __global__ void status_init_kernel(unsigned long long *status) {
@@ -172,6 +179,7 @@ int run_sum(const double *locs, const double *z, const int32_t *nbr, int64_t n, 
     a.k.g = L.vals + 1;
     a.k.g_stride = 4;
     a.k.flags = L.flags;
+    a.k.counter = L.counter;
     a.k.alpha = alpha;
     a.t_begin = 0;
     a.t_end = n;
@@ -181,9 +189,10 @@ int run_sum(const double *locs, const double *z, const int32_t *nbr, int64_t n, 
     const int64_t nb = num_reduce_blocks(n);
     if (nb > 0)
         hipLaunchKernelGGL(reduce_kernel, dim3((unsigned)nb), dim3(kReduceThreads), 0, s, L.vals, L.flags, n,
-                           L.partial, L.pfail);
-    hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(kFinalizeThreads), 0, s, L.partial, L.pfail, nb, theta, out,
-                       with_grad ? grad : nullptr, status);
+                           L.partial, L.pfail, L.counter, theta, out, with_grad ? grad : nullptr, status);
+    else
+        hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(kFinalizeThreads), 0, s, L.partial, L.pfail, nb, theta, out,
+                           with_grad ? grad : nullptr, status);
     return hipGetLastError() == hipSuccess ? VECCHIA_OK : VECCHIA_EHIP;
 }
 
