@@ -607,41 +607,56 @@ __device__ __forceinline__ double maxmin_side(const GridParams &p) {
     return (w > 0.0) ? w : 1.0;
 }
 
-__device__ __forceinline__ unsigned long long wave_min_u64(unsigned long long v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        const unsigned long long o = __shfl_xor(v, off, kWaveK);
-        v = o < v ? o : v;
-    }
-    return v;
+// phase 1: the least squared distance of each cell (non-negative doubles
+// order as their bit patterns).  Atomics on one address take 11.6 ns each and
+// spread ones 0.1 ns, so what counts is how many are issued:
+//   grids of up to kStagedCells cells  a workgroup keeps the cells in LDS over
+//                all its points and adds at most one atomic per cell;
+//   finer grids  a point issues one only below the cell's current value, read
+//                past the caches (a line that an XCD has read once stays stale
+//                there for the rest of the kernel), and the launch holds at
+//                most kDistBlocks workgroups, so that later points meet cells
+//                that earlier ones have lowered.
+constexpr int kStagedCells = 256;
+constexpr int kStagedBlocks = 256, kStagedThreads = 1024;
+constexpr int kDistBlocks = 1024;
+
+__device__ __forceinline__ void lower_cell(unsigned long long *__restrict__ cell, unsigned long long key) {
+    if (key < __hip_atomic_load(cell, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(cell, key);
 }
 
-// phase 1: the least squared distance of each cell (non-negative doubles
-// order as their bit patterns).  On the coarse grids (at most 16 cells) every
-// wavefront first takes the minimum per cell, so a cell sees one atomic per
-// wavefront instead of one per point.  An atomic is issued only below the
-// value read just before it (cells only decrease, so a stale value costs an
-// atomic and no more): without that the grids of 64 to 4096 cells queued 500,000
-// points on few addresses (148 us a round on average; now 8).
+__global__ void __launch_bounds__(kStagedThreads)
+    maxmin_dist_staged_kernel(const double *__restrict__ locs, int64_t n, const GridParams *__restrict__ gp, int64_t G,
+                              const int32_t *__restrict__ sel, unsigned long long *__restrict__ cd) {
+    __shared__ unsigned long long cell[kStagedCells];
+    const int cells = (int)(G * G);
+    if ((int)threadIdx.x < cells) cell[threadIdx.x] = ~0ull;
+    __syncthreads();
+    const GridParams p = *gp;
+    const double w = maxmin_side(p);
+    for (int64_t i = blockIdx.x * (int64_t)kStagedThreads + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * kStagedThreads) {
+        if (sel[i]) continue;
+        int64_t c;
+        double d;
+        maxmin_pos(locs, i, p, w, G, c, d);
+        const unsigned long long key = (unsigned long long)__double_as_longlong(d);
+        if (key < cell[c]) atomicMin(cell + c, key);
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < cells && cell[threadIdx.x] != ~0ull) lower_cell(cd + threadIdx.x, cell[threadIdx.x]);
+}
+
 __global__ void maxmin_dist_kernel(const double *__restrict__ locs, int64_t n, const GridParams *__restrict__ gp,
                                    int64_t G, const int32_t *__restrict__ sel, unsigned long long *__restrict__ cd) {
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    const bool active = i < n && !sel[i];
-    int64_t c = 0;
-    double d = 0.0;
-    if (active) {
-        const GridParams p = *gp;
-        maxmin_pos(locs, i, p, maxmin_side(p), G, c, d);
-    }
-    const unsigned long long key = (unsigned long long)__double_as_longlong(d);
-    if (G * G <= 16) {  // uniform over the launch
-        const int lane = threadIdx.x % kWaveK;
-        for (int64_t cc = 0; cc < G * G; ++cc) {
-            const unsigned long long v = wave_min_u64((active && c == cc) ? key : ~0ull);
-            if (lane == 0 && v < cd[cc]) atomicMin(cd + cc, v);
-        }
-    } else if (active) {
-        if (key < cd[c]) atomicMin(cd + c, key);
+    const GridParams p = *gp;
+    const double w = maxmin_side(p);
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        if (sel[i]) continue;
+        int64_t c;
+        double d;
+        maxmin_pos(locs, i, p, w, G, c, d);
+        lower_cell(cd + c, (unsigned long long)__double_as_longlong(d));
     }
 }
 
@@ -659,12 +674,14 @@ __global__ void maxmin_index_kernel(const double *__restrict__ locs, int64_t n, 
 }
 
 // phase 3: elected points (all unselected ones when G == 0) take the round's
-// number; `count` collects how many, one atomic per wavefront
+// number.  From the finest grid on every block also writes how many of its
+// points are left (one atomic per wavefront on a common count took 91 us).
 __global__ void maxmin_elect_kernel(const double *__restrict__ locs, int64_t n, const GridParams *__restrict__ gp,
                                     int64_t G, int32_t round, int32_t *__restrict__ sel,
-                                    const int32_t *__restrict__ ci, int32_t *__restrict__ count) {
+                                    const int32_t *__restrict__ ci, int32_t *__restrict__ block_left) {
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    bool elected = i < n && !sel[i];
+    const bool open = i < n && !sel[i];
+    bool elected = open;
     if (elected && G > 0) {
         const GridParams p = *gp;
         int64_t c;
@@ -673,8 +690,24 @@ __global__ void maxmin_elect_kernel(const double *__restrict__ locs, int64_t n, 
         elected = ci[c] == (int32_t)i;
     }
     if (elected) sel[i] = round;
-    const uint64_t mask = __ballot(elected);
-    if (mask && threadIdx.x % kWaveK == 0) atomicAdd(count, (int32_t)__popcll(mask));
+    if (!block_left) return;
+    const int left = __syncthreads_count(open && !elected);
+    if (threadIdx.x == 0) block_left[blockIdx.x] = left;
+}
+
+__global__ void __launch_bounds__(1024) maxmin_left_kernel(const int32_t *__restrict__ block_left, int32_t blocks,
+                                                           int32_t *__restrict__ left) {
+    __shared__ int32_t sum[1024 / kWaveK];
+    int32_t v = 0;
+    for (int32_t b = threadIdx.x; b < blocks; b += 1024) v += block_left[b];
+#pragma unroll
+    for (int off = kWaveK / 2; off >= 1; off >>= 1) v += __shfl_xor(v, off, kWaveK);
+    if (threadIdx.x % kWaveK == 0) sum[threadIdx.x / kWaveK] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int k = 1; k < 1024 / kWaveK; ++k) v += sum[k];
+        *left = v;
+    }
 }
 
 // both cell arrays of a round
@@ -967,37 +1000,44 @@ extern "C" int vecchia_maxmin_order(const double *locs, int64_t n, uint64_t seed
     int32_t *ci = (int32_t *)(base + L.ci);
     uint64_t *key = (uint64_t *)(base + L.key), *skey = (uint64_t *)(base + L.skey);
     int32_t *val = (int32_t *)(base + L.val), *sval = (int32_t *)(base + L.sval);
-    int32_t *count = (int32_t *)(base + L.count);
+    int32_t *left = (int32_t *)(base + L.count);
+    int32_t *block_left = (int32_t *)key;  // the keys come after the rounds
     const int lmax = maxmin_levels(n);
     const int nb = blocks_for(n, 256);
     hipLaunchKernelGGL(box_partial_kernel, dim3(kBoxBlocks), dim3(256), 0, s, locs, n, part);
     hipLaunchKernelGGL(box_final_kernel, dim3(1), dim3(kBoxBlocks), 0, s, part, 0, gp);
     hipLaunchKernelGGL(fill_int_kernel, dim3(std::min(nb, 4096)), dim3(256), 0, s, sel, n, 0);
-    hipLaunchKernelGGL(fill_int_kernel, dim3(1), dim3(64), 0, s, count, 1, 0);
     // every point gets its round first; the number of points left is read back
     // only from the finest grid on, the first that can finish
-    int32_t done = 0;
-    for (int r = 0; done < n; ++r) {
+    int32_t todo = (int32_t)n;
+    for (int r = 0; todo > 0; ++r) {
         const bool last = r >= lmax + 33;
         const int64_t G = last ? 0 : (int64_t)1 << std::min(r, lmax);
         if (!last) {
             const int64_t cells = G * G;
             hipLaunchKernelGGL(maxmin_clear_kernel, dim3(std::min(blocks_for(cells, 256), 4096)), dim3(256), 0, s, cd,
                                ci, cells);
-            hipLaunchKernelGGL(maxmin_dist_kernel, dim3(nb), dim3(256), 0, s, locs, n, (const GridParams *)gp, G,
-                               (const int32_t *)sel, cd);
+            if (cells <= kStagedCells)
+                hipLaunchKernelGGL(maxmin_dist_staged_kernel,
+                                   dim3(std::min(blocks_for(n, kStagedThreads), kStagedBlocks)), dim3(kStagedThreads),
+                                   0, s, locs, n, (const GridParams *)gp, G, (const int32_t *)sel, cd);
+            else
+                hipLaunchKernelGGL(maxmin_dist_kernel, dim3(std::min(nb, kDistBlocks)), dim3(256), 0, s, locs, n,
+                                   (const GridParams *)gp, G, (const int32_t *)sel, cd);
             hipLaunchKernelGGL(maxmin_index_kernel, dim3(nb), dim3(256), 0, s, locs, n, (const GridParams *)gp, G,
                                (const int32_t *)sel, (const unsigned long long *)cd, ci);
         }
         hipLaunchKernelGGL(maxmin_elect_kernel, dim3(nb), dim3(256), 0, s, locs, n, (const GridParams *)gp, G, r + 1,
-                           sel, (const int32_t *)ci, count);
+                           sel, (const int32_t *)ci, r < lmax ? nullptr : block_left);
+        if (r >= lmax)
+            hipLaunchKernelGGL(maxmin_left_kernel, dim3(1), dim3(1024), 0, s, (const int32_t *)block_left, nb, left);
         if (hipGetLastError() != hipSuccess) return VECCHIA_EHIP;
         if (r < lmax) continue;
-        const int32_t before = done;
-        if (hipMemcpyAsync(&done, count, sizeof(done), hipMemcpyDeviceToHost, s) != hipSuccess ||
+        const int32_t before = todo;
+        if (hipMemcpyAsync(&todo, left, sizeof(todo), hipMemcpyDeviceToHost, s) != hipSuccess ||
             hipStreamSynchronize(s) != hipSuccess)
             return VECCHIA_EHIP;
-        if (done <= before || done > n) return VECCHIA_EHIP;  // every round elects at least one point
+        if (todo < 0 || (r > lmax && todo >= before)) return VECCHIA_EHIP;  // every round elects at least one point
     }
     // one sort by hash, then a stable one by round (at most lmax + 34 < 64)
     hipLaunchKernelGGL(random_key_kernel, dim3(nb), dim3(256), 0, s, n, seed, key, val);

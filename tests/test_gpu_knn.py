@@ -209,3 +209,16 @@ def test_queries_far_outside_and_without_enough_finite_points(v):
         d = ((few[100:103] - p) ** 2).sum(1)
         np.testing.assert_array_equal(row[:3], 100 + np.argsort(d, kind="stable"))
         assert (row[3:] == -1).all()
+
+
+@pytest.mark.parametrize("n,distinct", [(1025, 0), (262_145, 0), (300_001, 0), (300_001, 4000)])
+def test_maxmin_order_over_many_blocks(v, n, distinct):
+    """More points than one workgroup of the coarse grids and one sweep of the fine ones hold, also with
+    coincident points (which tie in every round and stay for the late ones)."""
+    import torch
+    rng = np.random.default_rng(8100 + n)
+    locs = rng.uniform(size=(n, 2))
+    if distinct:
+        locs[n - distinct:] = locs[rng.integers(0, n - distinct, distinct)]
+    got = v.vecchia_maxmin_order(torch.from_numpy(locs).cuda(), seed=3)
+    np.testing.assert_array_equal(got.cpu().numpy(), oracle.maxmin_order(locs, 3))
