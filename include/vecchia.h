@@ -206,10 +206,14 @@ int vecchia_predict(const double *locs, const double *z, int64_t n, const double
  *                              or 8 wavefronts, Cholesky blocked by tile columns
  *                              with FP64 matrix-core trailing updates.
  * VECCHIA_VARIANT_AUTO uses the per-(m, gradient) table below, or a built-in
- * default: one wavefront up to 62 neighbours with the gradient (and without
- * it for the Matern codes on Euclidean distances; two for the other codes
- * and for kriging from 31 to 62), two up to 94, four beyond.  A tile variant
- * is feasible when each wavefront holds at most 20 tiles;
+ * default.  For the Matern codes on Euclidean distances: one wavefront up to
+ * 78 neighbours, two from 79 to 94 with the gradient and from 95 to 110
+ * without it, else four.  For the other codes: one up to 46; up to 62 four
+ * for values of the power exponential and one otherwise; up to 78 one for
+ * the gradient of the Euclidean power exponential and four otherwise; from
+ * 79 four (eight for great-circle values from 143 to 158).
+ * vecchia_get_variant reports the Matern choice.  A tile variant is feasible
+ * when each wavefront holds at most 20 tiles;
  * vecchia_variant_feasible reports it.
  */
 enum vecchia_variant {

@@ -435,20 +435,40 @@ inline bool variant_feasible(int variant, int m) {
     return tiles_per_wave(T, W) <= 20;
 }
 
-// Built-in choice when the variant table has no entry: the fastest variant
-// per tile count measured on MI355X (value and value + gradient, nu = 1/2,
-// 3/2, 5/2, 60,000 to 300,000 uniform points).  One wavefront up to four tile
-// rows (the rows kernel, for the Matern codes on Euclidean distances), except
-// for values of the other codes at four rows, where two wavefronts of tiles
-// are faster (great-circle power exponential, 100,000 points, m = 60: 1.72
-// against 2.13 ms; m = 40: 1.17 against 1.06 ms).  Up to six rows two
-// wavefronts; beyond, four (eight wavefronts lose to their barriers at every
-// size).  kc < 0: the code is not known.
-inline int default_variant(int m, bool grad, int kc = -1) {
+// Built-in choice when the variant table has no entry: the fastest wavefront
+// count per tile rows, measured on MI355X (ms; 40,000 uniform points, 20,000
+// from nine tile rows on).  It does not depend on the number of points, and a
+// value is bitwise the same under any wavefront count of the tiles.
+//   Matern, Euclidean (nu = 3/2; 1/2 and 5/2 agree within 2 %)
+//     rows 5   value  W1 0.53  W2 0.59          gradient  W1 0.75  W2 0.87
+//          6          W2 0.91  W4 0.87                    W2 1.31  W4 1.37
+//          7          W2 1.22  W4 1.28                    W2 1.92  W4 1.75
+//          8          W2 1.99  W4 1.56                    W2 2.94  W4 2.17
+//          9          W4 1.20  W8 1.32                    W4 1.67  W8 1.89
+//         10          W4 1.49  W8 1.58                    W4 2.05  W8 2.25
+//   power exponential, Euclidean
+//     rows 4   value  W1 0.51  W2 0.55  W4 0.50   gradient  W1 0.74  W2 0.82
+//          5          W1 0.79  W2 0.85  W4 0.76             W1 1.18  W4 1.22
+//          6          W2 1.24  W4 1.07                      W2 1.86  W4 1.81
+//         10          W4 1.91  W8 1.91                      W4 2.74  W8 2.90
+//   great circle, Matern 3/2 (power exponential)
+//     rows 3   value  W1 0.38 (0.44)  W2 0.40 (0.48)    gradient  W1 0.51 (0.58)  W2 0.56 (0.65)
+//          4          W1 0.58 (0.69)  W4 0.60 (0.68)              W1 0.76 (0.88)  W2 0.86 (1.02)
+//          5          W1 0.94 (1.28)  W4 0.87 (1.00)              W1 1.33 (1.89)  W4 1.29 (1.66)
+//          6          W2 1.35 (1.63)  W4 1.26 (1.48)              W2 2.00 (2.48)  W4 1.94 (2.30)
+//          8          W2 3.32 (3.62)  W4 2.48 (2.47)              (W2 6.01  W4 3.73)
+//         10          W4 2.59 (2.96)  W8 2.01 (2.25)              W4 3.87 (3.87)  W8 4.16 (4.52)
+inline int default_variant(int m, bool grad, int kc) {
     const int T = tile_rows(m);
     if (T <= 3) return V_TILE_W1;
-    if (T <= 4) return (grad || (kc >= 0 && kc <= 2)) ? V_TILE_W1 : V_TILE_W2;
-    if (T <= 6) return V_TILE_W2;
+    if (kc < 3) {
+        if (T <= 5) return V_TILE_W1;
+        if (T == (grad ? 6 : 7)) return V_TILE_W2;
+        return V_TILE_W4;
+    }
+    if (T == 4) return grad || (kc & 3) != 3 ? V_TILE_W1 : V_TILE_W4;
+    if (T == 5 && grad && kc == 3) return V_TILE_W1;
+    if (T == 10 && !grad && kc >= 4) return V_TILE_W8;
     return V_TILE_W4;
 }
 
@@ -520,7 +540,7 @@ int launch_variant(int variant, const EvalArgs &a, hipStream_t s) {
 // variant table, and the launcher for any covariance code (0..7).
 int nu_code(double nu);
 int cov_code(const vecchia_cov *cov, double *alpha);
-int resolve_variant(int m, bool grad, int requested, int kc = -1);
+int resolve_variant(int m, bool grad, int requested, int kc);
 extern int g_variant[2][VECCHIA_MAX_M + 1];
 int launch_any(int kc, bool grad, int variant, const EvalArgs &a, hipStream_t s);
 

@@ -100,7 +100,7 @@ extern "C" int vecchia_loglik_grad_noalloc(const double *locs, const double *z, 
     double *partial = (double *)(base + kPartialOff);
     int64_t *pfail = (int64_t *)(base + kPfailOff);
     hipStream_t s = (hipStream_t)stream;
-    const int variant = resolve_variant(m, true, V_AUTO);
+    const int variant = resolve_variant(m, true, V_AUTO, kc);
     for (int64_t s0 = 0; s0 < n; s0 += kSlicePoints) {
         const int64_t s1 = std::min(n, s0 + kSlicePoints);
         EvalArgs a{};
