@@ -191,9 +191,9 @@ __device__ __forceinline__ double cov_scaled(double d, const Params &P, const do
 
 // ---- the tiled kernel's forms -------------------------------------------------
 //
-// The exponential of exp_neg_tab rearranged for fewer instructions (15 against
-// 19; the tiled kernels evaluate it for every pair and are bound by vector
-// issue).  Entry j of the staged table holds hi = 2^(j/64) with j 2^14
+// The exponential of exp_neg_tab rearranged for fewer instructions (16 against
+// 22 with the table's address; the tiled kernels evaluate it for every pair
+// and are bound by vector issue).  Entry j of the staged table holds hi = 2^(j/64) with j 2^14
 // subtracted from its high word, and lo / hi: adding n 2^14 = k 2^20 + j 2^14
 // to the high word then scales hi by 2^k in one integer instruction, and the
 // low part joins e^f - 1 in the polynomial's last step.  n = rint(64 x / ln2)
@@ -210,37 +210,56 @@ __device__ __forceinline__ void stage_exp_entry(int j, double *tab) {
 // that meet another constant, or are overwritten by a fused multiply-add, in
 // vector registers of their own, and the rest in scalar registers.
 struct CovConst {
-    double eps, magic, c120;                                     // vector
-    double unmagic, inv_ln2_64, head, tail, c720, c24, c6, rmax;  // scalar
+    double eps, magic, c24;                                       // vector
+    double unmagic, inv_ln2_64, head, tail, c120, c6, half, rmax;  // scalar
 };
 template <bool PIN>
 __device__ __forceinline__ CovConst cov_const() {
-    CovConst c{0x1p-1000, 0x1.8p52, 1.0 / 120.0, -0x1.8p52, -0x1.71547652b82fep+6, -0x1.62e42fefa0000p-7,
-               -0x1.cf79abc9e3b3ap-46, 1.0 / 720.0, 1.0 / 24.0, 1.0 / 6.0, 708.0};
+    constexpr double A2 = (0.6931471805599453 / 128.0) * (0.6931471805599453 / 128.0);  // the largest f^2
+    CovConst c{0x1p-1000, 0x1.8p52, 1.0 / 24.0 + 1.5 * A2 / 720.0, -0x1.8p52, -0x1.71547652b82fep+6, -0x1.62e42fefa0000p-7,
+               -0x1.cf79abc9e3b3ap-46, 1.0 / 120.0, 1.0 / 6.0, 0.5 - 0.5625 * A2 * A2 / 720.0, 708.0};
     if constexpr (PIN) {
-        asm volatile("" : "+v"(c.eps), "+v"(c.magic), "+v"(c.c120));
+        asm volatile("" : "+v"(c.eps), "+v"(c.magic), "+v"(c.c24));
         asm volatile("" : "+s"(c.unmagic), "+s"(c.inv_ln2_64), "+s"(c.head), "+s"(c.tail));
-        asm volatile("" : "+s"(c.c720), "+s"(c.c24), "+s"(c.c6), "+s"(c.rmax));
+        asm volatile("" : "+s"(c.c120), "+s"(c.c6), "+s"(c.half), "+s"(c.rmax));
     }
     return c;
 }
 
+// A staged table by its LDS address in a scalar register, opaque to the
+// compiler: it would otherwise add the (zero) base of the dynamic LDS to every
+// entry's address in an instruction of its own.
+typedef const __attribute__((address_space(3))) double *LdsTab;
+typedef double dvec2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ LdsTab lds_table(const double *tab) {
+    uint32_t a = (uint32_t)(uintptr_t)(LdsTab)tab;
+    asm volatile("" : "+s"(a));
+    return (LdsTab)(uintptr_t)a;
+}
+// entry j (two doubles)
+__device__ __forceinline__ dvec2 table_entry(LdsTab tab, uint32_t j) {
+    uint32_t a;
+    asm("v_lshl_add_u32 %0, %1, 4, %2" : "=v"(a) : "v"(j), "s"((uint32_t)(uintptr_t)tab));
+    return *(const __attribute__((address_space(3))) dvec2 *)(uintptr_t)a;
+}
+
 // e^-r for r >= -709, one rounding at the end (just above half an ulp, as
 // exp_neg_tab).  Arguments beyond 708 give e^-708 (3e-308), NaN as well, so
-// callers validate their inputs.
-__device__ __forceinline__ double exp_neg_staged(double r, const double *tab, const CovConst &c) {
+// callers validate their inputs.  e^f - 1 is the Taylor polynomial with its
+// last term, f^6 / 720, replaced by the Chebyshev fit of lower degree, f^6 =
+// 3/2 a^2 f^4 - 9/16 a^4 f^2 to a^6 / 16 on |f| <= a = ln2 / 128 (2e-18 of e^f).
+__device__ __forceinline__ double exp_neg_staged(double r, LdsTab tab, const CovConst &c) {
     r = fmin(r, c.rmax);
     const double t = fma(r, c.inv_ln2_64, c.magic);
     const int n = __double2loint(t);
     const double nf = t + c.unmagic;
     double f = fma(nf, c.head, -r);
     f = fma(nf, c.tail, f);
-    double q = fma(f, c.c720, c.c120);
-    q = fma(q, f, c.c24);
+    double q = fma(f, c.c120, c.c24);
     q = fma(q, f, c.c6);
-    q = fma(q, f, 0.5);
+    q = fma(q, f, c.half);
     q = fma(q, f, 1.0);
-    const double2 e = *reinterpret_cast<const double2 *>(tab + 2 * (n & 63));
+    const dvec2 e = table_entry(tab, n & 63);
     const double hi = __hiloint2double(__double2hiint(e.x) + (n << 14), __double2loint(e.x));
     return fma(hi, fma(q, f, e.y), hi);
 }
@@ -316,11 +335,11 @@ __device__ __forceinline__ void stage_tables(int t, double *tab) {
 // the result plus 2^-54 (it feeds an exponential): x = 2^k m with m in
 // [1/2, 1), r = m c - 1 with c near 1 / m (|r| <= 2^-7), log x = k ln2 - log c
 // + log1p r, the last by its Taylor polynomial of degree 7 (truncation 2e-18).
-__device__ __forceinline__ double log_staged(double x, const double *tab) {
+__device__ __forceinline__ double log_staged(double x, LdsTab tab) {
     const double m = __builtin_amdgcn_frexp_mant(x);
     const double k = (double)__builtin_amdgcn_frexp_exp(x);
     const int j = (__double2hiint(m) >> 14) & 63;
-    const double2 e = *reinterpret_cast<const double2 *>(tab + 2 * kExpTableSize + 2 * j);
+    const dvec2 e = table_entry(tab + 2 * kExpTableSize, j);
     const double r = fma(m, e.x, -1.0);
     double p = fma(r, 1.0 / 7.0, -1.0 / 6.0);
     p = fma(p, r, 1.0 / 5.0);
@@ -402,7 +421,7 @@ __device__ __forceinline__ double sqrt_lean(double x) {
 // by its own series in h (to h^7, truncation 8e-19).
 template <int KC>
 __device__ __forceinline__ double pair_dist_pow(double xa, double ya, double ca, double xb, double yb, double cb,
-                                                const Params &P, const double *tab, const CovConst &cc) {
+                                                const Params &P, LdsTab tab, const CovConst &cc) {
     if constexpr (kc_gcd(KC)) {
         const double dy = ya - yb, dx = xa - xb;
         const double x1 = dy * (0.5 * kDeg2Rad), x2 = dx * (0.5 * kDeg2Rad);

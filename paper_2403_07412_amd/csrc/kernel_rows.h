@@ -70,7 +70,7 @@ template <int T, int KC, bool GRAD>
 __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ locs, const double *__restrict__ z,
                                                     const int32_t *__restrict__ nbr, int64_t i, int64_t n, int32_t m,
                                                     const double *qloc, const Params &P, bool active,
-                                                    const double *ET, double *smem) {
+                                                    LdsTab ET, double *smem) {
     constexpr bool GCD = kc_gcd(KC);
     using Ls = RowsLds<T, GRAD, GCD>;
     constexpr int KP = Ls::KP;
@@ -422,7 +422,9 @@ __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ l
             });
             wave_lds_sync();
             const uint32_t N = (uint32_t)k + 1, NP = N * (uint32_t)k / 2, N16 = 16 * N;
-            const uint32_t sb16 = 16 * (16 % N), sa16 = sb16 + 16 * ((16 / N) % N);
+            const uint32_t sb16 = 16 * (16 % N);
+            uint32_t sa16 = sb16 + 16 * ((16 / N) % N);
+            sa16 = min(sa16, sa16 - N16);
             uint32_t b16 = 16 * ((uint32_t)j % N), a16 = b16 + 16 + 16 * (((uint32_t)j / N) % N);
             a16 = min(a16, a16 - N16);
             const char *XYb = reinterpret_cast<const char *>(XY), *UBb = reinterpret_cast<const char *>(UB);
@@ -441,7 +443,6 @@ __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ l
                 b16 += sb16;
                 a16 += sa16 + (b16 >= N16 ? 16u : 0u);
                 b16 = min(b16, b16 - N16);
-                a16 = min(a16, a16 - N16);
                 a16 = min(a16, a16 - N16);
             };
 #pragma unroll 2

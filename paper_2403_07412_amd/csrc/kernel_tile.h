@@ -578,7 +578,7 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
     // branches on them are uniform over the wavefront.  With the gradient,
     // dC/dbeta is kept in dtile from the same exponential when registers allow.
     constexpr bool KEEP_D = GRAD && keep_dbeta(T, W, GCD);
-    const double *ET = smem + Ls::EXPT;
+    const LdsTab ET = lds_table(smem + Ls::EXPT);
     const CovConst CC = cov_const<W == 1>();
     dvec4 tile[NTW];
     dvec4 dtile[KEEP_D ? NTW : 1];
@@ -620,8 +620,10 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
             double da;
             if constexpr (SHARE_D)
                 da = dslot(4 * s + r)[l];
-            else
-                da = pair_dist_pow<KC>(XY[2 * a], XY[2 * a + 1], GCD ? CLv[a] : 0.0, xb, yb, cb, P, ET, CC);
+            else {
+                const double2 pa = *reinterpret_cast<const double2 *>(XY + 2 * a);
+                da = pair_dist_pow<KC>(pa.x, pa.y, GCD ? CLv[a] : 0.0, xb, yb, cb, P, ET, CC);
+            }
             const double rs = da * P.inv_beta;
             const double e = exp_neg_staged(rs, ET, CC);
             tile[s][r] = cov_value<KC>(rs, e, P);
@@ -839,12 +841,12 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
             // the next item: b += NTG mod N, o += NTG / N, one more when b passes N
             uint32_t a16 = b16 + o16;
             a16 = min(a16, a16 - N16);
-            const uint32_t sa16 = sb16 + so16;
+            uint32_t sa16 = sb16 + so16;
+            sa16 = min(sa16, sa16 - N16);
             auto next_item = [&]() {
                 b16 += sb16;
                 a16 += sa16 + (b16 >= N16 ? 16u : 0u);
                 b16 = min(b16, b16 - N16);
-                a16 = min(a16, a16 - N16);
                 a16 = min(a16, a16 - N16);
             };
             auto pair_dist = [&](uint32_t pa, uint32_t pb) {

@@ -308,7 +308,7 @@ __global__ void __launch_bounds__(kRowsWaves *kWave)
     const bool pred = a.qlocs != nullptr;
     const bool run = mine && valid && i >= 0 && i < (pred ? a.nq : n);
     CondOut o = rows_conditional<T, KC, GRAD>(locs, z, nbr, run ? i : 0, n, m, pred ? a.qlocs + 2 * (run ? i : 0) : nullptr,
-                                              P, run, ET,
+                                              P, run, lds_table(ET),
                                               smem + staged_doubles(kc_family(KC) == 3) + wave * RowsLds<T, GRAD, kc_gcd(KC)>::TOTAL);
     const bool bad = o.bad || !run;
     if (bad) o.ell = o.g0 = o.g1 = o.g2 = o.mean = o.var = __builtin_nan("");
