@@ -4,16 +4,22 @@
 // copy, no synchronisation), with all temporary storage in the caller's
 // workspace, so the preprocessing that uses them can be captured in a graph.
 //
-// Radix sort, per 8-bit digit from the least significant:
+// Radix sort, per digit from the least significant (the key bits in the fewest
+// digits of at most nine bits, evenly: 17 bits of cells take two passes where
+// digits of eight bits took three):
 //   histogram  one wavefront per tile of 1024 keys counts its digits in LDS
 //              and writes them digit-major: counts[d][tile];
 //   scan       an exclusive prefix sum over that array gives every (digit,
 //              tile) its first output position;
 //   scatter    the tile's keys are ranked 64 at a time in input order: the
-//              lanes holding the same digit are found with eight ballots, the
+//              lanes holding the same digit are found with nine ballots, the
 //              rank is the number of such lanes below, and a running count
 //              per digit in LDS carries the order across the 16 rounds.
 // Equal digits keep their input order in every pass, so the sort is stable.
+// At the sizes of a field (10^5 to 10^6 keys) a pass is bound by waits, not
+// bytes: a tile's keys, values and first positions are all requested before
+// the first is used (250,000 pairs: scatter 5 us a pass, 14 with one wait a
+// round).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -26,7 +32,8 @@ namespace vecchia {
 constexpr int kSortWave = 64;
 constexpr int kSortRounds = 16;
 constexpr int kSortTile = kSortWave * kSortRounds;  // keys per tile
-constexpr int kSortDigits = 256;
+constexpr int kSortBits = 9;  // most bits of a digit
+constexpr int kSortDigits = 1 << kSortBits;
 constexpr int kScanThreads = 256;
 constexpr int kScanPerThread = 16;
 constexpr int kScanChunk = kScanThreads * kScanPerThread;  // elements per scan block
@@ -45,15 +52,20 @@ __global__ void __launch_bounds__(kSortWave) sort_histogram_kernel(const K *__re
     __shared__ int32_t hist[kSortDigits];
     const int lane = threadIdx.x;
     const int64_t tile = blockIdx.x;
-    for (int d = lane; d < kSortDigits; d += kSortWave) hist[d] = 0;
-    __syncthreads();
     const int64_t base = tile * kSortTile;
+    K key[kSortRounds];
+#pragma unroll
     for (int r = 0; r < kSortRounds; ++r) {
         const int64_t idx = base + r * kSortWave + lane;
-        if (idx < n) atomicAdd(&hist[sort_digit(keys[idx], shift, dmask)], 1);
+        key[r] = idx < n ? keys[idx] : 0;
     }
+    for (int d = lane; d <= dmask; d += kSortWave) hist[d] = 0;
     __syncthreads();
-    for (int d = lane; d < kSortDigits; d += kSortWave) counts[(int64_t)d * ntiles + tile] = hist[d];
+#pragma unroll
+    for (int r = 0; r < kSortRounds; ++r)
+        if (base + r * kSortWave + lane < n) atomicAdd(&hist[sort_digit(key[r], shift, dmask)], 1);
+    __syncthreads();
+    for (int d = lane; d <= dmask; d += kSortWave) counts[(int64_t)d * ntiles + tile] = hist[d];
 }
 
 template <class K>
@@ -66,25 +78,30 @@ __global__ void __launch_bounds__(kSortWave) sort_scatter_kernel(const K *__rest
     __shared__ int32_t running[kSortDigits];
     const int lane = threadIdx.x;
     const int64_t tile = blockIdx.x;
-    for (int d = lane; d < kSortDigits; d += kSortWave) running[d] = 0;
-    __syncthreads();
-    const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));  // lanes under this one
     const int64_t base = tile * kSortTile;
+    K key[kSortRounds];
+    int32_t val[kSortRounds];
+#pragma unroll
     for (int r = 0; r < kSortRounds; ++r) {
         const int64_t idx = base + r * kSortWave + lane;
-        const bool valid = idx < n;
-        K key = 0;
-        int32_t val = 0;
-        int d = 0;
-        if (valid) {
-            key = kin[idx];
-            val = vin[idx];
-            d = sort_digit(key, shift, dmask);
-        }
+        key[r] = idx < n ? kin[idx] : 0;
+        val[r] = idx < n ? vin[idx] : 0;
+    }
+#pragma unroll
+    for (int q = 0; q < kSortDigits / kSortWave; ++q) {
+        const int d = q * kSortWave + lane;
+        if (d <= dmask) running[d] = offsets[(int64_t)d * ntiles + tile];
+    }
+    __syncthreads();
+    const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));  // lanes under this one
+#pragma unroll
+    for (int r = 0; r < kSortRounds; ++r) {
+        const bool valid = base + r * kSortWave + lane < n;
+        const int d = valid ? sort_digit(key[r], shift, dmask) : 0;
         // lanes holding this lane's digit
         uint64_t same = __ballot(valid);
 #pragma unroll
-        for (int b = 0; b < 8; ++b) {
+        for (int b = 0; b < kSortBits; ++b) {
             const bool bit = (d >> b) & 1;
             const uint64_t ones = __ballot(bit);
             same &= bit ? ones : ~ones;
@@ -99,9 +116,8 @@ __global__ void __launch_bounds__(kSortWave) sort_scatter_kernel(const K *__rest
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         if (valid) {
-            const int64_t pos = (int64_t)offsets[(int64_t)d * ntiles + tile] + before + rank;
-            kout[pos] = key;
-            vout[pos] = val;
+            kout[before + rank] = key[r];
+            vout[before + rank] = val[r];
         }
     }
 }
@@ -113,9 +129,10 @@ __global__ void __launch_bounds__(kScanThreads) scan_chunk_sums_kernel(const int
     const int t = threadIdx.x;
     const int64_t base = (int64_t)blockIdx.x * kScanChunk;
     int32_t s = 0;
+#pragma unroll
     for (int q = 0; q < kScanPerThread; ++q) {
         const int64_t idx = base + (int64_t)q * kScanThreads + t;
-        if (idx < n) s += in[idx];
+        s += idx < n ? in[idx] : 0;
     }
     red[t] = s;
     __syncthreads();
@@ -144,21 +161,9 @@ __device__ __forceinline__ int32_t block_exclusive_scan(int32_t v, int32_t *sh, 
     return excl;
 }
 
-// Level 2: exclusive scan of the chunk sums in place (one block, any count).
-__global__ void __launch_bounds__(kScanThreads) scan_sums_kernel(int32_t *__restrict__ sums, int64_t count) {
-    __shared__ int32_t sh[kScanThreads];
-    int32_t carry = 0;
-    for (int64_t b0 = 0; b0 < count; b0 += kScanThreads) {
-        const int64_t idx = b0 + threadIdx.x;
-        const int32_t v = idx < count ? sums[idx] : 0;
-        int32_t total;
-        const int32_t excl = block_exclusive_scan(v, sh, total);
-        if (idx < count) sums[idx] = carry + excl;
-        carry += total;
-    }
-}
-
-// Level 3: every chunk scanned in order from its offset.  Thread t owns the
+// Level 2: every chunk scanned in order from its offset, the sum of the chunks
+// before it (which every block adds up for itself: fewer than a hundred at the
+// sizes of a field, where a kernel for it cost its launch).  Thread t owns the
 // kScanPerThread consecutive elements starting at t * kScanPerThread.
 __global__ void __launch_bounds__(kScanThreads) scan_chunks_kernel(const int32_t *__restrict__ in, int64_t n,
                                                                    const int32_t *__restrict__ sums,
@@ -174,8 +179,10 @@ __global__ void __launch_bounds__(kScanThreads) scan_chunks_kernel(const int32_t
         local[q] = idx < n ? in[idx] : 0;
         s += local[q];
     }
-    int32_t total;
-    int32_t run = sums[blockIdx.x] + block_exclusive_scan(s, sh, total);
+    int32_t total, before, head = 0;
+    for (int64_t c = t; c < blockIdx.x; c += kScanThreads) head += sums[c];
+    block_exclusive_scan(head, sh, before);
+    int32_t run = before + block_exclusive_scan(s, sh, total);
 #pragma unroll
     for (int q = 0; q < kScanPerThread; ++q) {
         const int64_t idx = base + q;
@@ -200,7 +207,6 @@ inline hipError_t exclusive_scan_i32(void *temp, size_t temp_bytes, const int32_
     const int64_t chunks = (n + kScanChunk - 1) / kScanChunk;
     int32_t *sums = (int32_t *)temp;
     hipLaunchKernelGGL(scan_chunk_sums_kernel, dim3((unsigned)chunks), dim3(kScanThreads), 0, s, in, n, sums);
-    hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(kScanThreads), 0, s, sums, chunks);
     hipLaunchKernelGGL(scan_chunks_kernel, dim3((unsigned)chunks), dim3(kScanThreads), 0, s, in, n,
                        (const int32_t *)sums, out);
     return hipGetLastError();
@@ -225,18 +231,19 @@ hipError_t radix_sort_pairs(void *temp, size_t temp_bytes, const K *kin, K *kout
     if (temp_bytes < radix_sort_temp_bytes<K>(n) || end_bit <= begin_bit || end_bit > (int)(8 * sizeof(K)))
         return hipErrorInvalidValue;
     const int64_t ntiles = sort_tiles(n);
-    const int64_t cnt = (int64_t)kSortDigits * ntiles;
+    const int64_t max_cnt = (int64_t)kSortDigits * ntiles;
     char *p = (char *)temp;
     K *kalt = (K *)p;
     p += sort_align256(sizeof(K) * (size_t)n);
     int32_t *valt = (int32_t *)p;
     p += sort_align256(sizeof(int32_t) * (size_t)n);
     int32_t *counts = (int32_t *)p;
-    p += sort_align256(sizeof(int32_t) * (size_t)cnt);
+    p += sort_align256(sizeof(int32_t) * (size_t)max_cnt);
     int32_t *offsets = (int32_t *)p;
-    p += sort_align256(sizeof(int32_t) * (size_t)cnt);
+    p += sort_align256(sizeof(int32_t) * (size_t)max_cnt);
     void *scan_temp = p;
-    const int passes = (end_bit - begin_bit + 7) / 8;
+    const int passes = (end_bit - begin_bit + kSortBits - 1) / kSortBits;
+    const int bits = (end_bit - begin_bit + passes - 1) / passes;
     const K *ki = kin;
     const int32_t *vi = vin;
     for (int pass = 0; pass < passes; ++pass) {
@@ -244,8 +251,9 @@ hipError_t radix_sort_pairs(void *temp, size_t temp_bytes, const K *kin, K *kout
         const bool to_out = ((passes - 1 - pass) % 2) == 0;
         K *ko = to_out ? kout : kalt;
         int32_t *vo = to_out ? vout : valt;
-        const int shift = begin_bit + 8 * pass;
-        const int dmask = (1 << std::min(8, end_bit - shift)) - 1;  // bits past end_bit take no part
+        const int shift = begin_bit + bits * pass;
+        const int dmask = (1 << std::min(bits, end_bit - shift)) - 1;  // bits past end_bit take no part
+        const int64_t cnt = (int64_t)(dmask + 1) * ntiles;
         hipLaunchKernelGGL(sort_histogram_kernel<K>, dim3((unsigned)ntiles), dim3(kSortWave), 0, s, ki, n, shift,
                            dmask, counts, ntiles);
         const hipError_t e = exclusive_scan_i32(scan_temp, scan_temp_bytes(cnt), counts, offsets, cnt, s);
