@@ -34,10 +34,14 @@ __host__ __device__ constexpr bool rows_keep_dbeta(int T) { return T <= 2; }
 // Whether finished rows of tiles leave the registers: four tile rows with the
 // gradient are ten tiles of 32 registers.  Once diagonal tile C is factored the
 // tiles (C, 0..C) are needed only by the back substitution; they are
-// transposed there and then and kept in the wavefront's scratch memory (six
-// tiles, 12 KB per conditional each way), so that the factorisation holds six
-// tiles at most, as it does without the gradient.
+// transposed there and then and kept in the wavefront's scratch memory, as far
+// as the factorisation would otherwise hold more than six tiles, its most
+// without the gradient: tiles (2, 1) and (2, 2) stay, beside the four of the
+// last row.  The four tiles in scratch memory are 8 KB per conditional each
+// way, mostly past the L2 (400,000 points, m = 62: 4.15 ms with all six there,
+// 3.44 with none moved).
 __host__ __device__ constexpr bool rows_stash(int T, bool grad) { return grad && T == 4; }
+__host__ __device__ constexpr bool rows_stash_tile(int T, int R, int C) { return R < T - 2 || (R == T - 2 && C == 0); }
 
 // LDS of one wavefront, in doubles: everything is per row group.
 template <int T, bool GRAD, bool GCD>
@@ -194,7 +198,7 @@ __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ l
         }
     };
     typedef __attribute__((address_space(5))) double *ScratchPtr;
-    double stash_mem[STASH ? 16 * (NT - T) : 1];
+    double stash_mem[STASH ? 16 * ((T - 2) * (T - 1) / 2 + 1) : 1];
     ScratchPtr stash = (ScratchPtr)stash_mem;
     if constexpr (STASH) asm volatile("" : "+v"(stash));  // kept in memory: the compiler cannot see through it
     double Lk = 1.0, yk = 0.0;
@@ -330,11 +334,13 @@ __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ l
             if (16 * C + 15 >= kmin) keep_observation_row(std::integral_constant<int, C>{});
             static_for<0, C + 1>([&](auto Ec) {
                 constexpr int E = decltype(Ec)::value;
-                double Lt[16];
-                if constexpr (E == C) transpose_diag(A[tix(C, C)], C, Lt);
-                else transpose(A[tix(C, E)], Lt);
+                if constexpr (rows_stash_tile(T, C, E)) {
+                    double Lt[16];
+                    if constexpr (E == C) transpose_diag(A[tix(C, C)], C, Lt);
+                    else transpose(A[tix(C, E)], Lt);
 #pragma unroll
-                for (int r = 0; r < 16; ++r) stash[16 * tix(C, E) + r] = Lt[r];
+                    for (int r = 0; r < 16; ++r) stash[16 * tix(C, E) + r] = Lt[r];
+                }
             });
         }
     });
@@ -363,7 +369,7 @@ __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ l
             static_for<C + 1, T>([&](auto Rc) {
                 constexpr int R = decltype(Rc)::value;
                 if (16 * R <= kmax) {
-                    if constexpr (STASH && R + 1 < T) {
+                    if constexpr (STASH && rows_stash_tile(T, R, C)) {
 #pragma unroll
                         for (int r = 0; r < 16; ++r) Lt[r] = stash[16 * tix(R, C) + r];
                     } else {
@@ -376,7 +382,7 @@ __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ l
                     });
                 }
             });
-            if constexpr (STASH && C + 1 < T) {
+            if constexpr (STASH && rows_stash_tile(T, C, C)) {
 #pragma unroll
                 for (int r = 0; r < 16; ++r) Lt[r] = stash[16 * tix(C, C) + r];
             } else {
