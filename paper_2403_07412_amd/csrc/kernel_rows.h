@@ -67,10 +67,24 @@ __device__ __forceinline__ double shift_up(double v) {
     return __hiloint2double(hi, lo);
 }
 
+// v of lane j of row group G, in lane j of every row group.
+template <int G>
+__device__ __forceinline__ double from_group(double v, int j4) {
+    const int lo = __builtin_amdgcn_ds_bpermute(j4 + 64 * G, (int)__double2loint(v));
+    const int hi = __builtin_amdgcn_ds_bpermute(j4 + 64 * G, (int)__double2hiint(v));
+    return __hiloint2double(hi, lo);
+}
+
 // One conditional per row group (modes as lds_conditional); `active` is false
 // in groups without an item, which compute on an empty set.  Results are
 // valid in every lane of the group.
-template <int T, int KC, bool GRAD>
+//
+// SHARE: the row groups hold one point under four parameter vectors.  Each
+// evaluates the distances of every fourth column, or round of the
+// contraction, and the others take them through the LDS crossbar, which is
+// idle: a Matern evaluation is 14 instructions of distance and 14 to 17 of
+// covariance.
+template <int T, int KC, bool GRAD, bool SHARE>
 __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ locs, const double *__restrict__ z,
                                                     const int32_t *__restrict__ nbr, int64_t i, int64_t n, int32_t m,
                                                     const double *qloc, const Params &P, bool active,
@@ -154,6 +168,7 @@ __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ l
     // (j + 16 - c, 16 - c)) and a lane shift moves the second into place; with
     // zeros shifted in, dC/dbeta of the tile is its strictly lower half.
     const CovConst CC = cov_const<true>();
+    const int j4 = 4 * j;
     double A[NT][16], D[KEEP ? NT : 1][16];
     auto tix = [](int R, int C) constexpr { return R * (R + 1) / 2 + C; };
     const double diag = P.sigma2 + P.tau2;
@@ -207,26 +222,37 @@ __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ l
         const double2 *XYt = reinterpret_cast<const double2 *>(XY) + 16 * C;
         if (16 * C <= kmax) {
             // the diagonal tile, columns c and 16 - c together
+            auto diag_dist = [&](auto c) __attribute__((always_inline)) {  // of columns c and 16 - c, 0 <= c < 8
+                const bool low = j >= c;  // this lane evaluates column c
+                const int ra = low ? j : j + 16 - c, cl = low ? c : 16 - c;
+                const double2 pa = XYt[ra], pb = XYt[cl];
+                double ca = 0.0, cb = 0.0;
+                if constexpr (GCD) {
+                    ca = CLv[16 * C + ra];
+                    cb = CLv[16 * C + cl];
+                }
+                return pair_dist_pow<KC>(pa.x, pa.y, ca, pb.x, pb.y, cb, P, ET, CC);
+            };
+            auto column_dist = [&](auto Rc, auto c) __attribute__((always_inline)) {  // of tile (R, C), column c
+                constexpr int R = decltype(Rc)::value;
+                const double2 pb = XYt[c];
+                return pair_dist_pow<KC>(px[R], py[R], GCD ? pc[R] : 0.0, pb.x, pb.y, GCD ? CLv[16 * C + c] : 0.0, P,
+                                         ET, CC);
+            };
+            double shared = 0.0;
             static_for<0, 9>([&](auto cc) {
                 constexpr int c = decltype(cc)::value;
                 constexpr bool two = c > 0 && c < 8;
                 if (16 * C + c <= kmax) {
-                    const bool low = j >= c;  // this lane evaluates column c
-                    double2 pa = double2{px[C], py[C]}, pb;
-                    double ca = GCD ? pc[C] : 0.0, cb = 0.0;
-                    if constexpr (two) {
-                        const int ra = low ? j : j + 16 - c, cl = low ? c : 16 - c;
-                        pa = XYt[ra];
-                        pb = XYt[cl];
-                        if constexpr (GCD) {
-                            ca = CLv[16 * C + ra];
-                            cb = CLv[16 * C + cl];
-                        }
+                    double da;
+                    if constexpr (SHARE && c < 8) {
+                        if constexpr (c % 4 == 0) shared = diag_dist(c + g);
+                        da = from_group<c % 4>(shared, j4);
+                    } else if constexpr (two) {
+                        da = diag_dist(cc);
                     } else {
-                        pb = XYt[c];
-                        if constexpr (GCD) cb = CLv[16 * C + c];
+                        da = column_dist(Cc, cc);
                     }
-                    const double da = pair_dist_pow<KC>(pa.x, pa.y, ca, pb.x, pb.y, cb, P, ET, CC);
                     const double rs = da * P.inv_beta;
                     const double e = exp_neg_staged(rs, ET, CC);
                     const double v = cov_value<KC>(rs, e, P);
@@ -254,9 +280,13 @@ __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ l
                 constexpr int R = decltype(Rc)::value;
                 static_for<0, 16>([&](auto cc) {
                     constexpr int c = decltype(cc)::value;
-                    const double2 pb = XYt[c];
-                    const double da = pair_dist_pow<KC>(px[R], py[R], GCD ? pc[R] : 0.0, pb.x, pb.y,
-                                                        GCD ? CLv[16 * C + c] : 0.0, P, ET, CC);
+                    double da;
+                    if constexpr (SHARE) {
+                        if constexpr (c % 4 == 0) shared = column_dist(Rc, c + g);
+                        da = from_group<c % 4>(shared, j4);
+                    } else {
+                        da = column_dist(Rc, cc);
+                    }
                     const double rs = da * P.inv_beta;
                     const double e = exp_neg_staged(rs, ET, CC);
                     A[tix(R, C)][c] = cov_value<KC>(rs, e, P);
@@ -427,34 +457,71 @@ __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ l
                 UB[2 * (16 * R + j) + 1] = xb[R];
             });
             wave_lds_sync();
-            const uint32_t N = (uint32_t)k + 1, NP = N * (uint32_t)k / 2, N16 = 16 * N;
-            const uint32_t sb16 = 16 * (16 % N);
-            uint32_t sa16 = sb16 + 16 * ((16 / N) % N);
-            sa16 = min(sa16, sa16 - N16);
-            uint32_t b16 = 16 * ((uint32_t)j % N), a16 = b16 + 16 + 16 * (((uint32_t)j / N) % N);
-            a16 = min(a16, a16 - N16);
+            const uint32_t N = (uint32_t)k + 1, NP = N * (uint32_t)k / 2;
             const char *XYb = reinterpret_cast<const char *>(XY), *UBb = reinterpret_cast<const char *>(UB);
-            const uint32_t whole = ((uint32_t)kmin + 1) * (uint32_t)kmin / 32;          // rounds every lane takes part in
-            const uint32_t rounds = (((uint32_t)kmax + 1) * (uint32_t)kmax / 2 + 15) / 16;
-            auto round = [&]() {
-                const double2 xa = *reinterpret_cast<const double2 *>(XYb + a16);
-                const double2 xc = *reinterpret_cast<const double2 *>(XYb + b16);
-                const double da = pair_dist_pow<KC>(xa.x, xa.y, GCD ? CLv[a16 / 16] : 0.0, xc.x, xc.y,
-                                                    GCD ? CLv[b16 / 16] : 0.0, P, ET, CC);
+            // the pairs `first`, `first` + `step`, ..: byte offsets of the two points
+            struct Walk {
+                uint32_t N16, sb, sa, b, a;
+                __device__ __forceinline__ Walk(uint32_t N, uint32_t first, uint32_t step) : N16(16 * N) {
+                    sb = 16 * (step % N);
+                    sa = sb + 16 * ((step / N) % N);
+                    sa = min(sa, sa - N16);
+                    b = 16 * (first % N);
+                    a = b + 16 + 16 * ((first / N) % N);
+                    a = min(a, a - N16);
+                }
+                __device__ __forceinline__ void next() {
+                    b += sb;
+                    a += sa + (b >= N16 ? 16u : 0u);
+                    b = min(b, b - N16);
+                    a = min(a, a - N16);
+                }
+            };
+            Walk w(N, j, 16);
+            auto pair_dist = [&](const Walk &p) __attribute__((always_inline)) {
+                const double2 xa = *reinterpret_cast<const double2 *>(XYb + p.a);
+                const double2 xc = *reinterpret_cast<const double2 *>(XYb + p.b);
+                return pair_dist_pow<KC>(xa.x, xa.y, GCD ? CLv[p.a / 16] : 0.0, xc.x, xc.y, GCD ? CLv[p.b / 16] : 0.0,
+                                         P, ET, CC);
+            };
+            auto add_pair = [&](double da) __attribute__((always_inline)) {
                 const double rs = da * P.inv_beta;
                 const double d = dbeta_raw<KC>(rs, exp_neg_staged(rs, ET, CC));
-                const double2 ua = *reinterpret_cast<const double2 *>(UBb + a16);
-                const double2 vb = *reinterpret_cast<const double2 *>(UBb + b16);
+                const double2 ua = *reinterpret_cast<const double2 *>(UBb + w.a);
+                const double2 vb = *reinterpret_cast<const double2 *>(UBb + w.b);
                 gb = fma(d, fma(ua.x, vb.y, vb.x * ua.y), gb);
-                b16 += sb16;
-                a16 += sa16 + (b16 >= N16 ? 16u : 0u);
-                b16 = min(b16, b16 - N16);
-                a16 = min(a16, a16 - N16);
             };
+            if constexpr (SHARE) {
+                Walk own(N, 16 * g + j, 64);  // the pairs whose distance this lane evaluates
+                uint32_t p = 0;
+                for (; p + 64 <= NP; p += 64) {
+                    const double mine = pair_dist(own);
+                    own.next();
+                    static_for<0, 4>([&](auto sc) {
+                        add_pair(from_group<decltype(sc)::value>(mine, j4));
+                        w.next();
+                    });
+                }
+                const double mine = pair_dist(own);  // any pair of the set past the last item
+                static_for<0, 4>([&](auto sc) {
+                    constexpr int q = decltype(sc)::value;
+                    const double da = from_group<q>(mine, j4);
+                    if (p + 16 * q + j < NP) add_pair(da);
+                    w.next();
+                });
+            } else {
+                const uint32_t whole = ((uint32_t)kmin + 1) * (uint32_t)kmin / 32;  // rounds every lane takes part in
+                const uint32_t rounds = (((uint32_t)kmax + 1) * (uint32_t)kmax / 2 + 15) / 16;
 #pragma unroll 2
-            for (uint32_t c = 0; c < whole; ++c) round();
-            for (uint32_t c = whole; c < rounds; ++c)
-                if (16 * c + j < NP) round();
+                for (uint32_t c = 0; c < whole; ++c) {
+                    add_pair(pair_dist(w));
+                    w.next();
+                }
+                for (uint32_t c = whole; c < rounds; ++c) {
+                    if (16 * c + j < NP) add_pair(pair_dist(w));
+                    w.next();
+                }
+            }
         }
         ub = row_sum16(ub);
         gb = row_sum16(gb);

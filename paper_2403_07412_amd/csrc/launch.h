@@ -246,7 +246,9 @@ __global__ void __launch_bounds__(Impl::NT) __attribute__((amdgpu_waves_per_eu(I
 
 // Rows kernel: wavefronts of four conditionals, kRowsWaves to a workgroup
 // (they share the staged exponential table).  Item t of KernelArgs is row
-// group (t - t0) % 4 of wavefront (t - t0) / 4, for t < t_end.
+// group (t - t0) % 4 of wavefront (t - t0) / 4, for t < t_end.  SHARE (plans of
+// parameter vectors in groups of four): the four items of a wavefront are one
+// point's, which then works with placeholder parameters under an invalid vector.
 constexpr int kRowsWaves = 4;
 constexpr int kRowsItems = 4 * kRowsWaves;  // items per workgroup
 
@@ -259,7 +261,7 @@ struct RowsImpl {
     static constexpr size_t SMEM = (kRowsWaves * RowsLds<T, GRAD, kc_gcd(KC)>::TOTAL + staged_doubles(kc_family(KC) == 3)) * sizeof(double);
 };
 
-template <int T, int KC, bool GRAD>
+template <int T, int KC, bool GRAD, bool SHARE>
 __global__ void __launch_bounds__(kRowsWaves *kWave)
     __attribute__((amdgpu_waves_per_eu(RowsImpl<T, KC, GRAD>::WPE)))
     rows_kernel(const KernelArgs a, int64_t t_end) {
@@ -306,11 +308,11 @@ __global__ void __launch_bounds__(kRowsWaves *kWave)
         P.tau2 = 1.0;
     }
     const bool pred = a.qlocs != nullptr;
-    const bool run = mine && valid && i >= 0 && i < (pred ? a.nq : n);
-    CondOut o = rows_conditional<T, KC, GRAD>(locs, z, nbr, run ? i : 0, n, m, pred ? a.qlocs + 2 * (run ? i : 0) : nullptr,
+    const bool run = mine && (SHARE || valid) && i >= 0 && i < (pred ? a.nq : n);
+    CondOut o = rows_conditional<T, KC, GRAD, SHARE>(locs, z, nbr, run ? i : 0, n, m, pred ? a.qlocs + 2 * (run ? i : 0) : nullptr,
                                               P, run, lds_table(ET),
                                               smem + staged_doubles(kc_family(KC) == 3) + wave * RowsLds<T, GRAD, kc_gcd(KC)>::TOTAL);
-    const bool bad = o.bad || !run;
+    const bool bad = o.bad || !run || !valid;
     if (bad) o.ell = o.g0 = o.g1 = o.g2 = o.mean = o.var = __builtin_nan("");
     if (mine && threadIdx.x % 16 == 0) {
         if (pred) {
@@ -375,11 +377,13 @@ int launch_group_impl(const EvalArgs &a, hipStream_t s) {
     return hipGetLastError() == hipSuccess ? VECCHIA_OK : VECCHIA_EHIP;
 }
 
+// group > 1: the parameter vectors of a point come in groups of four
+// consecutive items.
 template <int T, int KC, bool GRAD>
 int launch_rows(const EvalArgs &a, hipStream_t s) {
     if (a.t_end <= a.t_begin) return VECCHIA_OK;
     constexpr size_t smem = RowsImpl<T, KC, GRAD>::SMEM;
-    auto kern = rows_kernel<T, KC, GRAD>;
+    auto kern = a.group > 1 ? rows_kernel<T, KC, GRAD, true> : rows_kernel<T, KC, GRAD, false>;
     if (allow_smem(kern, smem) != hipSuccess) return VECCHIA_EHIP;
     constexpr int64_t kMaxGrid = (int64_t)1 << 22;
     for (int64_t t0 = a.t_begin; t0 < a.t_end; t0 += kMaxGrid * kRowsItems) {
@@ -481,8 +485,8 @@ int launch_tile(const EvalArgs &a, hipStream_t s) {
     } else {
         constexpr int G = lockstep_group(T, W);
         if constexpr (rows_shape(T, W, KC)) {
-            // lockstep groups too: consecutive items are consecutive parameter
-            // vectors of a point, and every row group has its own parameters
+            // lockstep groups too: the row groups of a wavefront are four
+            // parameter vectors of a point and share its distances
             if (a.group > 1 && (a.group != G || !a.k.fields || a.k.qlocs || a.k.ntheta % G != 0))
                 return VECCHIA_EUNSUPPORTED;
             return launch_rows<T, KC, GRAD>(a, s);
