@@ -533,9 +533,9 @@ size_t vecchia_mle_workspace_size(int64_t n, int32_t m);
  * information) the next trial_steps halvings of the step at once, taking
  * the longest that satisfies the Armijo condition, the step one-at-a-time
  * backtracking would take.  Round trips of four or eight vectors take the
- * plan's lockstep form, so at 63..78 neighbours their values and those of
- * single-vector round trips come from different kernel variants and may
- * differ in the last bits.  Synchronises the stream once per round trip.  Returns VECCHIA_OK,
+ * plan's lockstep form, so at 63..78 neighbours of a great-circle model their
+ * values and those of single-vector round trips come from different kernel
+ * variants and may differ in the last bits.  Synchronises the stream once per round trip.  Returns VECCHIA_OK,
  * VECCHIA_EINVAL (bad arguments or options, or theta0 does not evaluate),
  * VECCHIA_EUNSUPPORTED, VECCHIA_EWORKSPACE or VECCHIA_EHIP.
  */

@@ -121,6 +121,7 @@ struct vecchia_plan {
     int64_t total_rows = 0, total_pblocks = 0;
     std::vector<uint64_t> table;  // host image of the device table (fields, class lists), 8-byte words
     bool any_empty = false;  // some field has no points
+    bool any_split = false;  // some field is summed by several blocks, which count themselves
     size_t ws_counter = 0;   // finished reduce blocks per evaluation
     size_t ws_vals = 0, ws_flags = 0, ws_partial = 0, ws_pfail = 0, ws_bytes = 0;
 };
@@ -152,7 +153,7 @@ int run_batched(const vecchia_plan *p, const double *thetas, double *out, double
         PutChunk c;
         c.word0 = w0;
         c.nwords = (uint32_t)std::min<size_t>(kPutWords, p->table.size() - w0);
-        c.nzero = w0 == 0 ? (uint32_t)((int64_t)p->nf * p->ntheta) : 0;
+        c.nzero = w0 == 0 && p->any_split ? (uint32_t)((int64_t)p->nf * p->ntheta) : 0;
         std::copy(p->table.begin() + w0, p->table.begin() + w0 + c.nwords, c.w);
         const uint32_t nb = std::min<uint32_t>(c.nzero / (8 * kPutWords) + 1, 1024);
         hipLaunchKernelGGL(put_words_kernel, dim3(nb), dim3(kPutWords), 0, s, table, counter, c);
@@ -254,6 +255,7 @@ int plan_build(const vecchia_field *fields, int32_t nf, int32_t ntheta, const ve
         d.nb = num_reduce_blocks(d.n);
         pblocks += (int64_t)ntheta * d.nb;
         p->any_empty |= d.nb == 0;
+        p->any_split |= d.nb > 1;
         rows += (int64_t)ntheta * d.n;
         p->fields.push_back(d);
     }
@@ -319,7 +321,7 @@ int plan_build(const vecchia_field *fields, int32_t nf, int32_t ntheta, const ve
     p->ws_pfail = w;
     w = align256(w + (size_t)pblocks * sizeof(int64_t));
     p->ws_counter = w;
-    w = align256(w + (size_t)nf * (size_t)ntheta * sizeof(int32_t));
+    if (p->any_split) w = align256(w + (size_t)nf * (size_t)ntheta * sizeof(int32_t));
     p->ws_bytes = w + 256;
     *plan = p;
     return VECCHIA_OK;

@@ -124,6 +124,9 @@ __host__ __device__ constexpr int lockstep_group(int T, int W) { return (T <= 5 
 //   T = 4, W = 2 (m from 47 to 62; LDS leaves room only without the
 //     gradient): 2.82 ms at nine workgroups against 2.89 ms at eight for the
 //     same points at m = 60, value only.
+// (Times and spills of the first two from before the covariances and the
+// contraction became leaner: T = 8 now fits at 125 VGPRs and T = 10 at 166,
+// without scratch.)
 // T = 7 and 9 with W = 4, T = 2 to 4 with W = 1 and T = 3, 5, 6 with W = 2
 // measured no faster one workgroup up.  Other shapes keep the estimate.
 __host__ __device__ constexpr bool tile_measured_raise(int T, int W, bool gcd) {
@@ -162,14 +165,16 @@ __host__ __device__ constexpr int tile_waves_per_simd(int T, int W, bool keep_d,
 // still fit (measured, power exponential, 100,000 points, m = 60: 2.17 ms
 // keeping at two wavefronts per SIMD, 2.56 recomputing at three; with four
 // wavefronts per conditional, m = 120, 50,000 points, keeping lost: 5.74
-// against 4.64 ms).  One-wavefront shapes of two and three tile rows always
-// keep them (Matern, m = 40, 100,000 points: 0.63 against 0.73 ms).
-// Lockstep workgroups follow the one-vector decision: the two ways round the derivative contract their arithmetic
-// differently, and the lockstep results must be the one-vector bits.
+// against 4.64 ms).  The one-wavefront shape of three tile rows always keeps
+// them (measured with Matern, whose shapes up to four rows the rows kernel has
+// since taken over, m = 40, 100,000 points: 0.63 against 0.73 ms).
+// Lockstep workgroups follow the one-vector decision: the two ways round the
+// derivative contract their arithmetic differently, and the lockstep results
+// must be the one-vector bits.
 __host__ __device__ constexpr bool keep_dbeta(int T, int W, bool gcd = false) {
     return VECCHIA_KEEP_DBETA &&
            (tile_waves_per_simd(T, W, true, true, gcd) >= tile_waves_per_simd(T, W, false, true, gcd) ||
-            (gcd && W == 1 && tile_waves_per_simd(T, W, true, true, gcd) >= 2) || ((T == 2 || T == 3) && W == 1));
+            (gcd && W == 1 && tile_waves_per_simd(T, W, true, true, gcd) >= 2) || (T == 3 && W == 1));
 }
 
 // Tile enumeration: column C descending, row R ascending inside a column, so

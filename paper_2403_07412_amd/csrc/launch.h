@@ -423,7 +423,7 @@ inline int variant_waves(int variant) {
 // gradient: 1.52 ms rows, 1.39 tiles; m = 30: 0.57, 0.63).  Tiles
 // against rows, Matern 3/2, 100,000 points, ms:
 //   value            m = 10: 0.148, 0.057   30: 0.314, 0.144   40: 0.538, 0.280   60: 0.881, 0.530
-//   value, gradient  m = 10: 0.180, 0.078   30: 0.361, 0.213   40: 0.729, 0.462   60: 1.239, 1.039
+//   value, gradient  m = 10: 0.180, 0.078   30: 0.361, 0.213   40: 0.729, 0.462   60: 1.239, 0.962
 // The rule does not look at the number of points, so that a field gives the
 // same bits alone and in a plan, nor at the gradient, so that the value is the
 // same with and without it; a launch too small to fill the GPU waits longer
