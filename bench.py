@@ -53,16 +53,17 @@ FP64_PEAK_TFLOPS = 78.6   # MI355X FP64 vector (and matrix) peak: 256 CU x 2.4 G
 # The record describes the kernel sources it was measured on only, so it is
 # reported when their digest still matches (kernel_sources_digest).
 MEASURED_TRAFFIC = {
-    "sources_sha256": "889c220c3831158fe298add76f30a8e6c52522e07d8e3b70db4fb2defa6e8b6d",
+    "sources_sha256": "77aadbc982647fe27d303b7274167656f34f86cf9dd139ad52fbadc5e849e8c8",
     "workload": "n1M_m120_nu0.5", "variant": "tile_w4",
-    "fetch_kib_raw": 9754650.7083, "fetch_factor": 524288.0 / 262167.25,
-    "write_kib_raw": 8415836.7500, "write_factor": 524288.0 / 524288.0,
-    "f64_add": 1628957056.0, "f64_mul": 3441903358.0, "f64_fma": 8037825600.0, "f64_trans": 433989312.0,
-    "f64_mfma_mops": 1792000000.0,
+    "fetch_kib_raw": 7981367.4792, "fetch_factor": 524288.0 / 262167.25,
+    "write_kib_raw": 62500.3021, "write_factor": 524288.0 / 524288.0,
+    "f64_add": 977972631.0, "f64_mul": 1719953929.0, "f64_fma": 7012844845.0, "f64_trans": 392990877.0,
+    "f64_mfma_mops": 1440000000.0,
 }
 
 
-KERNEL_SOURCES = ("device_common.h", "exp_table.h", "kernel_lds.h", "kernel_tile.h", "launch.h",
+KERNEL_SOURCES = ("device_common.h", "exp_table.h", "kernel_lds.h", "kernel_rows.h", "kernel_tile.h", "launch.h",
+                  "log_table.h",
                   "kernels_nu05.hip", "kernels_nu15.hip", "kernels_nu25.hip")
 
 
@@ -134,7 +135,7 @@ def host_cpu_info():
     return {"lscpu_model": model, "nproc": os.cpu_count() or 1, "cpus_allowed": allowed}
 
 
-# The GPU machine gives one GPU a share of 16 host CPUs, whatever nproc shows; the
+# One GPU comes with a share of 16 host CPUs, whatever nproc shows; the
 # oracle's OpenMP threads stay within that share.
 HOST_CPU_SHARE = 16
 
