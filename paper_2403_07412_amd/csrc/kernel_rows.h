@@ -512,7 +512,6 @@ __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ l
             } else {
                 const uint32_t whole = ((uint32_t)kmin + 1) * (uint32_t)kmin / 32;  // rounds every lane takes part in
                 const uint32_t rounds = (((uint32_t)kmax + 1) * (uint32_t)kmax / 2 + 15) / 16;
-#pragma unroll 2
                 for (uint32_t c = 0; c < whole; ++c) {
                     add_pair(pair_dist(w));
                     w.next();

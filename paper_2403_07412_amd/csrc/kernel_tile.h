@@ -124,13 +124,16 @@ __host__ __device__ constexpr int lockstep_group(int T, int W) { return (T <= 5 
 //   T = 4, W = 2 (m from 47 to 62; LDS leaves room only without the
 //     gradient): 2.82 ms at nine workgroups against 2.89 ms at eight for the
 //     same points at m = 60, value only.
+//   T = 11, W = 4, great circle (m of 159 and 160): Matern 3/2 value + gradient
+//     3.91 ms at three workgroups against 4.65 ms at two, power exponential
+//     4.48 against 5.52 ms, for 20,000 points.
 // (Times and spills of the first two from before the covariances and the
 // contraction became leaner: T = 8 now fits at 125 VGPRs and T = 10 at 166,
 // without scratch.)
 // T = 7 and 9 with W = 4, T = 2 to 4 with W = 1 and T = 3, 5, 6 with W = 2
 // measured no faster one workgroup up.  Other shapes keep the estimate.
 __host__ __device__ constexpr bool tile_measured_raise(int T, int W, bool gcd) {
-    return ((T == 8 || T == 10) && W == 4 && !gcd) || (T == 4 && W == 2 && !gcd);
+    return ((T == 8 || T == 10) && W == 4 && !gcd) || (T == 4 && W == 2 && !gcd) || (T == 11 && W == 4 && gcd);
 }
 
 // Occupancy target (wavefronts per SIMD) the register allocation aims at.
@@ -595,7 +598,9 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
     constexpr bool SHARE_D = Ls::INPLACE && G > 1 && T >= 2;
     constexpr int DCH = SHARE_D ? ((T - 1) * DS) / kWave : 1;  // 64-double chunks per vector past slot 0
     static_assert(!SHARE_D || G * DCH >= 4 * NTW, "the shared distances fit in the panel slots");
-    auto dslot = [&](int p) -> double * { return smem + Ls::SLOT + (p / DCH) * Ls::SLOT_G + DS + (p % DCH) * kWave; };
+    auto dslot = [&](int p) __attribute__((always_inline)) -> double * {
+        return smem + Ls::SLOT + (p / DCH) * Ls::SLOT_G + DS + (p % DCH) * kWave;
+    };
     if constexpr (SHARE_D) {
 #pragma unroll
         for (int s = 0; s < NTW; ++s) {
@@ -611,12 +616,12 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
         }
         __syncthreads();
     }
-#pragma unroll
-    for (int s = 0; s < NTW; ++s) {
+    auto fill = [&](auto sc) __attribute__((always_inline)) {
+        const int s = sc;
         tile[s] = dvec4{0.0, 0.0, 0.0, 0.0};
         if constexpr (KEEP_D) dtile[s] = dvec4{0.0, 0.0, 0.0, 0.0};
         const int R_ = SR(s), C_ = SC(s);
-        if (!SVALID(s)) continue;
+        if (!SVALID(s)) return;
         const int b = 16 * C_ + j;
         const double xb = XY[2 * b], yb = XY[2 * b + 1], cb = GCD ? CLv[b] : 0.0;
 #pragma unroll
@@ -643,6 +648,15 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
 #pragma unroll
             for (int r = 0; r < 4; ++r) tile[s][r] = augment_value(16 * R_ + 4 * r + g, b, k, tile[s][r], Z);
         }
+    };
+    // Great-circle codes as a template loop: with the branches of far pairs the
+    // optimiser gives up a loop of this length, and the tiles, indexed at run
+    // time, go to scratch memory.
+    if constexpr (GCD) {
+        static_for<0, NTW>(fill);
+    } else {
+#pragma unroll
+        for (int s = 0; s < NTW; ++s) fill(s);
     }
     // every wavefront has read the shared distances before any writes a
     // panel tile over them
@@ -742,7 +756,7 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
             double su = 0.0, sb = 0.0;
             int uo = 2 * g;  // the lane's rows within a block of the solution, opaque per step (no hoisting)
             asm volatile("" : "+v"(uo));
-            auto add_tile = [&](const dvec4 &L, int R) {
+            auto add_tile = [&](const dvec4 &L, int R) __attribute__((always_inline)) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const double2 x = *reinterpret_cast<const double2 *>(UB + 32 * R + 8 * r + uo);
@@ -848,13 +862,13 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
             a16 = min(a16, a16 - N16);
             uint32_t sa16 = sb16 + so16;
             sa16 = min(sa16, sa16 - N16);
-            auto next_item = [&]() {
+            auto next_item = [&]() __attribute__((always_inline)) {
                 b16 += sb16;
                 a16 += sa16 + (b16 >= N16 ? 16u : 0u);
                 b16 = min(b16, b16 - N16);
                 a16 = min(a16, a16 - N16);
             };
-            auto pair_dist = [&](uint32_t pa, uint32_t pb) {
+            auto pair_dist = [&](uint32_t pa, uint32_t pb) __attribute__((always_inline)) {
                 const double2 xa = *reinterpret_cast<const double2 *>(XYb + pa);
                 const double2 xb = *reinterpret_cast<const double2 *>(XYb + pb);
                 return pair_dist_pow<KC>(xa.x, xa.y, GCD ? CLv[pa / 16] : 0.0, xb.x, xb.y, GCD ? CLv[pb / 16] : 0.0, P,
@@ -875,7 +889,7 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
                 b16 = b0;
                 a16 = a0;
             }
-            auto add_item = [&](uint32_t pa, uint32_t pb, int c) {
+            auto add_item = [&](uint32_t pa, uint32_t pb, int c) __attribute__((always_inline)) {
                 double da;
                 if constexpr (SHARE_D) da = dslot(c)[l];
                 else da = pair_dist(pa, pb);
@@ -886,7 +900,6 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
                 gb = fma(dr, fma(ua.x, vb.y, vb.x * ua.y), gb);
             };
             const uint32_t whole = NP / NTG;  // rounds in which every lane has an item
-#pragma unroll 2
             for (uint32_t c = 0; c < whole; ++c) {
                 add_item(a16, b16, (int)c);
                 next_item();

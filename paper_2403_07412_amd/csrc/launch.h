@@ -27,8 +27,9 @@ struct LdsImpl {
     static constexpr int NT = 256;
     static constexpr int WPE = 2;  // wavefronts per SIMD the register allocation targets
     static size_t smem(int m) { return lds_kernel_smem_bytes(m); }
-    static __device__ CondOut run(const double *locs, const double *z, const int32_t *nbr, int64_t i, int64_t n,
-                                  int32_t m, const double *qloc, const Params &P, double *sm) {
+    static __device__ __forceinline__ CondOut run(const double *locs, const double *z, const int32_t *nbr, int64_t i,
+                                                  int64_t n, int32_t m, const double *qloc, const Params &P,
+                                                  double *sm) {
         return lds_conditional<KC, GRAD>(locs, z, nbr, i, n, m, qloc, P, sm);
     }
 };
@@ -44,8 +45,9 @@ struct TileImpl {
                                    ? VECCHIA_WPE_OVERRIDE
                                    : tile_waves_per_simd(T, W, GRAD && keep_dbeta(T, W, GCD), GRAD, GCD, G);
     static size_t smem(int) { return TileLds<T, W, GRAD, GCD, G, kc_family(KC) == 3>::BYTES; }
-    static __device__ CondOut run(const double *locs, const double *z, const int32_t *nbr, int64_t i, int64_t n,
-                                  int32_t m, const double *qloc, const Params &P, double *sm) {
+    static __device__ __forceinline__ CondOut run(const double *locs, const double *z, const int32_t *nbr, int64_t i,
+                                                  int64_t n, int32_t m, const double *qloc, const Params &P,
+                                                  double *sm) {
         return tile_conditional<T, W, KC, GRAD, G>(locs, z, nbr, i, n, m, qloc, P, sm);
     }
 };

@@ -68,3 +68,9 @@ def test_other_codes_match_oracle(lib, cov, m):
         assert_total_close(got.item(), oracle.compensated_sum(ell), 1e-10, f"m={m}")
     assert_grad_close(grad.cpu().numpy(), [oracle.compensated_sum(gref[:, p]) for p in range(3)],
                       np.abs(gref).sum(0), 1e-9, f"m={m}")
+
+
+@pytest.mark.parametrize("cov", [(1, 0, 0.9), (0, 1, 0.5), (0, 1, 1.5), (0, 1, 2.5), (1, 1, 0.9)])
+@pytest.mark.parametrize("m", [159, 160])
+def test_other_codes_with_eleven_tile_rows(lib, cov, m):
+    test_other_codes_match_oracle(lib, cov, m)
