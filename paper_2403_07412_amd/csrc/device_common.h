@@ -193,14 +193,12 @@ __device__ __forceinline__ double cov_scaled(double d, const Params &P, const do
 //
 // The exponential of exp_neg_tab rearranged for fewer instructions (16 against
 // 22 with the table's address; the tiled kernels evaluate it for every pair
-// and are bound by vector issue).  Entry j of the staged table holds hi = 2^(j/64) with j 2^14
-// subtracted from its high word, and lo / hi: adding n 2^14 = k 2^20 + j 2^14
-// to the high word then scales hi by 2^k in one integer instruction, and the
-// low part joins e^f - 1 in the polynomial's last step.  n = rint(64 x / ln2)
-// is the low word of 64 x / ln2 + 1.5 2^52.
+// and are bound by vector issue).  Entry j of the staged table holds hi =
+// 2^(j/64) and lo / hi, so that the low part joins e^f - 1 in the polynomial's
+// last step.  n = rint(64 x / ln2) is the low word of 64 x / ln2 + 1.5 2^52.
 __device__ __forceinline__ void stage_exp_entry(int j, double *tab) {
     const ExpTableEntry e = kExp2Frac64[j];
-    tab[2 * j] = __hiloint2double(__double2hiint(e.hi) - (j << 14), __double2loint(e.hi));
+    tab[2 * j] = e.hi;
     tab[2 * j + 1] = e.lo * __builtin_amdgcn_rcp(e.hi);  // |lo / hi| < 2^-53: the estimate is plenty
 }
 
@@ -217,7 +215,7 @@ template <bool PIN>
 __device__ __forceinline__ CovConst cov_const() {
     constexpr double A2 = (0.6931471805599453 / 128.0) * (0.6931471805599453 / 128.0);  // the largest f^2
     CovConst c{0x1p-1000, 0x1.8p52, 1.0 / 24.0 + 1.5 * A2 / 720.0, -0x1.8p52, -0x1.71547652b82fep+6, -0x1.62e42fefa0000p-7,
-               -0x1.cf79abc9e3b3ap-46, 1.0 / 120.0, 1.0 / 6.0, 0.5 - 0.5625 * A2 * A2 / 720.0, 708.0};
+               -0x1.cf79abc9e3b3ap-46, 1.0 / 120.0, 1.0 / 6.0, 0.5 - 0.5625 * A2 * A2 / 720.0, 746.0};
     if constexpr (PIN) {
         asm volatile("" : "+v"(c.eps), "+v"(c.magic), "+v"(c.c24));
         asm volatile("" : "+s"(c.unmagic), "+s"(c.inv_ln2_64), "+s"(c.head), "+s"(c.tail));
@@ -243,13 +241,12 @@ __device__ __forceinline__ dvec2 table_entry(LdsTab tab, uint32_t j) {
     return *(const __attribute__((address_space(3))) dvec2 *)(uintptr_t)a;
 }
 
-// e^-r for r >= -709, one rounding at the end (just above half an ulp, as
-// exp_neg_tab).  Arguments beyond 708 give e^-708 (3e-308), NaN as well, so
-// callers validate their inputs.  e^f - 1 is the Taylor polynomial with its
-// last term, f^6 / 720, replaced by the Chebyshev fit of lower degree, f^6 =
-// 3/2 a^2 f^4 - 9/16 a^4 f^2 to a^6 / 16 on |f| <= a = ln2 / 128 (2e-18 of e^f).
+// e^-r for -709 <= r <= 746, one rounding at the end (just above half an ulp,
+// as exp_neg_tab) and another below the normal range; 0 at 746, where
+// scaled_dist stops.  e^f - 1 is the Taylor polynomial with its last term,
+// f^6 / 720, replaced by the Chebyshev fit of lower degree, f^6 = 3/2 a^2 f^4 -
+// 9/16 a^4 f^2 to a^6 / 16 on |f| <= a = ln2 / 128 (2e-18 of e^f).
 __device__ __forceinline__ double exp_neg_staged(double r, LdsTab tab, const CovConst &c) {
-    r = fmin(r, c.rmax);
     const double t = fma(r, c.inv_ln2_64, c.magic);
     const int n = __double2loint(t);
     const double nf = t + c.unmagic;
@@ -260,8 +257,7 @@ __device__ __forceinline__ double exp_neg_staged(double r, LdsTab tab, const Cov
     q = fma(q, f, c.half);
     q = fma(q, f, 1.0);
     const dvec2 e = table_entry(tab, n & 63);
-    const double hi = __hiloint2double(__double2hiint(e.x) + (n << 14), __double2loint(e.x));
-    return fma(hi, fma(q, f, e.y), hi);
+    return __builtin_ldexp(fma(e.x, fma(q, f, e.y), e.x), n >> 6);
 }
 
 // Distance of two points from their coordinate differences, without a branch:
@@ -477,8 +473,16 @@ __device__ __forceinline__ double pair_dist_pow(double xa, double ya, double ca,
     }
 }
 
-// Covariance from da = pair_dist_pow: sigma2 e^-r, sigma2 (1 + r) e^-r,
-// sigma2 (1 + r + r^2 / 3) e^-r with r = da / beta.  Every sum is an explicit
+// The scaled distance r = da / beta of the closed forms, da = pair_dist_pow, at
+// most 746: there e^-r is 0, and the powers of r that multiply it cannot bring
+// it back (or overflow), however small beta is.  Kernels use this r in every
+// factor.  A NaN becomes 746 as well, so callers validate their inputs.
+__device__ __forceinline__ double scaled_dist(double da, const Params &P, const CovConst &c) {
+    return fmin(da * P.inv_beta, c.rmax);
+}
+
+// Covariance from r = scaled_dist and e = e^-r: sigma2 e^-r, sigma2 (1 + r) e^-r,
+// sigma2 (1 + r + r^2 / 3) e^-r.  Every sum is an explicit
 // FMA: kernels that share distances between parameter vectors must give the
 // bits of those that do not, so nothing is left for the compiler to contract
 // in one kernel and not in another.

@@ -253,7 +253,7 @@ __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ l
                     } else {
                         da = column_dist(Cc, cc);
                     }
-                    const double rs = da * P.inv_beta;
+                    const double rs = scaled_dist(da, P, CC);
                     const double e = exp_neg_staged(rs, ET, CC);
                     const double v = cov_value<KC>(rs, e, P);
                     A[tix(C, C)][c] = (j == c) ? diag : v;
@@ -287,7 +287,7 @@ __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ l
                     } else {
                         da = column_dist(Rc, cc);
                     }
-                    const double rs = da * P.inv_beta;
+                    const double rs = scaled_dist(da, P, CC);
                     const double e = exp_neg_staged(rs, ET, CC);
                     A[tix(R, C)][c] = cov_value<KC>(rs, e, P);
                     if constexpr (KEEP) D[tix(R, C)][c] = dbeta_raw<KC>(rs, e);
@@ -485,7 +485,7 @@ __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ l
                                          P, ET, CC);
             };
             auto add_pair = [&](double da) __attribute__((always_inline)) {
-                const double rs = da * P.inv_beta;
+                const double rs = scaled_dist(da, P, CC);
                 const double d = dbeta_raw<KC>(rs, exp_neg_staged(rs, ET, CC));
                 const double2 ua = *reinterpret_cast<const double2 *>(UBb + w.a);
                 const double2 vb = *reinterpret_cast<const double2 *>(UBb + w.b);

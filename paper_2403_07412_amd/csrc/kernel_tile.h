@@ -588,6 +588,7 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
     constexpr bool KEEP_D = GRAD && keep_dbeta(T, W, GCD);
     const LdsTab ET = lds_table(smem + Ls::EXPT);
     const CovConst CC = cov_const<W == 1>();
+    const double diag = P.sigma2 + P.tau2;
     dvec4 tile[NTW];
     dvec4 dtile[KEEP_D ? NTW : 1];
     // With one wavefront per vector (INPLACE) every group needs the same
@@ -634,7 +635,7 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
                 const double2 pa = *reinterpret_cast<const double2 *>(XY + 2 * a);
                 da = pair_dist_pow<KC>(pa.x, pa.y, GCD ? CLv[a] : 0.0, xb, yb, cb, P, ET, CC);
             }
-            const double rs = da * P.inv_beta;
+            const double rs = scaled_dist(da, P, CC);
             const double e = exp_neg_staged(rs, ET, CC);
             tile[s][r] = cov_value<KC>(rs, e, P);
             if constexpr (KEEP_D) dtile[s][r] = dbeta_raw<KC>(rs, e);
@@ -642,7 +643,7 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
         if (R_ == C_) {
             asm volatile("");  // a branch: the selects cost more than it
 #pragma unroll
-            for (int r = 0; r < 4; ++r) tile[s][r] = (4 * r + g == j) ? tile[s][r] + P.tau2 : tile[s][r];
+            for (int r = 0; r < 4; ++r) tile[s][r] = (4 * r + g == j) ? diag : tile[s][r];
         }
         if (16 * R_ + 15 > k) {
 #pragma unroll
@@ -893,7 +894,7 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
                 double da;
                 if constexpr (SHARE_D) da = dslot(c)[l];
                 else da = pair_dist(pa, pb);
-                const double rs = da * P.inv_beta;
+                const double rs = scaled_dist(da, P, CC);
                 const double dr = dbeta_raw<KC>(rs, exp_neg_staged(rs, ET, CC));
                 const double2 ua = *reinterpret_cast<const double2 *>(UBb + pa);
                 const double2 vb = *reinterpret_cast<const double2 *>(UBb + pb);
