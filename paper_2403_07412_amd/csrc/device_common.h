@@ -477,8 +477,8 @@ __device__ __forceinline__ double pair_dist_pow(double xa, double ya, double ca,
 // most 746: there e^-r is 0, and the powers of r that multiply it cannot bring
 // it back (or overflow), however small beta is.  Kernels use this r in every
 // factor.  A NaN becomes 746 as well, so callers validate their inputs.
-__device__ __forceinline__ double scaled_dist(double da, const Params &P, const CovConst &c) {
-    return fmin(da * P.inv_beta, c.rmax);
+__device__ __forceinline__ double scaled_dist(double da, double inv_beta, const CovConst &c) {
+    return fmin(da * inv_beta, c.rmax);
 }
 
 // Covariance from r = scaled_dist and e = e^-r: sigma2 e^-r, sigma2 (1 + r) e^-r,

@@ -172,6 +172,10 @@ __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ l
     double A[NT][16], D[KEEP ? NT : 1][16];
     auto tix = [](int R, int C) constexpr { return R * (R + 1) / 2 + C; };
     const double diag = P.sigma2 + P.tau2;
+    // 1 / beta for columns c and 16 - c of a diagonal tile with dC/dbeta: lane 0 has
+    // the diagonal of column 16 - c, whose distance of 2^-500 is not small under
+    // every beta
+    const double inv_beta_two = j > 0 ? P.inv_beta : 0.0;
     // tile (R, C) by columns, as the back substitution takes it: register r of
     // lane n is L[r][n]
     auto transpose = [&](const double (&src)[16], double (&dst)[16]) __attribute__((always_inline)) {
@@ -253,7 +257,7 @@ __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ l
                     } else {
                         da = column_dist(Cc, cc);
                     }
-                    const double rs = scaled_dist(da, P, CC);
+                    const double rs = scaled_dist(da, KEEP && two ? inv_beta_two : P.inv_beta, CC);
                     const double e = exp_neg_staged(rs, ET, CC);
                     const double v = cov_value<KC>(rs, e, P);
                     A[tix(C, C)][c] = (j == c) ? diag : v;
@@ -264,7 +268,7 @@ __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ l
                     if constexpr (KEEP) {
                         const double d = dbeta_raw<KC>(rs, e);
                         D[tix(C, C)][c] = (j > c) ? d : 0.0;
-                        // lane 16 - c receives its own column's diagonal, about 2^-500
+                        // lane 16 - c receives its own column's diagonal from lane 0, exactly 0
                         if constexpr (two) D[tix(C, C)][16 - c] = shift_up<16 - c>(d);
                     }
                 } else {
@@ -287,7 +291,7 @@ __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ l
                     } else {
                         da = column_dist(Rc, cc);
                     }
-                    const double rs = scaled_dist(da, P, CC);
+                    const double rs = scaled_dist(da, P.inv_beta, CC);
                     const double e = exp_neg_staged(rs, ET, CC);
                     A[tix(R, C)][c] = cov_value<KC>(rs, e, P);
                     if constexpr (KEEP) D[tix(R, C)][c] = dbeta_raw<KC>(rs, e);
@@ -485,7 +489,7 @@ __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ l
                                          P, ET, CC);
             };
             auto add_pair = [&](double da) __attribute__((always_inline)) {
-                const double rs = scaled_dist(da, P, CC);
+                const double rs = scaled_dist(da, P.inv_beta, CC);
                 const double d = dbeta_raw<KC>(rs, exp_neg_staged(rs, ET, CC));
                 const double2 ua = *reinterpret_cast<const double2 *>(UBb + w.a);
                 const double2 vb = *reinterpret_cast<const double2 *>(UBb + w.b);

@@ -635,7 +635,7 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
                 const double2 pa = *reinterpret_cast<const double2 *>(XY + 2 * a);
                 da = pair_dist_pow<KC>(pa.x, pa.y, GCD ? CLv[a] : 0.0, xb, yb, cb, P, ET, CC);
             }
-            const double rs = scaled_dist(da, P, CC);
+            const double rs = scaled_dist(da, P.inv_beta, CC);
             const double e = exp_neg_staged(rs, ET, CC);
             tile[s][r] = cov_value<KC>(rs, e, P);
             if constexpr (KEEP_D) dtile[s][r] = dbeta_raw<KC>(rs, e);
@@ -894,7 +894,7 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
                 double da;
                 if constexpr (SHARE_D) da = dslot(c)[l];
                 else da = pair_dist(pa, pb);
-                const double rs = scaled_dist(da, P, CC);
+                const double rs = scaled_dist(da, P.inv_beta, CC);
                 const double dr = dbeta_raw<KC>(rs, exp_neg_staged(rs, ET, CC));
                 const double2 ua = *reinterpret_cast<const double2 *>(UBb + pa);
                 const double2 vb = *reinterpret_cast<const double2 *>(UBb + pb);

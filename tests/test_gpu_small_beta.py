@@ -27,6 +27,13 @@ def test_uncorrelated_points(v, cov, m):
     uncorrelated_points(v, cov, m)
 
 
+@pytest.mark.parametrize("cov", CODES)
+@pytest.mark.parametrize("m", [1, 5, 14, 15, 30])
+def test_uncorrelated_points_in_small_sets(v, cov, m):
+    """Up to two tile rows the derivative stays in registers from the fill, the diagonal's included."""
+    uncorrelated_points(v, cov, m)
+
+
 def uncorrelated_points(v, cov, m):
     """Lattice points at least 0.5 apart under beta from 1e-60 down: every covariance is 0, so the terms are
     those of independent points and the beta-derivative is exactly 0."""
