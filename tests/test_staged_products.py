@@ -2,9 +2,10 @@
 the steps of the staged exponential with the header's clamp, times the powers of the clamped distance that the
 closed forms multiply it by."""
 import math
+import random
 import re
 import struct
-from decimal import Decimal
+from decimal import Decimal, getcontext
 
 import pytest
 
@@ -38,3 +39,38 @@ def test_products_vanish_with_the_exponential(beta):
 def test_clamp_is_the_first_zero():
     c = _clamp()
     assert _exp_neg(c) == 0.0 and 0.0 < _exp_neg(c - 2.0) < 1e-322
+
+
+def _staged_exp(r):
+    """exp_neg_staged's own lines and constants, statement by statement."""
+    text = _body("device_common.h", "struct CovConst {")
+    names = [x.strip() for line in re.findall(r"double ([^;]+);", text) for x in line.split(",")]
+    init = _body("device_common.h", "CovConst cov_const()")
+    values = re.search(r"CovConst c\{(.*?)\};", init, re.S).group(1).split(",")
+    a2 = re.search(r"constexpr double A2 = (.*?);", init)
+    scope = {"A2": eval(a2.group(1))} if a2 else {}
+
+    def number(x):
+        return re.sub(r"-?0x[0-9a-f.]+p[-+]?\d+", lambda h: repr(float.fromhex(h.group(0))), x.strip())
+
+    const = {n: eval(number(v), scope) for n, v in zip(names, values)}
+    body = _body("device_common.h", "__device__ __forceinline__ double exp_neg_staged(")
+    t = fma(r, const["inv_ln2_64"], const["magic"])
+    env = {"fma": fma, "c": type("C", (), const), "r": r, "t": t, "nf": t + const["unmagic"]}
+    n = struct.unpack("<i", struct.pack("<d", t)[:4])[0]
+    for var, expr in re.findall(r"\b([fq]) = (fma\([^;]*\));", body):
+        env[var] = eval(expr, env)
+    hi, lo = _pairs("exp_table.h")[n & 63]
+    return math.ldexp(fma(hi, fma(env["q"], env["f"], lo / hi), hi), n >> 6)
+
+
+def test_exponential_rounds_once():
+    """Half an ulp for the last rounding; 0.004 for the correction's (below 2^-7.5, rounded to 53 bits), 0.003
+    for the polynomial's, and the truncated f^7 / 5040: 0.508 ulp, the bound of the unstaged form as well."""
+    rng = random.Random(5)
+    getcontext().prec = 40
+    for _ in range(3000):
+        r = rng.uniform(0.0, 40.0)
+        exact = (-Decimal(r)).exp()
+        ulp = Decimal(2) ** (math.frexp(float(exact))[1] - 53)
+        assert abs(Decimal(_staged_exp(r)) - exact) <= Decimal("0.508") * ulp, r
