@@ -322,19 +322,22 @@ __device__ __forceinline__ void stage_tables(int t, double *tab) {
     if constexpr (kc_family(KC) == 3) {
         if (t < kLogTableSize) {
             tab[2 * kExpTableSize + 2 * t] = kLogMant64[t].c;
-            tab[2 * kExpTableSize + 2 * t + 1] = kLogMant64[t].neg_log_c;
+            tab[2 * kExpTableSize + 2 * t + 1] = t < kLogLowEntries ? kLogMantLow[t] : kLogMant64[t].neg_log_c;
         }
     }
 }
 
-// log x for positive normal x, to an absolute error of about half an ulp of
-// the result plus 2^-54 (it feeds an exponential): x = 2^k m with m in
-// [1/2, 1), r = m c - 1 with c near 1 / m (|r| <= 2^-7), log x = k ln2 - log c
-// + log1p r, the last by its Taylor polynomial of degree 7 (truncation 2e-18).
-__device__ __forceinline__ double log_staged(double x, LdsTab tab) {
+// log x + a b for positive normal x, to about half an ulp of the result plus
+// 2^-54 (|a b| < 0.004; log x alone with a = 0), and within 2^-58 near 1, where the result is small (it feeds an
+// exponential): x = 2^e m with m in [1/2, 1), r = m c - 1 with c near 1 / m
+// (|r| <= 2^-7), log x = e ln2 - log c + log1p r, the last by its Taylor
+// polynomial of degree 7 (truncation 2e-18).  Mantissas of the table's first
+// entries count as 2 m and 2^(e - 1), so that no ln2 cancels near 1.
+__device__ __forceinline__ double log_staged(double x, double a, double b, LdsTab tab) {
     const double m = __builtin_amdgcn_frexp_mant(x);
-    const double k = (double)__builtin_amdgcn_frexp_exp(x);
-    const int j = (__double2hiint(m) >> 14) & 63;
+    const int hi = __double2hiint(x);
+    const double k = (double)((hi - ((1022 << 20) + (kLogLowEntries << 14))) >> 20);
+    const int j = (hi >> 14) & 63;
     const dvec2 e = table_entry(tab + 2 * kExpTableSize, j);
     const double r = fma(m, e.x, -1.0);
     double p = fma(r, 1.0 / 7.0, -1.0 / 6.0);
@@ -342,7 +345,7 @@ __device__ __forceinline__ double log_staged(double x, LdsTab tab) {
     p = fma(p, r, -1.0 / 4.0);
     p = fma(p, r, 1.0 / 3.0);
     p = fma(p, r, -0.5);
-    p = fma(r * r, p, r);
+    p = fma(r * r, p, fma(a, b, r));
     // ln2 as a 32-bit head (k head is exact) and a tail
     return fma(k, 0x1.62e42fee00000p-1, e.y + fma(k, 0x1.a39ef35793c76p-33, p));
 }
@@ -413,8 +416,9 @@ __device__ __forceinline__ double sqrt_lean(double x) {
 //
 // Great-circle distances: h = hav(d / R) as in gcd_km, d = 2 R asin sqrt h by
 // the series of asin(s) / s in h up to h = 0.01 (1270 km).  For the power exponential the
-// square root is not taken: ln d = ln(4 R^2 h) / 2 + ln(asin(s) / s), the last
-// by its own series in h (to h^7, truncation 8e-19).
+// square root is not taken: 2 ln d = ln(4 R^2 h) + 2 ln(asin(s) / s), the last
+// by its own series in h (to h^7, truncation 8e-19), added before the
+// logarithm's last rounding.
 template <int KC>
 __device__ __forceinline__ double pair_dist_pow(double xa, double ya, double ca, double xb, double yb, double cb,
                                                 const Params &P, LdsTab tab, const CovConst &cc) {
@@ -446,8 +450,8 @@ __device__ __forceinline__ double pair_dist_pow(double xa, double ya, double ca,
                 p = fma(p, h, 191.0 / 5670.0);
                 p = fma(p, h, 11.0 / 180.0);
                 p = fma(p, h, 1.0 / 6.0);
-                const double lnd = fma(0.5, log_staged(h * (r2 * r2), tab), p * h);
-                const double da = exp_neg_staged(-(P.alpha * lnd), tab, cc);
+                const double lnd2 = log_staged(h * (r2 * r2), h + h, p, tab);
+                const double da = exp_neg_staged(-((0.5 * P.alpha) * lnd2), tab, cc);
                 return h > 0x1p-999 ? da : 0.0;
             }
         }
@@ -467,7 +471,7 @@ __device__ __forceinline__ double pair_dist_pow(double xa, double ya, double ca,
         double d = dist_pos(xa - xb, ya - yb, cc);
         if constexpr (kc_family(KC) == 3) {
             if (P.alpha == 2.0) d = d * d;
-            else if (P.alpha != 1.0) d = d > 0x1p-499 ? exp_neg_staged(-(P.alpha * log_staged(d, tab)), tab, cc) : 0.0;
+            else if (P.alpha != 1.0) d = d > 0x1p-499 ? exp_neg_staged(-(P.alpha * log_staged(d, 0.0, 0.0, tab)), tab, cc) : 0.0;
         }
         return d;
     }

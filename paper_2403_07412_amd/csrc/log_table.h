@@ -78,4 +78,20 @@ constexpr LogTableEntry kLogMant64[kLogTableSize] = {
     {0x1.0100000000000p+0, -0x1.ff00aa2b10bc0p-9},
 };
 
+// -ln(c_j / 2) of the first entries, for mantissas below 0.703: the logarithm
+// takes these as twice the mantissa under an exponent one less, so that
+// arguments just above 1 do not add ln2 to a -ln c near -ln2.
+constexpr int kLogLowEntries = 26;
+constexpr double kLogMantLow[kLogLowEntries] = {
+    0x1.010157588de71p-7, 0x1.7c61b1cf5dee0p-6, 0x1.39f07ba0ebd62p-5,
+    0x1.b35dd9b58baadp-5, 0x1.174f76ab09171p-4, 0x1.518874226130ap-4,
+    0x1.8c985e9b9ec84p-4, 0x1.c6494a2e418a6p-4, 0x1.fe89139dbd566p-4,
+    0x1.1bc8af21436b3p-3, 0x1.3789c4c041337p-3, 0x1.527e5e4a1b58dp-3,
+    0x1.6dcf0165f8373p-3, 0x1.884807ce5638fp-3, 0x1.a1dfc40f1b7f1p-3,
+    0x1.bbca696b07e80p-3, 0x1.d60a17f903515p-3, 0x1.ef5ade4dcffe6p-3,
+    0x1.03d95a1d67686p-2, 0x1.102ac0a35cc1cp-2, 0x1.1ca28c64bae54p-2,
+    0x1.2896a13e086a4p-2, 0x1.34aedad5b168bp-2, 0x1.403d086cea79cp-2,
+    0x1.4becf95d97913p-2, 0x1.57bf753c8d1fbp-2,
+};
+
 }  // namespace vecchia

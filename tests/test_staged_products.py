@@ -9,7 +9,7 @@ from decimal import Decimal, getcontext
 
 import pytest
 
-from test_staged_functions import _body, _exp_constants, _pairs, fma
+from test_staged_functions import _body, _exp_constants, _pairs, _read, fma
 
 
 def _clamp():
@@ -74,3 +74,29 @@ def test_exponential_rounds_once():
         exact = (-Decimal(r)).exp()
         ulp = Decimal(2) ** (math.frexp(float(exact))[1] - 53)
         assert abs(Decimal(_staged_exp(r)) - exact) <= Decimal("0.508") * ulp, r
+
+
+def test_logarithm_near_one():
+    """Within 2^-8 of 1 the table's term is below 2^-6 and its rounding and that of the sum with it below 2^-59
+    each; the result's own rounding is smaller."""
+    text = _read("log_table.h")
+    low = [float.fromhex(x) for x in re.findall(r"0x[\d.a-f]+p[-+]\d+", text[text.index("kLogMantLow["):].split("}")[0])]
+    pairs = _pairs("log_table.h")
+    getcontext().prec = 40
+    for (c, _), neg in zip(pairs, low):
+        exact = -(Decimal(c) / 2).ln()
+        assert abs(Decimal(neg) - exact) <= Decimal(math.ulp(neg)) / 2
+    head, tail = float.fromhex("0x1.62e42fee00000p-1"), float.fromhex("0x1.a39ef35793c76p-33")
+    rng = random.Random(9)
+    for x in [1.0, 1.0 + 2.0 ** -52, 1.0 - 2.0 ** -53] + [1.0 + rng.uniform(-2.0 ** -8, 2.0 ** -8) for _ in range(2000)]:
+        m, e = math.frexp(x)
+        j = int((m - 0.5) * 128)
+        c, neg = pairs[j]
+        if j < len(low):
+            e, neg = e - 1, low[j]
+        r = fma(m, c, -1.0)
+        p = fma(r, 1.0 / 7.0, -1.0 / 6.0)
+        for k in (1.0 / 5.0, -1.0 / 4.0, 1.0 / 3.0, -0.5):
+            p = fma(p, r, k)
+        got = fma(float(e), head, neg + fma(float(e), tail, fma(r * r, p, r)))
+        assert abs(Decimal(got) - Decimal(x).ln()) <= Decimal(2) ** -58, x
