@@ -542,23 +542,6 @@ __device__ __forceinline__ double matern_dbeta_r(double r, double sigma2_over_be
     }
 }
 
-// Both at once (one exponential).
-template <int NU>
-__device__ __forceinline__ void matern_and_dbeta_r(double r, double sigma2, double sigma2_over_beta, double &c,
-                                                   double &db) {
-    double e = exp_neg(r);
-    if constexpr (NU == 0 || NU == 3) {
-        c = sigma2 * e;
-        db = sigma2_over_beta * (r * e);
-    } else if constexpr (NU == 1) {
-        c = sigma2 * ((1.0 + r) * e);
-        db = sigma2_over_beta * ((r * r) * e);
-    } else {
-        c = sigma2 * ((1.0 + r * (1.0 + r * (1.0 / 3.0))) * e);
-        db = sigma2_over_beta * ((r * r) * (1.0 + r) * (1.0 / 3.0) * e);
-    }
-}
-
 __device__ __forceinline__ double dist2d(double ax, double ay, double bx, double by) {
     double dx = ax - bx;
     double dy = ay - by;

@@ -169,8 +169,8 @@ __host__ __device__ constexpr int tile_waves_per_simd(int T, int W, bool keep_d,
 // keeping at two wavefronts per SIMD, 2.56 recomputing at three; with four
 // wavefronts per conditional, m = 120, 50,000 points, keeping lost: 5.74
 // against 4.64 ms).  The one-wavefront shape of three tile rows always keeps
-// them (measured with Matern, whose shapes up to four rows the rows kernel has
-// since taken over, m = 40, 100,000 points: 0.63 against 0.73 ms).
+// them, which on Euclidean distances concerns the power exponential (m = 44,
+// 40,000 points: 0.381 ms keeping with 24 registers spilled, 0.454 recomputing).
 // Lockstep workgroups follow the one-vector decision: the two ways round the
 // derivative contract their arithmetic differently, and the lockstep results
 // must be the one-vector bits.

@@ -257,7 +257,11 @@ constexpr int kRowsItems = 4 * kRowsWaves;  // items per workgroup
 template <int T, int KC, bool GRAD>
 struct RowsImpl {
     static constexpr int NT = kRowsWaves * kWave;
-    // wavefronts per SIMD the tiles (and derivatives) held per lane leave room for
+    // wavefronts per SIMD the tiles (and derivatives) held per lane leave room
+    // for; with two rows of the other codes' values at the price of 12 to 42
+    // spilled registers (m = 28, 100,000 points, ms: power exponential 0.262, and
+    // 0.282 at two wavefronts without a spill; great circle 0.494 and 0.539, with
+    // Matern 3/2 0.439 and 0.476)
     static constexpr int WPE =
         GRAD ? (T == 1 ? 4 : 2) : (T == 1 ? 5 : T == 2 ? (KC < 3 ? 4 : 3) : T == 3 ? 3 : 2);
     static constexpr size_t SMEM = (kRowsWaves * RowsLds<T, GRAD, kc_gcd(KC)>::TOTAL + staged_doubles(kc_family(KC) == 3)) * sizeof(double);
@@ -492,14 +496,15 @@ int launch_tile(const EvalArgs &a, hipStream_t s) {
             if (a.group > 1 && (a.group != G || !a.k.fields || a.k.qlocs || a.k.ntheta % G != 0))
                 return VECCHIA_EUNSUPPORTED;
             return launch_rows<T, KC, GRAD>(a, s);
-        }
-        if (a.group > 1) {
-            if constexpr (G > 1) {
-                if (a.group == G) return launch_group_impl<TileImpl<T, W, KC, GRAD, G>>(a, s);
+        } else {
+            if (a.group > 1) {
+                if constexpr (G > 1) {
+                    if (a.group == G) return launch_group_impl<TileImpl<T, W, KC, GRAD, G>>(a, s);
+                }
+                return VECCHIA_EUNSUPPORTED;
             }
-            return VECCHIA_EUNSUPPORTED;
+            return launch_cond_impl<TileImpl<T, W, KC, GRAD>>(a, s);
         }
-        return launch_cond_impl<TileImpl<T, W, KC, GRAD>>(a, s);
     }
 }
 

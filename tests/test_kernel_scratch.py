@@ -1,7 +1,8 @@
-"""The register tiles of the tiled kernels stay in registers: scratch memory of the built kernels, from the
-metadata of the library's own code objects, holds spilled registers and nothing else (a tile array indexed at
-run time, or a function call, would add hundreds of bytes)."""
+"""The kernels of the built library, from the metadata of its own code objects.  The register tiles of the tiled
+kernels stay in registers: their scratch memory holds spilled registers and nothing else (a tile array indexed at
+run time, or a function call, would add hundreds of bytes).  And no kernel is compiled that no call launches."""
 import os
+import re
 import struct
 
 import msgpack
@@ -50,3 +51,13 @@ def test_tiles_are_not_in_scratch_memory():
     bad = [(k[".name"], k[".private_segment_fixed_size"], k[".vgpr_spill_count"]) for k in kernels
            if k[".private_segment_fixed_size"] > 4 * k[".vgpr_spill_count"] + 16 or k.get(".uses_dynamic_stack")]
     assert not bad
+
+
+def test_no_tiled_kernel_where_the_rows_kernel_runs():
+    """One wavefront, up to four tile rows (codes 0 .. 2) or two (3 .. 7): only the rows kernel is compiled."""
+    if not os.path.exists(LIB):
+        pytest.skip("the library is not built")
+    shapes = [tuple(map(int, m.groups())) for m in
+              (re.search(r"TileImplILi(\d+)ELi(\d+)ELi(\d+)E", k[".name"]) for k in _kernels()) if m]
+    assert shapes
+    assert not [s for s in shapes if s[1] == 1 and s[0] <= (4 if s[2] < 3 else 2)]
