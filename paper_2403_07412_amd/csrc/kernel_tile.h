@@ -142,9 +142,9 @@ __host__ __device__ constexpr bool tile_measured_raise(int T, int W, bool gcd) {
 // for the diagonal factorisation, the covariance code and addressing (the
 // compiler reports 143 VGPRs for T = 8, W = 4 with the gradient, nine tiles).
 // A lockstep workgroup (G parameter vectors) has G W wavefronts.
-__host__ __device__ constexpr int tile_waves_per_simd(int T, int W, bool keep_d, bool grad, bool gcd = false,
-                                                      int G = 1) {
-    const int lds = tile_lds_doubles(T, W, grad, gcd, G) * 8;
+__host__ __device__ constexpr int tile_waves_per_simd(int T, int W, bool keep_d, bool grad, bool gcd, int G,
+                                                      bool powexp) {
+    const int lds = tile_lds_doubles(T, W, grad, gcd, G, powexp) * 8;
     const int blocks_lds = 163840 / lds;
     const int need = 8 * tiles_per_wave(T, W) * (keep_d ? 2 : 1) + 72 + (gcd ? 16 : 0);
     const int wps_regs = 512 / need;                 // wavefronts per SIMD the registers allow
@@ -174,10 +174,10 @@ __host__ __device__ constexpr int tile_waves_per_simd(int T, int W, bool keep_d,
 // Lockstep workgroups follow the one-vector decision: the two ways round the
 // derivative contract their arithmetic differently, and the lockstep results
 // must be the one-vector bits.
-__host__ __device__ constexpr bool keep_dbeta(int T, int W, bool gcd = false) {
-    return VECCHIA_KEEP_DBETA &&
-           (tile_waves_per_simd(T, W, true, true, gcd) >= tile_waves_per_simd(T, W, false, true, gcd) ||
-            (gcd && W == 1 && tile_waves_per_simd(T, W, true, true, gcd) >= 2) || (T == 3 && W == 1));
+__host__ __device__ constexpr bool keep_dbeta(int T, int W, bool gcd, bool powexp) {
+    const int kept = tile_waves_per_simd(T, W, true, true, gcd, 1, powexp);
+    return VECCHIA_KEEP_DBETA && (kept >= tile_waves_per_simd(T, W, false, true, gcd, 1, powexp) ||
+                                  (gcd && W == 1 && kept >= 2) || (T == 3 && W == 1));
 }
 
 // Tile enumeration: column C descending, row R ascending inside a column, so
@@ -585,7 +585,7 @@ __device__ __forceinline__ CondOut tile_conditional(const double *__restrict__ l
     // padding) and diagonal tiles (the nugget) need per-entry cases; the
     // branches on them are uniform over the wavefront.  With the gradient,
     // dC/dbeta is kept in dtile from the same exponential when registers allow.
-    constexpr bool KEEP_D = GRAD && keep_dbeta(T, W, GCD);
+    constexpr bool KEEP_D = GRAD && keep_dbeta(T, W, GCD, kc_family(KC) == 3);
     const LdsTab ET = lds_table(smem + Ls::EXPT);
     const CovConst CC = cov_const<W == 1>();
     const double diag = P.sigma2 + P.tau2;

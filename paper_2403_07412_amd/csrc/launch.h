@@ -40,11 +40,14 @@ struct TileImpl {
     static constexpr int NT = G * W * kWave;
     static constexpr int GROUP = G;
     static constexpr int WAVES = W;  // wavefronts per parameter vector
-    static constexpr bool GCD = kc_gcd(KC);
+    static constexpr bool GCD = kc_gcd(KC), POWEXP = kc_family(KC) == 3;
     static constexpr int WPE = VECCHIA_WPE_OVERRIDE > 0
                                    ? VECCHIA_WPE_OVERRIDE
-                                   : tile_waves_per_simd(T, W, GRAD && keep_dbeta(T, W, GCD), GRAD, GCD, G);
-    static size_t smem(int) { return TileLds<T, W, GRAD, GCD, G, kc_family(KC) == 3>::BYTES; }
+                                   : tile_waves_per_simd(T, W, GRAD && keep_dbeta(T, W, GCD, POWEXP), GRAD, GCD, G, POWEXP);
+    using Lds = TileLds<T, W, GRAD, GCD, G, POWEXP>;
+    static_assert(VECCHIA_WPE_OVERRIDE > 0 || WPE == 1 || (WPE - 1) * 4 / (W * G) < (int)(163840 / Lds::BYTES),
+                  "the LDS holds fewer workgroups than the registers are limited for");
+    static size_t smem(int) { return Lds::BYTES; }
     static __device__ __forceinline__ CondOut run(const double *locs, const double *z, const int32_t *nbr, int64_t i,
                                                   int64_t n, int32_t m, const double *qloc, const Params &P,
                                                   double *sm) {
