@@ -162,9 +162,12 @@ __device__ __forceinline__ int32_t block_exclusive_scan(int32_t v, int32_t *sh, 
 }
 
 // Level 2: every chunk scanned in order from its offset, the sum of the chunks
-// before it (which every block adds up for itself: fewer than a hundred at the
-// sizes of a field, where a kernel for it cost its launch).  Thread t owns the
-// kScanPerThread consecutive elements starting at t * kScanPerThread.
+// before it, which every block adds up for itself: one load a thread up to 256
+// chunks, a million elements, where a kernel for the sums cost its launch.  The
+// loads grow with the square of the count, yet up to 10^9 keys (125,000 chunks
+// a pass) they do not show: random order of 10^9 points 153.5 ms, 154.1 with a
+// scan of the sums in a kernel of its own.  Thread t owns the kScanPerThread
+// consecutive elements starting at t * kScanPerThread.
 __global__ void __launch_bounds__(kScanThreads) scan_chunks_kernel(const int32_t *__restrict__ in, int64_t n,
                                                                    const int32_t *__restrict__ sums,
                                                                    int32_t *__restrict__ out) {
