@@ -43,20 +43,50 @@ __host__ __device__ constexpr bool rows_keep_dbeta(int T) { return T <= 2; }
 __host__ __device__ constexpr bool rows_stash(int T, bool grad) { return grad && T == 4; }
 __host__ __device__ constexpr bool rows_stash_tile(int T, int R, int C) { return R < T - 2 || (R == T - 2 && C == 0); }
 
-// LDS of one wavefront, in doubles: everything is per row group.
-template <int T, bool GRAD, bool GCD>
+// What the four row groups of a wavefront hold.
+//   kRowsItems4  four items;
+//   kRowsShare   one point under four parameter vectors.  Each group evaluates
+//                the distances of every fourth column, or round of the
+//                contraction, and the others take them through the LDS
+//                crossbar, which is idle: a Matern evaluation is 14
+//                instructions of distance and 16 to 19 of covariance;
+//   kRowsSolo    one item, for launches that leave most of the GPU idle
+//                (rows_solo).  The covariances and their derivatives are
+//                shared as the distances are above, a quarter of the
+//                evaluations in a chain that a wavefront works through by
+//                itself; the groups repeat the factorisation.  (Two items, in
+//                two groups each, gained nothing between the two.)
+// An item's arithmetic and its order are the same in all of them, so its
+// results are the same bits.
+enum RowsMode { kRowsItems4, kRowsShare, kRowsSolo };
+__host__ __device__ constexpr int rows_groups(RowsMode mode) { return mode == kRowsSolo ? 4 : 1; }
+
+// Whether kRowsSolo keeps the block in LDS for the back substitution: with the
+// gradient from three tile rows on, where the other modes transpose tile after
+// tile or stash them, and evaluate dC/dbeta again.  One matrix per wavefront
+// takes the factor in its lower half and dC/dbeta in the upper, as they come.
+__host__ __device__ constexpr bool rows_matrix(int T, bool grad, RowsMode mode) {
+    return mode == kRowsSolo && grad && !rows_keep_dbeta(T);
+}
+
+// LDS of one wavefront, in doubles: everything is per item (whose row groups
+// write alike).
+template <int T, bool GRAD, bool GCD, RowsMode MODE>
 struct RowsLds {
     static constexpr int KP = 16 * T;
+    static constexpr int NG = 4 / rows_groups(MODE);
+    static constexpr bool MATRIX = rows_matrix(T, GRAD, MODE);
     static constexpr int TS = 16 * 17;                      // one tile, row stride 17
-    static constexpr int XY = 0;                            // [4][KP][2] coordinates
-    static constexpr int ZV = XY + 8 * KP;                  // [4][KP]    observations
-    static constexpr int CL = ZV + 4 * KP;                  // [4][KP]    cos(latitude) (great-circle codes only)
-    static constexpr int YP = CL + (GCD ? 4 * KP : 0);      // [4][KP]    zeros, later factor row k+1
-    static constexpr int SCAL = YP + 4 * KP;                // [4][2]     L_kk, y_k
-    static constexpr int BUF = SCAL + 8;                    // [4][TS]    tile being transposed (gradient)
-    static constexpr int UB = BUF;                          // [4][KP][2] solutions (u, b), once no tile is left
-    static constexpr int TOTAL = BUF + (GRAD ? 4 * TS : 0);
-    static_assert(8 * KP <= 4 * TS, "the solutions fit in the tile buffer");
+    static constexpr int LD = KP + 2;                       // row stride of the matrix
+    static constexpr int XY = 0;                            // [NG][KP][2] coordinates
+    static constexpr int ZV = XY + NG * 2 * KP;             // [NG][KP]    observations
+    static constexpr int CL = ZV + NG * KP;                 // [NG][KP]    cos(latitude) (great-circle codes only)
+    static constexpr int YP = CL + (GCD ? NG * KP : 0);     // [NG][KP]    zeros, later factor row k+1
+    static constexpr int SCAL = YP + NG * KP;               // [NG][2]     L_kk, y_k
+    static constexpr int BUF = SCAL + 2 * NG;               // [NG][TS]    tile being transposed (gradient), or the matrix
+    static constexpr int UB = BUF + (MATRIX ? KP * LD : 0); // [NG][KP][2] solutions (u, b), once no tile is left
+    static constexpr int TOTAL = MATRIX ? UB + 2 * KP : BUF + (GRAD ? NG * TS : 0);
+    static_assert(2 * KP <= TS, "the solutions fit in the tile buffer");
 };
 
 // v moved up N lanes within each row; the first N lanes get 0.
@@ -67,34 +97,32 @@ __device__ __forceinline__ double shift_up(double v) {
     return __hiloint2double(hi, lo);
 }
 
-// v of lane j of row group G, in lane j of every row group.
+// v of lane j of the G-th row group from the one whose lane j is lane first / 4.
 template <int G>
-__device__ __forceinline__ double from_group(double v, int j4) {
-    const int lo = __builtin_amdgcn_ds_bpermute(j4 + 64 * G, (int)__double2loint(v));
-    const int hi = __builtin_amdgcn_ds_bpermute(j4 + 64 * G, (int)__double2hiint(v));
+__device__ __forceinline__ double from_group(double v, int first) {
+    const int lo = __builtin_amdgcn_ds_bpermute(first + 64 * G, (int)__double2loint(v));
+    const int hi = __builtin_amdgcn_ds_bpermute(first + 64 * G, (int)__double2hiint(v));
     return __hiloint2double(hi, lo);
 }
 
 // One conditional per row group (modes as lds_conditional); `active` is false
 // in groups without an item, which compute on an empty set.  Results are
 // valid in every lane of the group.
-//
-// SHARE: the row groups hold one point under four parameter vectors.  Each
-// evaluates the distances of every fourth column, or round of the
-// contraction, and the others take them through the LDS crossbar, which is
-// idle: a Matern evaluation is 14 instructions of distance and 14 to 17 of
-// covariance.
-template <int T, int KC, bool GRAD, bool SHARE>
+template <int T, int KC, bool GRAD, RowsMode MODE>
 __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ locs, const double *__restrict__ z,
                                                     const int32_t *__restrict__ nbr, int64_t i, int64_t n, int32_t m,
                                                     const double *qloc, const Params &P, bool active,
                                                     LdsTab ET, double *smem) {
-    constexpr bool GCD = kc_gcd(KC);
-    using Ls = RowsLds<T, GRAD, GCD>;
+    constexpr bool GCD = kc_gcd(KC), SHARE = MODE == kRowsShare;
+    constexpr int GPI = rows_groups(MODE);  // row groups per item
+    constexpr bool SPLIT = GPI > 1;
+    using Ls = RowsLds<T, GRAD, GCD, MODE>;
     constexpr int KP = Ls::KP;
     constexpr int NT = T * (T + 1) / 2;
     constexpr bool KEEP = GRAD && rows_keep_dbeta(T);
-    constexpr bool STASH = rows_stash(T, GRAD);
+    constexpr bool MATRIX = Ls::MATRIX;
+    constexpr bool STASH = rows_stash(T, GRAD) && !MATRIX;
+    constexpr int LD = Ls::LD;
     const int l = threadIdx.x % kWave;
     const int g = l / 16, j = l % 16;
     const int64_t lim = qloc ? n : i;
@@ -107,12 +135,14 @@ __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ l
         kmin = min(kmin, kq);
         kmax = max(kmax, kq);
     }
-    double *XY = smem + Ls::XY + g * 2 * KP;
-    double *Z = smem + Ls::ZV + g * KP;
-    double *CLv = smem + Ls::CL + g * KP;
-    double *YP = smem + Ls::YP + g * KP;
-    double *SC = smem + Ls::SCAL + 2 * g;
-    double *BUF = smem + Ls::BUF + g * Ls::TS;
+    const int gl = g / GPI, sub = g % GPI;  // the item within the wavefront, the group within the item
+    double *XY = smem + Ls::XY + gl * 2 * KP;
+    double *Z = smem + Ls::ZV + gl * KP;
+    double *CLv = smem + Ls::CL + gl * KP;
+    double *YP = smem + Ls::YP + gl * KP;
+    double *SC = smem + Ls::SCAL + 2 * gl;
+    double *BUF = smem + Ls::BUF + gl * Ls::TS;
+    double *M = smem + Ls::BUF;  // MATRIX: L[a][b] at M[a LD + b], dC/dbeta of points a > b at M[b LD + a]
 
     // gather, as in the tiled kernel: a bad index or a non-finite input makes
     // the row's observation NaN
@@ -168,7 +198,7 @@ __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ l
     // (j + 16 - c, 16 - c)) and a lane shift moves the second into place; with
     // zeros shifted in, dC/dbeta of the tile is its strictly lower half.
     const CovConst CC = cov_const<true>();
-    const int j4 = 4 * j;
+    const int j4 = 4 * (j + 16 * (SPLIT ? g - sub : 0));  // lane j of the first group that shares with this one
     double A[NT][16], D[KEEP ? NT : 1][16];
     auto tix = [](int R, int C) constexpr { return R * (R + 1) / 2 + C; };
     const double diag = P.sigma2 + P.tau2;
@@ -189,22 +219,25 @@ __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ l
     // diagonal tile C the same way, ready for substitution: register r > n of
     // lane n is -L[r][n] / L[n][n], register 0 is 1 / L[n][n] (0 past row k),
     // the rest are 0
-    auto transpose_diag = [&](const double (&src)[16], int C, double (&dst)[16]) __attribute__((always_inline)) {
-        wave_lds_sync();
-#pragma unroll
-        for (int c = 0; c < 16; ++c) BUF[j * 17 + c] = src[c];
-        wave_lds_sync();
-        const double dn = BUF[j * 17 + j];
+    auto diag_weights = [&](const double *tile, int stride, int C, double (&dst)[16]) __attribute__((always_inline)) {
+        const double dn = tile[j * stride + j];
         double inv = __builtin_amdgcn_rcp(dn);
         inv = fma(fma(-dn, inv, 1.0), inv, inv);
         inv = fma(fma(-dn, inv, 1.0), inv, inv);
         inv = (16 * C + j <= k) ? inv : 0.0;
 #pragma unroll
         for (int r = 1; r < 16; ++r) {
-            const double v = BUF[r * 17 + j];
+            const double v = tile[r * stride + j];
             dst[r] = (r > j) ? -(v * inv) : 0.0;
         }
         dst[0] = inv;
+    };
+    auto transpose_diag = [&](const double (&src)[16], int C, double (&dst)[16]) __attribute__((always_inline)) {
+        wave_lds_sync();
+#pragma unroll
+        for (int c = 0; c < 16; ++c) BUF[j * 17 + c] = src[c];
+        wave_lds_sync();
+        diag_weights(BUF, 17, C, dst);
     };
     // the part of factor row k + 1 that lies in tile row R, from its lane
     auto keep_observation_row = [&](auto Rc) __attribute__((always_inline)) {
@@ -243,30 +276,54 @@ __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ l
                 return pair_dist_pow<KC>(px[R], py[R], GCD ? pc[R] : 0.0, pb.x, pb.y, GCD ? CLv[16 * C + c] : 0.0, P,
                                          ET, CC);
             };
-            double shared = 0.0;
+            double shared = 0.0, shared_v = 0.0, shared_d = 0.0;
+            // covariance and derivative at distance da
+            auto evaluate = [&](double da, double inv_beta, double &v, double &d) __attribute__((always_inline)) {
+                const double rs = scaled_dist(da, inv_beta, CC);
+                const double e = exp_neg_staged(rs, ET, CC);
+                v = cov_value<KC>(rs, e, P);
+                if constexpr (KEEP || MATRIX) d = dbeta_raw<KC>(rs, e);
+            };
+            // of column c of the tile whose column's distance is dist(c): this
+            // group's share of the columns from c, or the column itself;
+            // put(c) takes the lane's derivative to the matrix
+            auto column = [&](auto cc, auto &&dist, auto &&put, double inv_beta, double &v, double &d)
+                __attribute__((always_inline)) {
+                constexpr int c = decltype(cc)::value;
+                if constexpr (SPLIT) {
+                    if constexpr (c % GPI == 0) {
+                        evaluate(dist(c + sub), inv_beta, shared_v, shared_d);
+                        if constexpr (MATRIX) put(c + sub, shared_d);
+                    }
+                    v = from_group<c % GPI>(shared_v, j4);
+                    if constexpr (KEEP) d = from_group<c % GPI>(shared_d, j4);
+                } else if constexpr (SHARE) {
+                    if constexpr (c % 4 == 0) shared = dist(c + g);
+                    evaluate(from_group<c % 4>(shared, j4), inv_beta, v, d);
+                } else {
+                    evaluate(dist(cc), inv_beta, v, d);
+                }
+            };
+            auto diag_put = [&](int c, double d) __attribute__((always_inline)) {
+                const bool low = j >= c;
+                const int row = low ? j : j + 16 - c, col = low ? c : 16 - c;
+                if (row > col) M[(16 * C + col) * LD + 16 * C + row] = d;
+            };
             static_for<0, 9>([&](auto cc) {
                 constexpr int c = decltype(cc)::value;
                 constexpr bool two = c > 0 && c < 8;
                 if (16 * C + c <= kmax) {
-                    double da;
-                    if constexpr (SHARE && c < 8) {
-                        if constexpr (c % 4 == 0) shared = diag_dist(c + g);
-                        da = from_group<c % 4>(shared, j4);
-                    } else if constexpr (two) {
-                        da = diag_dist(cc);
-                    } else {
-                        da = column_dist(Cc, cc);
-                    }
-                    const double rs = scaled_dist(da, KEEP && two ? inv_beta_two : P.inv_beta, CC);
-                    const double e = exp_neg_staged(rs, ET, CC);
-                    const double v = cov_value<KC>(rs, e, P);
+                    double v, d;
+                    const double inv_beta = KEEP && (two || (SPLIT && c < 8)) ? inv_beta_two : P.inv_beta;
+                    if constexpr (c < 8 && (two || SHARE || SPLIT)) column(cc, diag_dist, diag_put, inv_beta, v, d);
+                    else evaluate(column_dist(Cc, cc), inv_beta, v, d);
+                    if constexpr (MATRIX && c == 8) diag_put(c, d);
                     A[tix(C, C)][c] = (j == c) ? diag : v;
                     if constexpr (two) {
                         const double w = shift_up<16 - c>(v);
                         A[tix(C, C)][16 - c] = (j == 16 - c) ? diag : w;
                     }
                     if constexpr (KEEP) {
-                        const double d = dbeta_raw<KC>(rs, e);
                         D[tix(C, C)][c] = (j > c) ? d : 0.0;
                         // lane 16 - c receives its own column's diagonal from lane 0, exactly 0
                         if constexpr (two) D[tix(C, C)][16 - c] = shift_up<16 - c>(d);
@@ -284,17 +341,13 @@ __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ l
                 constexpr int R = decltype(Rc)::value;
                 static_for<0, 16>([&](auto cc) {
                     constexpr int c = decltype(cc)::value;
-                    double da;
-                    if constexpr (SHARE) {
-                        if constexpr (c % 4 == 0) shared = column_dist(Rc, c + g);
-                        da = from_group<c % 4>(shared, j4);
-                    } else {
-                        da = column_dist(Rc, cc);
-                    }
-                    const double rs = scaled_dist(da, P.inv_beta, CC);
-                    const double e = exp_neg_staged(rs, ET, CC);
-                    A[tix(R, C)][c] = cov_value<KC>(rs, e, P);
-                    if constexpr (KEEP) D[tix(R, C)][c] = dbeta_raw<KC>(rs, e);
+                    double v, d;
+                    column(
+                        cc, [&](auto x) __attribute__((always_inline)) { return column_dist(Rc, x); },
+                        [&](int x, double dx) __attribute__((always_inline)) { M[(16 * C + x) * LD + 16 * R + j] = dx; },
+                        P.inv_beta, v, d);
+                    A[tix(R, C)][c] = v;
+                    if constexpr (KEEP) D[tix(R, C)][c] = d;
                 });
             });
         } else {
@@ -364,6 +417,21 @@ __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ l
                 });
             }
         });
+        if constexpr (MATRIX) {
+            static_for<C, T>([&](auto Rc) {
+                constexpr int R = decltype(Rc)::value;
+                double *row = M + (16 * R + j) * LD + 16 * C;
+                if constexpr (R > C) {
+#pragma unroll
+                    for (int c = 0; c < 16; c += 2)
+                        *reinterpret_cast<double2 *>(row + c) = make_double2(A[tix(R, C)][c], A[tix(R, C)][c + 1]);
+                } else {  // the derivative lies above the diagonal
+#pragma unroll
+                    for (int c = 0; c < 16; ++c)
+                        if (j >= c) row[c] = A[tix(R, C)][c];
+                }
+            });
+        }
         if constexpr (STASH && C + 1 < T) {
             if (16 * C + 15 >= kmin) keep_observation_row(std::integral_constant<int, C>{});
             static_for<0, C + 1>([&](auto Ec) {
@@ -381,7 +449,7 @@ __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ l
     // L_kk sits in the lane of row k, y_k in the lane of row k + 1
     if (j == k % 16) SC[0] = Lk;
     if (j == (k + 1) % 16) SC[1] = yk;
-    if constexpr (GRAD) static_for<STASH ? T - 1 : 0, T>(keep_observation_row);
+    if constexpr (GRAD && !MATRIX) static_for<STASH ? T - 1 : 0, T>(keep_observation_row);
     wave_lds_sync();
     CondOut o;
     const double Lkk = SC[0], wv = SC[1];
@@ -394,10 +462,11 @@ __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ l
         // back substitution with L^T for both right-hand sides (the tiled
         // kernel's): lane n holds entry n of each block
         double xu[T], xb[T];
+        const double *Y = MATRIX ? M + (k + 1) * LD : YP;  // the observation row of the factor
         for_columns<true, T - 1, -1, -1>([&](auto Cc) __attribute__((always_inline)) {
             constexpr int C = decltype(Cc)::value;
             const int row = 16 * C + j;
-            double qu = (row < k) ? rr * YP[row] : (row == k ? half * Lkk : 0.0);
+            double qu = (row < k) ? rr * Y[row] : (row == k ? half * Lkk : 0.0);
             double qb = (row == k) ? Lkk : 0.0;
             double Lt[16];
             static_for<C + 1, T>([&](auto Rc) {
@@ -406,6 +475,9 @@ __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ l
                     if constexpr (STASH && rows_stash_tile(T, R, C)) {
 #pragma unroll
                         for (int r = 0; r < 16; ++r) Lt[r] = stash[16 * tix(R, C) + r];
+                    } else if constexpr (MATRIX) {
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) Lt[r] = M[(16 * R + r) * LD + 16 * C + j];
                     } else {
                         transpose(A[tix(R, C)], Lt);
                     }
@@ -419,6 +491,8 @@ __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ l
             if constexpr (STASH && rows_stash_tile(T, C, C)) {
 #pragma unroll
                 for (int r = 0; r < 16; ++r) Lt[r] = stash[16 * tix(C, C) + r];
+            } else if constexpr (MATRIX) {
+                diag_weights(M + 16 * C * (LD + 1), LD, C, Lt);
             } else {
                 transpose_diag(A[tix(C, C)], C, Lt);
             }
@@ -454,7 +528,7 @@ __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ l
         } else {
             // D again over the N (N - 1) / 2 pairs of the N = k + 1 points, as
             // in the tiled kernel, 16 to a round
-            double *UB = smem + Ls::UB + g * 2 * KP;
+            double *UB = smem + Ls::UB + gl * 2 * KP;
             static_for<0, T>([&](auto Rc) {
                 constexpr int R = decltype(Rc)::value;
                 UB[2 * (16 * R + j)] = xu[R];
@@ -488,14 +562,40 @@ __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ l
                 return pair_dist_pow<KC>(xa.x, xa.y, GCD ? CLv[p.a / 16] : 0.0, xc.x, xc.y, GCD ? CLv[p.b / 16] : 0.0,
                                          P, ET, CC);
             };
-            auto add_pair = [&](double da) __attribute__((always_inline)) {
+            auto pair_dbeta = [&](double da) __attribute__((always_inline)) {
                 const double rs = scaled_dist(da, P.inv_beta, CC);
-                const double d = dbeta_raw<KC>(rs, exp_neg_staged(rs, ET, CC));
-                const double2 ua = *reinterpret_cast<const double2 *>(UBb + w.a);
-                const double2 vb = *reinterpret_cast<const double2 *>(UBb + w.b);
-                gb = fma(d, fma(ua.x, vb.y, vb.x * ua.y), gb);
+                return dbeta_raw<KC>(rs, exp_neg_staged(rs, ET, CC));
             };
-            if constexpr (SHARE) {
+            auto pair_weight = [&](const Walk &p) __attribute__((always_inline)) {
+                const double2 ua = *reinterpret_cast<const double2 *>(UBb + p.a);
+                const double2 vb = *reinterpret_cast<const double2 *>(UBb + p.b);
+                return fma(ua.x, vb.y, vb.x * ua.y);
+            };
+            auto add_pair = [&](double da) __attribute__((always_inline)) {
+                const double d = pair_dbeta(da);
+                gb = fma(d, pair_weight(w), gb);
+            };
+            if constexpr (SPLIT) {
+                constexpr int STEP = 16 * GPI;
+                Walk own(N, 16 * sub + j, STEP);  // the pairs this lane evaluates, any of the set past the last item
+                const uint32_t NPmax = ((uint32_t)kmax + 1) * (uint32_t)kmax / 2;
+                for (uint32_t p = 0; p < NPmax; p += STEP) {
+                    double d;
+                    if constexpr (MATRIX) {
+                        const uint32_t low = min(own.a, own.b), high = max(own.a, own.b);
+                        d = M[(low / 16) * LD + high / 16];
+                    } else {
+                        d = pair_dbeta(pair_dist(own));
+                    }
+                    const double u = pair_weight(own);
+                    own.next();
+                    static_for<0, GPI>([&](auto sc) {
+                        constexpr int q = decltype(sc)::value;
+                        const double dq = from_group<q>(d, j4), uq = from_group<q>(u, j4);
+                        gb = p + 16 * q + j < NP ? fma(dq, uq, gb) : gb;
+                    });
+                }
+            } else if constexpr (SHARE) {
                 Walk own(N, 16 * g + j, 64);  // the pairs whose distance this lane evaluates
                 uint32_t p = 0;
                 for (; p + 64 <= NP; p += 64) {
@@ -516,11 +616,26 @@ __device__ __forceinline__ CondOut rows_conditional(const double *__restrict__ l
             } else {
                 const uint32_t whole = ((uint32_t)kmin + 1) * (uint32_t)kmin / 32;  // rounds every lane takes part in
                 const uint32_t rounds = (((uint32_t)kmax + 1) * (uint32_t)kmax / 2 + 15) / 16;
-                for (uint32_t c = 0; c < whole; ++c) {
+                // four rounds at a time, each step's loads and chains in flight
+                // together (m = 60, 2,000 points: 66.9 us one by one, 63.2 so; m =
+                // 45, 100,000 points 512 and 486)
+                constexpr int NB = 4;
+                uint32_t c = 0;
+                for (; c + NB <= whole; c += NB) {
+                    double d[NB], u[NB];
+                    static_for<0, NB>([&](auto x) {
+                        d[x] = pair_dist(w);
+                        u[x] = pair_weight(w);
+                        w.next();
+                    });
+                    static_for<0, NB>([&](auto x) { d[x] = pair_dbeta(d[x]); });
+                    static_for<0, NB>([&](auto x) { gb = fma(d[x], u[x], gb); });
+                }
+                for (; c < whole; ++c) {
                     add_pair(pair_dist(w));
                     w.next();
                 }
-                for (uint32_t c = whole; c < rounds; ++c) {
+                for (c = whole; c < rounds; ++c) {
                     if (16 * c + j < NP) add_pair(pair_dist(w));
                     w.next();
                 }

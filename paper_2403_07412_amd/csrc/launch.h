@@ -249,13 +249,14 @@ __global__ void __launch_bounds__(Impl::NT) __attribute__((amdgpu_waves_per_eu(I
     cond_item_group<Impl>(a, a.t0 + (int64_t)Impl::GROUP * blockIdx.x, smem);
 }
 
-// Rows kernel: wavefronts of four conditionals, kRowsWaves to a workgroup
-// (they share the staged exponential table).  Item t of KernelArgs is row
-// group (t - t0) % 4 of wavefront (t - t0) / 4, for t < t_end.  SHARE (plans of
-// parameter vectors in groups of four): the four items of a wavefront are one
-// point's, which then works with placeholder parameters under an invalid vector.
+// Rows kernel: wavefronts of four conditionals (kRowsSolo one),
+// kRowsWaves to a workgroup (they share the staged exponential table).  The
+// items of KernelArgs from t0 to t_end lie in the row groups in order, each in
+// rows_groups(MODE) of them.  kRowsShare (plans of parameter vectors in groups of four): the four
+// items of a wavefront are one point's, which then works with placeholder
+// parameters under an invalid vector.
 constexpr int kRowsWaves = 4;
-constexpr int kRowsItems = 4 * kRowsWaves;  // items per workgroup
+__host__ __device__ constexpr int rows_items(RowsMode mode) { return 4 / rows_groups(mode) * kRowsWaves; }  // per workgroup
 
 template <int T, int KC, bool GRAD>
 struct RowsImpl {
@@ -267,10 +268,12 @@ struct RowsImpl {
     // Matern 3/2 0.439 and 0.476)
     static constexpr int WPE =
         GRAD ? (T == 1 ? 4 : 2) : (T == 1 ? 5 : T == 2 ? (KC < 3 ? 4 : 3) : T == 3 ? 3 : 2);
-    static constexpr size_t SMEM = (kRowsWaves * RowsLds<T, GRAD, kc_gcd(KC)>::TOTAL + staged_doubles(kc_family(KC) == 3)) * sizeof(double);
+    template <RowsMode MODE>
+    static constexpr size_t SMEM =
+        (kRowsWaves * RowsLds<T, GRAD, kc_gcd(KC), MODE>::TOTAL + staged_doubles(kc_family(KC) == 3)) * sizeof(double);
 };
 
-template <int T, int KC, bool GRAD, bool SHARE>
+template <int T, int KC, bool GRAD, RowsMode MODE>
 __global__ void __launch_bounds__(kRowsWaves *kWave)
     __attribute__((amdgpu_waves_per_eu(RowsImpl<T, KC, GRAD>::WPE)))
     rows_kernel(const KernelArgs a, int64_t t_end) {
@@ -280,7 +283,9 @@ __global__ void __launch_bounds__(kRowsWaves *kWave)
     stage_tables<KC>((int)threadIdx.x, ET);
     __syncthreads();
     const int wave = threadIdx.x / kWave, g = (threadIdx.x % kWave) / 16;
-    const int64_t t = a.t0 + (int64_t)kRowsItems * blockIdx.x + 4 * wave + g;
+    constexpr bool SHARE = MODE == kRowsShare;
+    constexpr int GPI = rows_groups(MODE);
+    const int64_t t = a.t0 + (int64_t)rows_items(MODE) * blockIdx.x + (4 * wave + g) / GPI;
     const bool mine = t < t_end;
     const double *locs = a.locs, *z = a.z, *theta = a.theta;
     const int32_t *nbr = a.nbr;
@@ -318,12 +323,12 @@ __global__ void __launch_bounds__(kRowsWaves *kWave)
     }
     const bool pred = a.qlocs != nullptr;
     const bool run = mine && (SHARE || valid) && i >= 0 && i < (pred ? a.nq : n);
-    CondOut o = rows_conditional<T, KC, GRAD, SHARE>(locs, z, nbr, run ? i : 0, n, m, pred ? a.qlocs + 2 * (run ? i : 0) : nullptr,
+    CondOut o = rows_conditional<T, KC, GRAD, MODE>(locs, z, nbr, run ? i : 0, n, m, pred ? a.qlocs + 2 * (run ? i : 0) : nullptr,
                                               P, run, lds_table(ET),
-                                              smem + staged_doubles(kc_family(KC) == 3) + wave * RowsLds<T, GRAD, kc_gcd(KC)>::TOTAL);
+                                              smem + staged_doubles(kc_family(KC) == 3) + wave * RowsLds<T, GRAD, kc_gcd(KC), MODE>::TOTAL);
     const bool bad = o.bad || !run || !valid;
     if (bad) o.ell = o.g0 = o.g1 = o.g2 = o.mean = o.var = __builtin_nan("");
-    if (mine && threadIdx.x % 16 == 0) {
+    if (mine && threadIdx.x % (16 * GPI) == 0) {
         if (pred) {
             a.pmean[row] = o.mean;
             a.pvar[row] = o.var;
@@ -386,23 +391,49 @@ int launch_group_impl(const EvalArgs &a, hipStream_t s) {
     return hipGetLastError() == hipSuccess ? VECCHIA_OK : VECCHIA_EHIP;
 }
 
+// Items up to which a launch gives every item a wavefront of its own (0: never).
+// 1,024 put one on every SIMD; a second one there waits for the first, except
+// where evaluations, of which it does a quarter, are most of its work: the
+// power exponential breaks even at two, great-circle codes at three.  One tile row of
+// Matern on Euclidean distances gains nothing.  Four items to a wavefront, and one,
+// us per call:
+//   Matern 3/2, value      m = 60: n = 300 40.4, 33.3; 1,500 42.0, 44.5
+//     value + gradient     m = 60: n = 300 65.2, 48.0; 1,000 66.6, 48.4; 1,500 64, 85
+//                          m = 45: n = 300 41.2, 34.1      m = 30: 23.2, 21.8
+//   power exponential, value + gradient, m = 30: n = 300 29.7, 24.0; 2,000 29.6, 28.2; 2,500 30.9, 38.3
+//   great circle, Matern 3/2 + gradient, m = 30: n = 300 51.5, 28.1; 3,000 48.2, 47.1; 4,000 48.1, 54.7
+__host__ __device__ constexpr int64_t rows_solo(int T, int KC) {
+    return KC < 3 ? (T > 1 ? 1024 : 0) : KC == 3 ? 2048 : 3072;
+}
+
+template <int T, int KC, bool GRAD, RowsMode MODE>
+int launch_rows_mode(const EvalArgs &a, hipStream_t s) {
+    constexpr size_t smem = RowsImpl<T, KC, GRAD>::template SMEM<MODE>;
+    static_assert(smem <= 163840, "a workgroup fits the LDS");
+    constexpr int kItems = rows_items(MODE);
+    auto kern = rows_kernel<T, KC, GRAD, MODE>;
+    if (allow_smem(kern, smem) != hipSuccess) return VECCHIA_EHIP;
+    constexpr int64_t kMaxGrid = (int64_t)1 << 22;
+    for (int64_t t0 = a.t_begin; t0 < a.t_end; t0 += kMaxGrid * kItems) {
+        const int64_t grid = std::min<int64_t>((a.t_end - t0 + kItems - 1) / kItems, kMaxGrid);
+        KernelArgs k = a.k;
+        k.t0 = t0;
+        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(RowsImpl<T, KC, GRAD>::NT), smem, s, k,
+                           std::min<int64_t>(a.t_end, t0 + grid * kItems));
+    }
+    return hipGetLastError() == hipSuccess ? VECCHIA_OK : VECCHIA_EHIP;
+}
+
 // group > 1: the parameter vectors of a point come in groups of four
 // consecutive items.
 template <int T, int KC, bool GRAD>
 int launch_rows(const EvalArgs &a, hipStream_t s) {
     if (a.t_end <= a.t_begin) return VECCHIA_OK;
-    constexpr size_t smem = RowsImpl<T, KC, GRAD>::SMEM;
-    auto kern = a.group > 1 ? rows_kernel<T, KC, GRAD, true> : rows_kernel<T, KC, GRAD, false>;
-    if (allow_smem(kern, smem) != hipSuccess) return VECCHIA_EHIP;
-    constexpr int64_t kMaxGrid = (int64_t)1 << 22;
-    for (int64_t t0 = a.t_begin; t0 < a.t_end; t0 += kMaxGrid * kRowsItems) {
-        const int64_t grid = std::min<int64_t>((a.t_end - t0 + kRowsItems - 1) / kRowsItems, kMaxGrid);
-        KernelArgs k = a.k;
-        k.t0 = t0;
-        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(RowsImpl<T, KC, GRAD>::NT), smem, s, k,
-                           std::min<int64_t>(a.t_end, t0 + grid * kRowsItems));
+    if constexpr (rows_solo(T, KC) > 0) {
+        if (a.t_end - a.t_begin <= rows_solo(T, KC)) return launch_rows_mode<T, KC, GRAD, kRowsSolo>(a, s);
     }
-    return hipGetLastError() == hipSuccess ? VECCHIA_OK : VECCHIA_EHIP;
+    if (a.group > 1) return launch_rows_mode<T, KC, GRAD, kRowsShare>(a, s);
+    return launch_rows_mode<T, KC, GRAD, kRowsItems4>(a, s);
 }
 
 // Kernel variants.  The tiled family is instantiated for T = ceil((m+2)/16)
@@ -435,8 +466,8 @@ inline int variant_waves(int variant) {
 //   value, gradient  m = 10: 0.180, 0.078   30: 0.361, 0.213   40: 0.729, 0.462   60: 1.239, 0.962
 // The rule does not look at the number of points, so that a field gives the
 // same bits alone and in a plan, nor at the gradient, so that the value is the
-// same with and without it; a launch too small to fill the GPU waits longer
-// for one wavefront of four (2,000 points, m = 30: 26 against 24 us).
+// same with and without it; small launches of the rows kernel spread out
+// (rows_solo).
 __host__ __device__ constexpr bool rows_shape(int T, int W, int KC) { return W == 1 && T <= (KC < 3 ? 4 : 2); }
 
 // register budget: at most 20 tiles per wavefront
