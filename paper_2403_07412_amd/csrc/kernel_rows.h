@@ -13,7 +13,7 @@
 // an FMA with a broadcast operand does as much work per cycle as the matrix
 // product.  The tiled kernel's wavefront factors one diagonal tile at a time,
 // all four row groups repeating it (380 issue slots); here the same slots
-// factor four (m = 30, value: 815 vector instructions per conditional for
+// factor four (m = 30, value: 636 vector instructions per conditional for
 // about 1800).  The registers set the limit: 32 per tile and lane.
 //
 // Gradient: back substitution needs columns of the factor in lanes; each tile

@@ -27,12 +27,14 @@
 //      tile lives in lane c of every 16-lane row, so each step is one DPP
 //      broadcast FMA per register), and publish X to LDS in T-layout;
 //   3. the owners of the trailing tiles subtract X_R X_C^T (4 MFMAs per
-//      tile), the next diagonal tile first, so that its factorisation
-//      overlaps the other updates of the column.
+//      tile), in the order of their slots: column t + 1, the next diagonal
+//      tile with it, comes last, and the other waves wait for its
+//      factorisation.
 // Gradient: back substitution with L^T by columns of tiles: the sums of
 // L_Rt^T x_R over the tiles below diagonal tile t on the vector units (every
-// wave its own tiles), then x_t by substitution (one wave).  No step multiplies by an explicit inverse, so every
-// solve is backward stable, as in the unblocked kernel.
+// wave its own tiles), then x_t by substitution (one wave).  No step
+// multiplies by an explicit inverse, so every solve is backward stable, as in
+// the unblocked kernel.
 #pragma once
 
 #include <type_traits>
@@ -124,6 +126,9 @@ __host__ __device__ constexpr int lockstep_group(int T, int W) { return (T <= 5 
 //   T = 4, W = 2 (m from 47 to 62; LDS leaves room only without the
 //     gradient): 2.82 ms at nine workgroups against 2.89 ms at eight for the
 //     same points at m = 60, value only.
+//   T = 8, W = 4, great circle: power exponential value + gradient 3.67 ms at four
+//     workgroups (two registers spilled) against 4.28 ms at three (129 VGPRs),
+//     Matern 3/2 3.09 against 3.63 ms, for 40,000 points, m = 124;
 //   T = 11, W = 4, great circle (m of 159 and 160): Matern 3/2 value + gradient
 //     3.91 ms at three workgroups against 4.65 ms at two, power exponential
 //     4.48 against 5.52 ms, for 20,000 points.
@@ -133,7 +138,7 @@ __host__ __device__ constexpr int lockstep_group(int T, int W) { return (T <= 5 
 // T = 7 and 9 with W = 4, T = 2 to 4 with W = 1 and T = 3, 5, 6 with W = 2
 // measured no faster one workgroup up.  Other shapes keep the estimate.
 __host__ __device__ constexpr bool tile_measured_raise(int T, int W, bool gcd) {
-    return ((T == 8 || T == 10) && W == 4 && !gcd) || (T == 4 && W == 2 && !gcd) || (T == 11 && W == 4 && gcd);
+    return (T == 8 && W == 4) || (T == 10 && W == 4 && !gcd) || (T == 4 && W == 2 && !gcd) || (T == 11 && W == 4 && gcd);
 }
 
 // Occupancy target (wavefronts per SIMD) the register allocation aims at.

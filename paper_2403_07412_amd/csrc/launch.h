@@ -495,13 +495,15 @@ inline bool variant_feasible(int variant, int m) {
 //          5          W1 0.79  W2 0.85  W4 0.76             W1 1.18  W4 1.22
 //          6          W2 1.24  W4 1.07                      W2 1.86  W4 1.81
 //         10          W4 1.91  W8 1.91                      W4 2.74  W8 2.90
-//   great circle, Matern 3/2 (power exponential)
-//     rows 3   value  W1 0.38 (0.44)  W2 0.40 (0.48)    gradient  W1 0.51 (0.58)  W2 0.56 (0.65)
-//          4          W1 0.58 (0.69)  W4 0.60 (0.68)              W1 0.76 (0.88)  W2 0.86 (1.02)
-//          5          W1 0.94 (1.28)  W4 0.87 (1.00)              W1 1.33 (1.89)  W4 1.29 (1.66)
-//          6          W2 1.35 (1.63)  W4 1.26 (1.48)              W2 2.00 (2.48)  W4 1.94 (2.30)
-//          8          W2 3.32 (3.62)  W4 2.48 (2.47)              (W2 6.01  W4 3.73)
-//         10          W4 2.59 (2.96)  W8 2.01 (2.25)              W4 3.87 (3.87)  W8 4.16 (4.52)
+//   great circle, Matern 3/2 (power exponential), m = 16 rows - 4 (eleven: 160)
+//     rows 3   value  W1 0.38 (0.44)  W2 0.40 (0.47)    gradient  W1 0.50 (0.57)  W2 0.57 (0.66)
+//          4          W1 0.59 (0.71)  W4 0.61 (0.69)              W1 0.76 (0.89)  W2 0.91 (1.08)
+//          5          W1 0.95 (1.13)  W4 0.88 (1.01)              W1 1.33 (1.65)  W4 1.31 (1.54)
+//          6          W2 1.34 (1.62)  W4 1.27 (1.48)              W2 1.98 (2.42)  W4 1.93 (2.30)
+//          7          W2 2.21 (2.66)  W4 1.61 (1.90)              W2 3.29 (4.07)  W4 2.47 (2.92)
+//          8          W2 2.91 (3.51)  W4 2.06 (2.42)              W2 4.46 (5.44)  W4 3.09 (3.67)
+//         10          W4 1.97 (2.26)  W8 1.94 (2.17)              W4 2.87 (3.45)  W8 3.96 (4.36)
+//         11          W4 2.58 (3.01)  W8 2.46 (2.76)              W4 3.76 (4.53)  W8 5.08 (5.54)
 inline int default_variant(int m, bool grad, int kc) {
     const int T = tile_rows(m);
     if (T <= 3) return V_TILE_W1;

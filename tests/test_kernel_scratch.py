@@ -61,3 +61,11 @@ def test_no_tiled_kernel_where_the_rows_kernel_runs():
               (re.search(r"TileImplILi(\d+)ELi(\d+)ELi(\d+)E", k[".name"]) for k in _kernels()) if m]
     assert shapes
     assert not [s for s in shapes if s[1] == 1 and s[0] <= (4 if s[2] < 3 else 2)]
+
+
+def test_eight_tile_rows_run_four_workgroups():
+    """Eight tile rows by four wavefronts: up to 128 registers hold four workgroups per compute unit, 129 three."""
+    if not os.path.exists(LIB):
+        pytest.skip("the library is not built")
+    regs = {k[".name"]: k[".vgpr_count"] for k in _kernels() if "TileImplILi8ELi4E" in k[".name"]}
+    assert len(regs) == 16 and max(regs.values()) <= 128, regs
