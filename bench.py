@@ -53,11 +53,11 @@ FP64_PEAK_TFLOPS = 78.6   # MI355X FP64 vector (and matrix) peak: 256 CU x 2.4 G
 # The record describes the kernel sources it was measured on only, so it is
 # reported when their digest still matches (kernel_sources_digest).
 MEASURED_TRAFFIC = {
-    "sources_sha256": "77aadbc982647fe27d303b7274167656f34f86cf9dd139ad52fbadc5e849e8c8",
+    "sources_sha256": "ae34b078e0684ee471e5eac7201af49e7f3889c29935752aca1e3f63ad09bde5",
     "workload": "n1M_m120_nu0.5", "variant": "tile_w4",
-    "fetch_kib_raw": 7981367.4792, "fetch_factor": 524288.0 / 262167.25,
-    "write_kib_raw": 62500.3021, "write_factor": 524288.0 / 524288.0,
-    "f64_add": 977972631.0, "f64_mul": 1719953929.0, "f64_fma": 7012844845.0, "f64_trans": 392990877.0,
+    "fetch_kib_raw": 7981194.3333, "fetch_factor": 524288.0 / 262168.75,
+    "write_kib_raw": 62500.1042, "write_factor": 524288.0 / 524288.0,
+    "f64_add": 949972631.0, "f64_mul": 1719953929.0, "f64_fma": 7270835722.0, "f64_trans": 392990877.0,
     "f64_mfma_mops": 1440000000.0,
 }
 
