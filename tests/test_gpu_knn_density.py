@@ -60,7 +60,7 @@ def test_a_dense_place_does_not_multiply_the_work(v):
         out = torch.empty((len(x), m), dtype=torch.int32, device="cuda")
         ws = torch.empty(v.vecchia_knn_workspace_size(len(x)), dtype=torch.uint8, device="cuda")
         times = []
-        for _ in range(6):
+        for _ in range(12):
             a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
             a.record()
             v.vecchia_knn(t, m, out=out, ws=ws)

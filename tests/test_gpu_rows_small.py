@@ -86,7 +86,7 @@ def test_small_launch_does_not_wait_for_one_wavefront(lib, cov, m):
             for _ in range(20):
                 lib.vecchia_loglik_cov(locs, z, nbr, m, cov, theta, with_grad=True, ws=ws)
         best = np.inf
-        for _ in range(8):
+        for _ in range(40):
             a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
             a.record()
             graph.replay()
